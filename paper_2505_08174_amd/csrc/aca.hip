@@ -112,44 +112,26 @@ __device__ __forceinline__ NT det3(const T* K) {
 // MFK = 2 FP32 tiles; fr is the matching fragment table in LDS.
 enum { MF_NONE = 0, MF_BF16 = 1, MF_F32 = 2 };
 
-// K(x_i - y_j) from NT independent MFMA MLP tiles: symmetrised 3x3 entries
-// of this lane's pair of each tile.
-template <int NT, int MFK>
-__device__ __forceinline__ void mfma_entries(const void* fr, int mode, const double (&d)[NT][3],
-                                             float (&K)[NT][9]) {
-  if constexpr (MFK == MF_F32) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) entry_f32tile((const float*)fr, mode, d[t][0], d[t][1], d[t][2], K[t]);
-    return;
-  }
-  float v[NT][3], rs[NT], o[NT][9];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const float rx = (float)d[t][0], ry = (float)d[t][1], rz = (float)d[t][2];
-    rs[t] = hh_rsqrt(rx * rx + ry * ry + rz * rz);
-    const float sc = mode == HH_MLP_INPUT_DIRECTION ? rs[t] : 1.0f;
-    v[t][0] = rx * sc;
-    v[t][1] = ry * sc;
-    v[t][2] = rz * sc;
-  }
-  mlp_tiles_bf16<true, NT>((const bf16x8*)fr, v, o);
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const float s = rs[t] * (float)(1.0 / (16.0 * HH_PI));
-    K[t][0] = 2.0f * o[t][0] * s; K[t][1] = (o[t][1] + o[t][3]) * s; K[t][2] = (o[t][2] + o[t][6]) * s;
-    K[t][3] = K[t][1];            K[t][4] = 2.0f * o[t][4] * s;       K[t][5] = (o[t][5] + o[t][7]) * s;
-    K[t][6] = K[t][2];            K[t][7] = K[t][5];                  K[t][8] = 2.0f * o[t][8] * s;
-  }
-}
-
-template <int MFK>
+// K(x_i - y_j) of this lane's pair from MFMA MLP tiles. PAIRS: 64 different
+// pairs, one per lane (two tiles); otherwise one tile of 32 pairs, lanes l and
+// l + 32 holding the same one.
+template <bool PAIRS, int MFK>
 __device__ __forceinline__ void mfma_entry(const void* fr, int mode, double dx, double dy,
                                            double dz, float K[9]) {
-  const double d[1][3] = {{dx, dy, dz}};
-  float k1[1][9];
-  mfma_entries<1, MFK>(fr, mode, d, k1);
-#pragma unroll
-  for (int e = 0; e < 9; ++e) K[e] = k1[0][e];
+  const PairIn in = pair_in(mode, (float)dx, (float)dy, (float)dz, !PAIRS);
+  float o[9];
+  if constexpr (MFK == MF_F32) {
+    if constexpr (PAIRS)
+      mlp_pairs_f32((const float*)fr, in.v0, in.v1, in.v2, o);
+    else
+      mlp_tile_f32((const float*)fr, in.v0, in.v1, in.v2, o);
+  } else {
+    if constexpr (PAIRS)
+      mlp_pairs_bf16<true>((const bf16x8*)fr, in, o);
+    else
+      mlp_tile_bf16<true>((const bf16x8*)fr, in, o);
+  }
+  pair_entry(o, in.rs, K);
 }
 
 __device__ __forceinline__ int tri(int m) { return m * (m + 1) / 2; }
@@ -279,54 +261,38 @@ __device__ __forceinline__ void team_sync() {
     __syncthreads();
 }
 
-// Raw samples K(sgn (p_i - y)) for rows i in [0, n) of `pts`, written to
-// slot[9 i ..]: 32-row MFMA tiles, lanes l and l + 32 share a row, the tiles
-// spread over the TW waves of the team.
-template <int NT, int MFK>
-__device__ __forceinline__ void sample_tiles(const void* fr, int mode, const double* pts, int n,
-                                             double y0, double y1, double y2, double sgn,
-                                             float* slot, int t0, int step) {
+// Raw samples K(sgn (p_i - y)) of `pts`, written to slot[9 i ..]: rows
+// t0 + lane % 32 (one tile), or with PAIRS rows t0 + lane and, for lanes 32-63,
+// t1 + lane - 32 (two tiles, one row per lane).
+template <bool PAIRS, int MFK>
+__device__ __forceinline__ void sample_rows(const void* fr, int mode, const double* pts, int n,
+                                            double y0, double y1, double y2, double sgn,
+                                            float* slot, int t0, int t1) {
   const int lane = threadIdx.x & 63;
-  double d[NT][3];
-  int row[NT];
+  const int i = (PAIRS && lane >= 32 ? t1 : t0) + (lane & 31);
+  const int ii = i < n ? i : t0;
+  float K[9];
+  mfma_entry<PAIRS, MFK>(fr, mode, sgn * (pts[3 * ii] - y0), sgn * (pts[3 * ii + 1] - y1),
+                         sgn * (pts[3 * ii + 2] - y2), K);
+  if (i < n && (PAIRS || lane < 32)) {
+    float* d = slot + 9 * (int64_t)i;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int tb = t0 + t * step;
-    const int i = tb + (lane & 31);
-    row[t] = i;
-    const int ii = i < n ? i : tb;
-    d[t][0] = sgn * (pts[3 * ii] - y0);
-    d[t][1] = sgn * (pts[3 * ii + 1] - y1);
-    d[t][2] = sgn * (pts[3 * ii + 2] - y2);
-  }
-  float K[NT][9];
-  mfma_entries<NT, MFK>(fr, mode, d, K);
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int i = row[t];
-    if (i < n) {
-      if (lane < 32) {
-#pragma unroll
-        for (int e = 0; e < 5; ++e) slot[9 * (int64_t)i + e] = K[t][e];
-      } else {
-#pragma unroll
-        for (int e = 5; e < 9; ++e) slot[9 * (int64_t)i + e] = K[t][e];
-      }
-    }
+    for (int e = 0; e < 9; ++e) d[e] = K[e];
   }
 }
 
+// The samples of all rows [0, n): 32-row tiles spread over the TW waves of the
+// team, a wave's tiles in pairs.
 template <int TW, int MFK>
 __device__ __forceinline__ void sample_mfma(const void* fr, int mode, const double* pts, int n,
                                             double y0, double y1, double y2, double sgn,
                                             float* slot, int wit) {
-  // this wave's tiles t0, t0 + 32 TW, ... in pairs (two independent MFMA chains)
   const int step = 32 * TW;
   int t0 = 32 * wit;
 #pragma unroll 1
   for (; t0 + step < n; t0 += 2 * step)
-    sample_tiles<2, MFK>(fr, mode, pts, n, y0, y1, y2, sgn, slot, t0, step);
-  if (t0 < n) sample_tiles<1, MFK>(fr, mode, pts, n, y0, y1, y2, sgn, slot, t0, step);
+    sample_rows<true, MFK>(fr, mode, pts, n, y0, y1, y2, sgn, slot, t0, t0 + step);
+  if (t0 < n) sample_rows<false, MFK>(fr, mode, pts, n, y0, y1, y2, sgn, slot, t0, t0);
 }
 
 // Combines the per-wave results of a pass over the team: sums v[0..NV) in
@@ -828,7 +794,7 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
 #pragma unroll 1
         for (int jj = 0; jj < q; ++jj) {
           float K[9];
-          mfma_entry<MF>(fr, a.kp.input_mode, x0 - xsr[3 * jj], x1 - xsr[3 * jj + 1],
+          mfma_entry<false, MF>(fr, a.kp.input_mode, x0 - xsr[3 * jj], x1 - xsr[3 * jj + 1],
                      x2 - xsr[3 * jj + 2], K);
           const T* f = a.Fs + 3 * ((int64_t)ns.x + jj);
           v0 += (double)(K[0] * (float)f[0] + K[1] * (float)f[1] + K[2] * (float)f[2]);

@@ -84,6 +84,19 @@ __global__ __launch_bounds__(T256) void k_far_t(const int2* __restrict__ G, int6
   }
 }
 
+// Near-field row s: its partial rows in a fixed order.
+template <class TU>
+__device__ __forceinline__ void near_sum(const TU* __restrict__ Un, int groups, int64_t n,
+                                         int64_t s, double& u0, double& u1, double& u2) {
+#pragma unroll 4
+  for (int g = 0; g < groups; ++g) {
+    const TU* r = Un + 3 * ((int64_t)g * n + s);
+    u0 += (double)r[0];
+    u1 += (double)r[1];
+    u2 += (double)r[2];
+  }
+}
+
 template <class T, class TU, class TO, int KIND>
 __global__ __launch_bounds__(T256) void k_combine(
     int64_t n, const int32_t* __restrict__ perm, const int32_t* __restrict__ leaf_of,
@@ -92,7 +105,8 @@ __global__ __launch_bounds__(T256) void k_combine(
     const int32_t* __restrict__ rank, const int32_t* __restrict__ flag,
     const int64_t* __restrict__ fptr, const int64_t* __restrict__ toff,
     const T* __restrict__ pool, const double* __restrict__ tbuf, const double* __restrict__ xs,
-    const T* __restrict__ Fs, const TU* __restrict__ Un, KParams kp, TO* __restrict__ U) {
+    const T* __restrict__ Fs, const TU* __restrict__ Un, int groups, KParams kp,
+    TO* __restrict__ U) {
   __shared__ T wl[KIND == KIND_MLP ? MLP_NP : 1];
   if (KIND == KIND_MLP) {
     const T* w = (const T*)kp.w;
@@ -101,7 +115,8 @@ __global__ __launch_bounds__(T256) void k_combine(
   }
   int64_t s = (int64_t)blockIdx.x * T256 + threadIdx.x;
   if (s >= n) return;
-  double u0 = (double)Un[3 * s], u1 = (double)Un[3 * s + 1], u2 = (double)Un[3 * s + 2];
+  double u0 = 0, u1 = 0, u2 = 0;
+  near_sum(Un, groups, n, s, u0, u1, u2);
   const double x0 = xs[3 * s], x1 = xs[3 * s + 1], x2 = xs[3 * s + 2];
   for (int tau = leaf_of[s]; tau >= 0; tau = parent[tau]) {
     const int il = (int)(s - nodes[tau].x);
@@ -174,31 +189,38 @@ __global__ __launch_bounds__(T256) void k_far_gather(
 template <class T, class TU, class TO>
 __global__ __launch_bounds__(T256) void k_final(int64_t n, const int32_t* __restrict__ perm,
                                                 const T* __restrict__ Fs, const TU* __restrict__ Un,
-                                                const double* __restrict__ Uf, double alpha1,
-                                                double alpha2, TO* __restrict__ U) {
+                                                int groups, const double* __restrict__ Uf,
+                                                double alpha1, double alpha2,
+                                                TO* __restrict__ U) {
   int64_t s = (int64_t)blockIdx.x * T256 + threadIdx.x;
   if (s >= n) return;
   const int64_t o = perm[s];
   const double a1 = (s & 1) ? alpha2 : alpha1;   // odd rows: rotational rows of a 6N kernel
+  double u[3] = {0, 0, 0};
+  near_sum(Un, groups, n, s, u[0], u[1], u[2]);
 #pragma unroll
   for (int d = 0; d < 3; ++d)
-    U[3 * o + d] = (TO)(((double)Un[3 * s + d] + Uf[3 * s + d]) + a1 * (double)Fs[3 * s + d]);
+    U[3 * o + d] = (TO)((u[d] + Uf[3 * s + d]) + a1 * (double)Fs[3 * s + d]);
+}
+
+// Bytes of `groups` sets of near-field rows.
+int64_t near_bytes(hh_tree t, hh_kernel k, int prec, int groups) {
+  return 3 * t->n * (int64_t)groups * (near_rows_f64(k, prec, groups) ? 8 : 4);
 }
 
 // Stored mode. Fs_ws and Un_ws hold the sorted forces (3 n T) and the
-// near-field rows (3 n TU); timed = false records no phase events.
-template <class T, class TI, class TO, class TU>
+// near-field rows (`groups` sets); timed = false records no phase events.
+template <class T, class TO>
 void matvec_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, const void* F,
-              void* U, void* Fs_ws, void* Un_ws, bool timed) {
+              void* U, void* Fs_ws, void* Un_ws, int groups, bool timed) {
   hipStream_t st = ctx->stream;
   const int64_t n = t->n;
   T* Fs = (T*)Fs_ws;
-  TU* Un = (TU*)Un_ws;
-  hipLaunchKernelGGL((k_gather_rows<TI, T>), dim3(nblk(n)), dim3(T256), 0, st, (const TI*)F,
+  hipLaunchKernelGGL((k_gather_rows<T, T>), dim3(nblk(n)), dim3(T256), 0, st, (const T*)F,
                      t->perm.as<int32_t>(), n, Fs);
   {
     PhaseTimer timer(ctx, HH_PHASE_NEAR, timed);
-    launch_near(ctx, t, p, k, lr->prec, Fs, Un);
+    launch_near(ctx, t, p, k, lr->prec, Fs, Un_ws, groups);
   }
   int64_t nG = p->nG;
   if (nG > 0) {
@@ -210,16 +232,20 @@ void matvec_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, cons
                        lr->tbuf.as<double>());
   }
   KParams kp = make_kparams(k, sizeof(T) == 8);
-#define COMBINE(KIND_)                                                                       \
-  hipLaunchKernelGGL((k_combine<T, TU, TO, KIND_>), dim3(nblk(n)), dim3(T256), 0, st, n,      \
+#define COMBINE(TU_, KIND_)                                                                   \
+  hipLaunchKernelGGL((k_combine<T, TU_, TO, KIND_>), dim3(nblk(n)), dim3(T256), 0, st, n,      \
                      t->perm.as<int32_t>(), t->leaf_of.as<int32_t>(), t->parent.as<int32_t>(), \
                      t->nodes.as<int4>(), p->far_ptr.as<int32_t>(), p->G.as<int2>(),           \
                      lr->rank.as<int32_t>(), lr->flag.as<int32_t>(), lr->fptr.as<int64_t>(),   \
                      lr->toff.as<int64_t>(), lr->pool.as<T>(), lr->tbuf.as<double>(),          \
-                     t->xs.as<double>(), Fs, Un, kp, (TO*)U)
+                     t->xs.as<double>(), Fs, (const TU_*)Un_ws, groups, kp, (TO*)U)
   {
     PhaseTimer timer(ctx, HH_PHASE_COMBINE, timed);
-    if (k->kind == KIND_MLP) COMBINE(KIND_MLP); else COMBINE(KIND_RPY);
+    if (near_rows_f64(k, lr->prec, groups)) {
+      if (k->kind == KIND_MLP) COMBINE(double, KIND_MLP); else COMBINE(double, KIND_RPY);
+    } else {
+      if (k->kind == KIND_MLP) COMBINE(T, KIND_MLP); else COMBINE(T, KIND_RPY);
+    }
   }
 #undef COMBINE
   HIP_OK(hipGetLastError());
@@ -227,31 +253,34 @@ void matvec_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, cons
 
 // Stored mode with the workspaces of the low-rank handle (sized on the first
 // product, reused after).
-template <class T, class TI, class TO, class TU>
+template <class T, class TO>
 void matvec_ws_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, const void* F,
                  void* U) {
-  const int64_t n = t->n;
-  lr->ws_f.ensure(ctx->stream, 3 * n * sizeof(T));
-  lr->ws_near.ensure(ctx->stream, 3 * n * sizeof(TU));
-  matvec_t<T, TI, TO, TU>(ctx, t, p, lr, k, F, U, lr->ws_f.p, lr->ws_near.p, true);
+  const int groups = near_groups(ctx, t, p, k, lr->prec);
+  lr->ws_f.ensure(ctx->stream, 3 * t->n * sizeof(T));
+  lr->ws_near.ensure(ctx->stream, near_bytes(t, k, lr->prec, groups));
+  matvec_t<T, TO>(ctx, t, p, lr, k, F, U, lr->ws_f.p, lr->ws_near.p, groups, true);
+}
+
+// Bytes of the sorted forces in the static scratch of the allocation-free
+// product.
+int64_t noalloc_forces(int64_t n, int prec) {
+  return (3 * n * (prec == HH_FP64 ? 8 : 4) + 255) / 256 * 256;
 }
 
 // The allocation-free product: the same launches with the workspaces in the
-// device's static scratch (base, HH_NOALLOC_SCRATCH_BYTES).
-template <class T, class TI, class TO, class TU>
+// device's static scratch (base, HH_NOALLOC_SCRATCH_BYTES); the near-field
+// sources are split only as far as the partial rows fit.
+template <class T, class TO>
 void matvec_noalloc_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k,
                       const void* F, void* U, char* base) {
-  const int64_t n = t->n;
-  const int64_t bf = (3 * n * (int64_t)sizeof(T) + 255) / 256 * 256;
-  const int64_t bu = 3 * n * (int64_t)sizeof(TU);
-  HH_REQUIRE(bf + bu <= (int64_t)HH_NOALLOC_SCRATCH_BYTES, HH_ERR_CAPACITY,
-             "hh_matvec_noalloc: " + std::to_string(n) + " particles need " +
-                 std::to_string(bf + bu) + " bytes of scratch, more than the " +
-                 std::to_string((int64_t)HH_NOALLOC_SCRATCH_BYTES) + " available");
-  matvec_t<T, TI, TO, TU>(ctx, t, p, lr, k, F, U, base, base + bf, false);
+  const int64_t bf = noalloc_forces(t->n, lr->prec);
+  int groups = near_groups(ctx, t, p, k, lr->prec);
+  if (bf + near_bytes(t, k, lr->prec, groups) > (int64_t)HH_NOALLOC_SCRATCH_BYTES) groups = 1;
+  matvec_t<T, TO>(ctx, t, p, lr, k, F, U, base, base + bf, groups, false);
 }
 
-template <class T, class TI, class TO, class TU>
+template <class T, class TO>
 void matvec_streamed_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k,
                        const void* F, void* U) {
   hipStream_t st = ctx->stream;
@@ -261,13 +290,14 @@ void matvec_streamed_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kerne
   DevBuf& Uf = lr->ws_far;
   DevBuf& counters = lr->ws_cnt;
   Fs.ensure(st, 3 * n * sizeof(T));
-  Un.ensure(st, 3 * n * sizeof(TU));
+  const int groups = near_groups(ctx, t, p, k, lr->prec);
+  Un.ensure(st, near_bytes(t, k, lr->prec, groups));
   Uf.ensure(st, 3 * n * sizeof(double));
-  hipLaunchKernelGGL((k_gather_rows<TI, T>), dim3(nblk(n)), dim3(T256), 0, st, (const TI*)F,
+  hipLaunchKernelGGL((k_gather_rows<T, T>), dim3(nblk(n)), dim3(T256), 0, st, (const T*)F,
                      t->perm.as<int32_t>(), n, Fs.as<T>());
   {
     PhaseTimer timer(ctx, HH_PHASE_NEAR);
-    launch_near(ctx, t, p, k, lr->prec, Fs.p, Un.p);
+    launch_near(ctx, t, p, k, lr->prec, Fs.p, Un.p, groups);
   }
   zero_words(ctx, Uf.p, 3 * n);
   const size_t nb = lr->bounds.size() - 1;
@@ -290,9 +320,14 @@ void matvec_streamed_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kerne
   }
   {
     PhaseTimer timer(ctx, HH_PHASE_COMBINE);
-    hipLaunchKernelGGL((k_final<T, TU, TO>), dim3(nblk(n)), dim3(T256), 0, st, n,
-                       t->perm.as<int32_t>(), Fs.as<T>(), Un.as<TU>(), Uf.as<double>(),
-                       k->alpha1, k->alpha2, (TO*)U);
+    if (near_rows_f64(k, lr->prec, groups))
+      hipLaunchKernelGGL((k_final<T, double, TO>), dim3(nblk(n)), dim3(T256), 0, st, n,
+                         t->perm.as<int32_t>(), Fs.as<T>(), Un.as<double>(), groups,
+                         Uf.as<double>(), k->alpha1, k->alpha2, (TO*)U);
+    else
+      hipLaunchKernelGGL((k_final<T, T, TO>), dim3(nblk(n)), dim3(T256), 0, st, n,
+                         t->perm.as<int32_t>(), Fs.as<T>(), Un.as<T>(), groups, Uf.as<double>(),
+                         k->alpha1, k->alpha2, (TO*)U);
   }
   HIP_OK(hipGetLastError());
   lr->stats_dirty = true;
@@ -370,25 +405,20 @@ hh_status hh_matvec(hh_ctx ctx, hh_tree tree, hh_part part, hh_lowrank lr, hh_ke
              "handles do not belong together");
   HH_REQUIRE(lr->prec == prec, HH_ERR_INVALID_ARG, "precision differs from the ACA build");
   HH_REQUIRE(lr->kern == kern, HH_ERR_INVALID_ARG, "kernel differs from the ACA build");
-  // <storage/kernel type, F type, U type, near-field row type>
-  const bool mfma = is_bf16(prec) && kern->kind == KIND_MLP;
+  // <storage, kernel and F type, U type>
   if (lr->streamed) {
     if (prec == HH_FP64)
-      matvec_streamed_t<double, double, double, double>(ctx, tree, part, lr, kern, F, U);
+      matvec_streamed_t<double, double>(ctx, tree, part, lr, kern, F, U);
     else if (prec == HH_FP32)
-      matvec_streamed_t<float, float, float, float>(ctx, tree, part, lr, kern, F, U);
-    else if (mfma)
-      matvec_streamed_t<float, float, double, double>(ctx, tree, part, lr, kern, F, U);
+      matvec_streamed_t<float, float>(ctx, tree, part, lr, kern, F, U);
     else
-      matvec_streamed_t<float, float, double, float>(ctx, tree, part, lr, kern, F, U);
+      matvec_streamed_t<float, double>(ctx, tree, part, lr, kern, F, U);
   } else if (prec == HH_FP64) {
-    matvec_ws_t<double, double, double, double>(ctx, tree, part, lr, kern, F, U);
+    matvec_ws_t<double, double>(ctx, tree, part, lr, kern, F, U);
   } else if (prec == HH_FP32) {
-    matvec_ws_t<float, float, float, float>(ctx, tree, part, lr, kern, F, U);
-  } else if (mfma) {
-    matvec_ws_t<float, float, double, double>(ctx, tree, part, lr, kern, F, U);
+    matvec_ws_t<float, float>(ctx, tree, part, lr, kern, F, U);
   } else {
-    matvec_ws_t<float, float, double, float>(ctx, tree, part, lr, kern, F, U);
+    matvec_ws_t<float, double>(ctx, tree, part, lr, kern, F, U);
   }
   HH_API_END(ctx)
 }
@@ -403,26 +433,21 @@ hh_status hh_matvec_noalloc(hh_ctx ctx, hh_tree tree, hh_part part, hh_lowrank l
   HH_REQUIRE(lr->kern == kern, HH_ERR_INVALID_ARG, "kernel differs from the ACA build");
   HH_REQUIRE(ctx->noalloc_scratch, HH_ERR_HIP, "no scratch address on this device");
   char* base = (char*)ctx->noalloc_scratch;
-  const bool mfma = is_bf16(prec) && kern->kind == KIND_MLP;
-  // the size limit first: it depends only on n and the precision
+  // the size limit first: it depends only on n, the kernel and the precision
   const int64_t n = tree->n;
-  const int64_t need = (3 * n * (prec == HH_FP64 ? 8 : 4) + 255) / 256 * 256 +
-                       3 * n * ((prec == HH_FP64 || mfma) ? 8 : 4);
+  const int64_t need = noalloc_forces(n, prec) + near_bytes(tree, kern, prec, 1);
   HH_REQUIRE(need <= (int64_t)HH_NOALLOC_SCRATCH_BYTES, HH_ERR_CAPACITY,
              "hh_matvec_noalloc: " + std::to_string(n) + " particles need " +
                  std::to_string(need) + " bytes of scratch, more than the " +
                  std::to_string((int64_t)HH_NOALLOC_SCRATCH_BYTES) + " available");
   HH_REQUIRE(!lr->streamed, HH_ERR_INVALID_ARG,
              "hh_matvec_noalloc needs stored factors (streamed mode runs the ACA in the product)");
-  HH_REQUIRE(tree->n_units > 0, HH_ERR_INVALID_ARG, "tree has no near-field work units");
   if (prec == HH_FP64)
-    matvec_noalloc_t<double, double, double, double>(ctx, tree, part, lr, kern, F, U, base);
+    matvec_noalloc_t<double, double>(ctx, tree, part, lr, kern, F, U, base);
   else if (prec == HH_FP32)
-    matvec_noalloc_t<float, float, float, float>(ctx, tree, part, lr, kern, F, U, base);
-  else if (mfma)
-    matvec_noalloc_t<float, float, double, double>(ctx, tree, part, lr, kern, F, U, base);
+    matvec_noalloc_t<float, float>(ctx, tree, part, lr, kern, F, U, base);
   else
-    matvec_noalloc_t<float, float, double, float>(ctx, tree, part, lr, kern, F, U, base);
+    matvec_noalloc_t<float, double>(ctx, tree, part, lr, kern, F, U, base);
   HH_API_END(ctx)
 }
 

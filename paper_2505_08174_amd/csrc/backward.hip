@@ -600,17 +600,20 @@ __global__ __launch_bounds__(TB) void k_gather3(const T* __restrict__ v,
 }
 
 // out[perm[s]] = (a1 * ws[s] + near_T[s] + far_T[s]) or dX scatter
-template <class T>
+template <class T, class TU>
 __global__ __launch_bounds__(TB) void k_scatter_dF(const T* __restrict__ ws,
-                                                   const T* __restrict__ nearT,
+                                                   const TU* __restrict__ nearT, int groups,
                                                    const double* __restrict__ farT,
                                                    const int32_t* __restrict__ perm, int64_t n,
                                                    double a1, T* __restrict__ dF) {
   int64_t s = (int64_t)blockIdx.x * TB + threadIdx.x;
   if (s >= n) return;
   int64_t o = perm[s];
+  double u[3] = {0, 0, 0};
+  for (int g = 0; g < groups; ++g)
+    for (int d = 0; d < 3; ++d) u[d] += (double)nearT[3 * ((int64_t)g * n + s) + d];
   for (int d = 0; d < 3; ++d)
-    dF[3 * o + d] = (T)((a1 * (double)ws[3 * s + d] + (double)nearT[3 * s + d]) + farT[3 * s + d]);
+    dF[3 * o + d] = (T)((a1 * (double)ws[3 * s + d] + u[d]) + farT[3 * s + d]);
 }
 
 __global__ __launch_bounds__(TB) void k_scatter_dX(const double* __restrict__ dXs,
@@ -721,11 +724,19 @@ void backward_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, co
     HIP_OK(hipGetLastError());
   }
   if (dF) {
-    nearT.alloc(st, 3 * n * sizeof(T));
-    launch_near_neg(ctx, t, p, k, sizeof(T) == 8 ? HH_FP64 : HH_FP32, ws.p, nearT.p);
-    hipLaunchKernelGGL((k_scatter_dF<T>), dim3(nblk(n)), dim3(TB), 0, st, ws.as<T>(),
-                       nearT.as<T>(), farT.as<double>(), t->perm.as<int32_t>(), n, k->alpha1,
-                       (T*)dF);
+    const int prec = sizeof(T) == 8 ? HH_FP64 : HH_FP32;
+    const int groups = near_groups(ctx, t, p, k, prec);
+    const bool f64 = near_rows_f64(k, prec, groups);
+    nearT.alloc(st, 3 * n * (int64_t)groups * (f64 ? sizeof(double) : sizeof(T)));
+    launch_near_neg(ctx, t, p, k, prec, ws.p, nearT.p, groups);
+    if (f64)
+      hipLaunchKernelGGL((k_scatter_dF<T, double>), dim3(nblk(n)), dim3(TB), 0, st, ws.as<T>(),
+                         nearT.as<double>(), groups, farT.as<double>(), t->perm.as<int32_t>(), n,
+                         k->alpha1, (T*)dF);
+    else
+      hipLaunchKernelGGL((k_scatter_dF<T, T>), dim3(nblk(n)), dim3(TB), 0, st, ws.as<T>(),
+                         nearT.as<T>(), groups, farT.as<double>(), t->perm.as<int32_t>(), n,
+                         k->alpha1, (T*)dF);
   }
   if (mlp) {
     if constexpr (mf)

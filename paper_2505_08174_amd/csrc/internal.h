@@ -168,6 +168,8 @@ struct hh_part_s {
   DevBuf G;        // int2 [nG] (tau, sigma) sorted
   DevBuf H;        // int2 [nH] (tau, sigma) sorted
   DevBuf near_ptr; // int32 [n_leaves+1] CSR of H by target leaf rank
+  DevBuf near_src; // int4 [nH] source rows [x, y) of every H entry, z sources before it in its list
+  DevBuf near_q;   // int32 [n_leaves] sources of a leaf's whole list
   DevBuf far_ptr;  // int32 [n_nodes+1]  CSR of G by target node
   int64_t near_pairs = 0;   // sum over H of |tau||sigma|
   int64_t far_entries = 0;  // sum over G of |tau||sigma|
@@ -250,14 +252,24 @@ void scan_exclusive_i64(hh_ctx ctx, const int64_t* in, int64_t* out, int64_t n);
 // Stable LSD radix sort of (key, value) pairs by the low `bits` bits of key.
 void radix_sort_u64(hh_ctx ctx, uint64_t* keys, uint32_t* vals, int64_t n, int bits);
 
-// Near-field, ACA, far-field and combine launches (near.hip, aca.hip, apply.hip).
-void launch_near(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, int prec, const void* F,
-                 void* Unear);
-void launch_near_bf16(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs, void* Un,
-                      bool split);
+// Near-field launches (near.hip, near_mfma.hip). The near field of a row is
+// the sum of `groups` partial rows, out[g][n][3], in FP64 when the sources are
+// split (groups > 1) and in the FP64 and BF16 forms, else in FP32.
+int near_groups(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, int prec);
+inline bool near_rows_f64(hh_kernel k, int prec, int groups) {
+  return prec == HH_FP64 || (is_bf16(prec) && k->kind == KIND_MLP) || groups > 1;
+}
+void launch_near(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, int prec, const void* Fs,
+                 void* out, int groups);
+// the displacement reversed: sum_j K(x_j - x_i) v_j
+void launch_near_neg(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, int prec, const void* Vs,
+                     void* out, int groups);
+int near_groups_mfma(hh_ctx ctx, hh_tree t, hh_part p);
+void launch_near_bf16(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs, void* out,
+                      int groups, bool split);
 // sgn = -1: the transposed product sum_j K(x_j - x_i) v_j
-void launch_near_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs, void* Un,
-                     float sgn = 1.0f);
+void launch_near_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs, void* out,
+                     int groups, float sgn = 1.0f);
 // FP32 MFMA back-propagation of near pairs and of the ACA samples
 // (backward_mfma.hip); slots: vjp_f32_waves(ctx) x MLP_NP doubles each.
 int64_t vjp_f32_waves(hh_ctx ctx);
@@ -267,7 +279,5 @@ void launch_far_vjp_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kern
                         int64_t b0, int64_t b1, const int64_t* goff, const float* gpool,
                         double* dXs, double* slots);
 void ensure_units(hh_ctx ctx, hh_tree t);
-void launch_near_neg(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, int prec, const void* Vs,
-                     void* out);
 void launch_aca(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr, double eps,
                 int32_t l_max, int64_t* pool_top_dev);

@@ -108,15 +108,60 @@ __device__ __forceinline__ void hidden_layer(const bf16x8* __restrict__ fr, int 
   }
 }
 
-// Raw outputs o[t][0..8] of the MLP at inputs v[t] for this lane's pair of
-// each of NT independent tiles. Must be called by all 64 lanes of the wave
-// with lanes l and l+32 holding the same inputs. ACC = false: activations
-// rounded to BF16 once (relative error ~1e-4 of a sample); ACC = true:
-// activations carried as BF16 hi + lo (~3e-6), used where samples must
-// resolve a 1e-4 cross-approximation.
+// Input of the kernel MLP at displacement (rx, ry, rz), |r|^-1, and the
+// symmetrised entry K(r) = (O + O^T)/2 / (8 pi |r|). The roundings are spelled
+// out (which product of |r|^2 is rounded, which remainder of v is taken), so
+// that every kernel that samples a pair gets the same bits: the ACA's pivots
+// and stopping tests hang on them, and a replay reproduces a build exactly.
+struct PairIn {
+  float v0, v1, v2, rs;
+  float l0, l1, l2;   // v minus its BF16 rounding, before its own rounding to BF16
+};
+__device__ __forceinline__ float pair_norm2(float rx, float ry, float rz) {
+  return __builtin_fmaf(rz, rz, __builtin_fmaf(rx, rx, ry * ry));
+}
+// exact = true: the remainder of the unrounded product r |r|^-1, else of v.
+__device__ __forceinline__ float pair_rest(float v, float r, float sc, bool exact) {
+#pragma clang fp contract(off)
+  const float h = (float)(__bf16)v;
+  const float d = v - h;
+  return exact ? __builtin_fmaf(r, sc, -h) : d;
+}
+__device__ __forceinline__ PairIn pair_in(int mode, float rx, float ry, float rz, bool exact) {
+  PairIn in;
+  in.rs = hh_rsqrt(pair_norm2(rx, ry, rz));
+  const float sc = mode == HH_MLP_INPUT_DIRECTION ? in.rs : 1.0f;
+  in.v0 = rx * sc;
+  in.v1 = ry * sc;
+  in.v2 = rz * sc;
+  in.l0 = pair_rest(in.v0, rx, sc, exact);
+  in.l1 = pair_rest(in.v1, ry, sc, exact);
+  in.l2 = pair_rest(in.v2, rz, sc, exact);
+  return in;
+}
+__device__ __forceinline__ void pair_entry(const float (&o)[9], float rs, float K[9]) {
+  const float s = rs * (float)(1.0 / (16.0 * HH_PI));
+  K[0] = 2.0f * o[0] * s; K[1] = (o[1] + o[3]) * s; K[2] = (o[2] + o[6]) * s;
+  K[3] = K[1];            K[4] = 2.0f * o[4] * s;   K[5] = (o[5] + o[7]) * s;
+  K[6] = K[2];            K[7] = K[5];              K[8] = 2.0f * o[8] * s;
+}
+// (K(r) f)_d of one pair; sc = |r|^-1 / (16 pi), or 0 for a pair that adds nothing
+__device__ __forceinline__ void pair_apply(const float (&q)[9], float sc, float f0, float f1,
+                                           float f2, double& u0, double& u1, double& u2) {
+  const float a = q[1] + q[3], b = q[2] + q[6], c = q[5] + q[7];
+  u0 += (double)(sc * __builtin_fmaf(b, f2, __builtin_fmaf(2.0f * q[0], f0, a * f1)));
+  u1 += (double)(sc * __builtin_fmaf(c, f2, __builtin_fmaf(a, f0, 2.0f * q[4] * f1)));
+  u2 += (double)(sc * __builtin_fmaf(2.0f * q[8], f2, __builtin_fmaf(b, f0, c * f1)));
+}
+
+// Result registers acc[t] of the output layer for NT independent tiles with
+// layer-1 operands b1[t] (K slots (v_hi, v_lo, 1, 1) in lanes 0-31, (v_hi, 0..)
+// in lanes 32-63). ACC = false: activations rounded to BF16 once (relative
+// error ~1e-4 of a sample); ACC = true: activations carried as BF16 hi + lo
+// (~3e-6), used where samples must resolve a 1e-4 cross-approximation.
 template <bool ACC, int NT>
-__device__ __forceinline__ void mlp_tiles_bf16(const bf16x8* __restrict__ fr,
-                                               const float (&v)[NT][3], float (&o)[NT][9]) {
+__device__ __forceinline__ void mlp_core_bf16(const bf16x8* __restrict__ fr,
+                                              const bf16x8 (&b1)[NT], f32x16 (&acc)[NT]) {
   // the fragments are re-read from LDS for every call: hoisting them out of
   // a caller's loop would pin 192 VGPRs and cut the occupancy to one wave
   __asm__ volatile("" ::: "memory");
@@ -126,25 +171,10 @@ __device__ __forceinline__ void mlp_tiles_bf16(const bf16x8* __restrict__ fr,
   bf16x8 Bone;
 #pragma unroll
   for (int u = 0; u < 8; ++u) Bone[u] = (!h1 && u < 2) ? one : z;
-  // layer 1 input column: K slots (v_hi, v_lo, 1, 1 | v_hi, 0...)
-  bf16x8 b1[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const __bf16 vh0 = (__bf16)v[t][0], vh1 = (__bf16)v[t][1], vh2 = (__bf16)v[t][2];
-    b1[t][0] = vh0;
-    b1[t][1] = vh1;
-    b1[t][2] = vh2;
-    b1[t][3] = h1 ? z : (__bf16)(v[t][0] - (float)vh0);
-    b1[t][4] = h1 ? z : (__bf16)(v[t][1] - (float)vh1);
-    b1[t][5] = h1 ? z : (__bf16)(v[t][2] - (float)vh2);
-    b1[t][6] = h1 ? z : one;
-    b1[t][7] = h1 ? z : one;
-  }
   bf16x8 B[NT][4], Bn[NT][4], Bl[NT][4], Bnl[NT][4];
 #pragma unroll
   for (int mo = 0; mo < 2; ++mo) {
     const bf16x8 w1 = fr[FR_L1 + mo * 64 + lane];
-    f32x16 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = mfma_bf16(w1, b1[t], f32x16{});
 #pragma unroll
@@ -155,7 +185,6 @@ __device__ __forceinline__ void mlp_tiles_bf16(const bf16x8* __restrict__ fr,
   }
   hidden_layer<ACC, NT>(fr, FR_L2, lane, B, Bl, Bone, Bn, Bnl);
   hidden_layer<ACC, NT>(fr, FR_L3, lane, Bn, Bnl, Bone, B, Bl);
-  f32x16 acc[NT];
   const bf16x8 w4b = fr[FR_L4 + (4 * 2) * 64 + lane];
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = mfma_bf16(w4b, Bone, f32x16{});
@@ -170,28 +199,90 @@ __device__ __forceinline__ void mlp_tiles_bf16(const bf16x8* __restrict__ fr,
       if (ACC) acc[t] = mfma_bf16(wh, Bl[t][s], acc[t]);
     }
   }
+}
+
+// Raw outputs o[0..8] for one tile of 32 pairs. Must be called by all 64 lanes
+// of the wave with lanes l and l + 32 holding the same input.
+template <bool ACC>
+__device__ __forceinline__ void mlp_tile_bf16(const bf16x8* __restrict__ fr, const PairIn& in,
+                                              float (&o)[9]) {
+  const bool h1 = (threadIdx.x & 63) >= 32;
+  const __bf16 z = (__bf16)0.0f, one = (__bf16)1.0f;
+  bf16x8 b1[1];
+  b1[0][0] = (__bf16)in.v0;
+  b1[0][1] = (__bf16)in.v1;
+  b1[0][2] = (__bf16)in.v2;
+  b1[0][3] = h1 ? z : (__bf16)in.l0;
+  b1[0][4] = h1 ? z : (__bf16)in.l1;
+  b1[0][5] = h1 ? z : (__bf16)in.l2;
+  b1[0][6] = h1 ? z : one;
+  b1[0][7] = h1 ? z : one;
+  f32x16 acc[1];
+  mlp_core_bf16<ACC, 1>(fr, b1, acc);
   // rows 0-3 and 8 live in lanes 0-31 (registers 0-3, 4); rows 4-7 in 32-63
+  const f32x16& c = acc[0];
+  const float t0 = __shfl_xor(c[0], 32, 64), t1 = __shfl_xor(c[1], 32, 64);
+  const float t2 = __shfl_xor(c[2], 32, 64), t3 = __shfl_xor(c[3], 32, 64);
+  const float t4 = __shfl_xor(c[4], 32, 64);
+  o[0] = h1 ? t0 : c[0]; o[1] = h1 ? t1 : c[1]; o[2] = h1 ? t2 : c[2];
+  o[3] = h1 ? t3 : c[3]; o[4] = h1 ? c[0] : t0; o[5] = h1 ? c[1] : t1;
+  o[6] = h1 ? c[2] : t2; o[7] = h1 ? c[3] : t3; o[8] = h1 ? t4 : c[4];
+}
+
+// v_permlane32_swap_b32: lo = (a of lanes 0-31, b of lanes 0-31), hi = (a of
+// lanes 32-63, b of lanes 32-63)
+struct HalfSwap {
+  uint32_t lo, hi;
+};
+__device__ __forceinline__ HalfSwap half_swap(uint32_t a, uint32_t b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  return HalfSwap{r[0], r[1]};
+}
+
+// Outputs of two tiles' result registers for 64 different pairs: lanes 0-31
+// take the pairs of tile 0, lanes 32-63 those of tile 1. Rows 0-3 and 8 of a
+// tile sit in its lanes 0-31 (registers 0-3, 4), rows 4-7 in its lanes 32-63.
+__device__ __forceinline__ void pair_outputs(const float (&c0)[5], const float (&c1)[5],
+                                             float (&o)[9]) {
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const f32x16& c = acc[t];
-    const float t0 = __shfl_xor(c[0], 32, 64), t1 = __shfl_xor(c[1], 32, 64);
-    const float t2 = __shfl_xor(c[2], 32, 64), t3 = __shfl_xor(c[3], 32, 64);
-    const float t4 = __shfl_xor(c[4], 32, 64);
-    o[t][0] = h1 ? t0 : c[0]; o[t][1] = h1 ? t1 : c[1]; o[t][2] = h1 ? t2 : c[2];
-    o[t][3] = h1 ? t3 : c[3]; o[t][4] = h1 ? c[0] : t0; o[t][5] = h1 ? c[1] : t1;
-    o[t][6] = h1 ? c[2] : t2; o[t][7] = h1 ? c[3] : t3; o[t][8] = h1 ? t4 : c[4];
+  for (int e = 0; e < 5; ++e) {
+    const HalfSwap r = half_swap(__float_as_uint(c0[e]), __float_as_uint(c1[e]));
+    if (e < 4) {
+      o[e] = __uint_as_float(r.lo);
+      o[4 + e] = __uint_as_float(r.hi);
+    } else {
+      o[8] = __uint_as_float(r.lo);
+    }
   }
 }
 
-// One tile of 32 pairs (see mlp_tiles_bf16).
+// Raw outputs o[0..8] for 64 different pairs, one per lane: two tiles, lanes
+// 0-31 and lanes 32-63. Each lane prepares the input of its own pair and takes
+// the outputs of its own pair; half-wave swaps move them to and from the two
+// tiles' operand layout, so nothing outside the tiles is computed twice (a
+// single tile spends both halves of the wave on the same 32 pairs).
 template <bool ACC>
-__device__ __forceinline__ void mlp_tile_bf16(const bf16x8* __restrict__ fr, float v0, float v1,
-                                              float v2, float o[9]) {
-  const float v[1][3] = {{v0, v1, v2}};
-  float oo[1][9];
-  mlp_tiles_bf16<ACC, 1>(fr, v, oo);
+__device__ __forceinline__ void mlp_pairs_bf16(const bf16x8* __restrict__ fr, const PairIn& in,
+                                               float (&o)[9]) {
+  const bool h1 = (threadIdx.x & 63) >= 32;
+  const uint32_t w0 = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)in.v0, (__bf16)in.v1});
+  const uint32_t w1 = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)in.v2, (__bf16)in.l0});
+  const uint32_t w2 = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)in.l1, (__bf16)in.l2});
+  const HalfSwap s0 = half_swap(w0, w0), s1 = half_swap(w1, w1), s2 = half_swap(w2, w2);
+  const uint32_t ones = h1 ? 0u : 0x3f803f80u;   // (1, 1) in the bias slots
+  const uint32_t m1 = h1 ? 0x0000ffffu : 0xffffffffu, m2 = h1 ? 0u : 0xffffffffu;
+  const uint4 q0 = make_uint4(s0.lo, s1.lo & m1, s2.lo & m2, ones);
+  const uint4 q1 = make_uint4(s0.hi, s1.hi & m1, s2.hi & m2, ones);
+  const bf16x8 b1[2] = {__builtin_bit_cast(bf16x8, q0), __builtin_bit_cast(bf16x8, q1)};
+  f32x16 acc[2];
+  mlp_core_bf16<ACC, 2>(fr, b1, acc);
+  float c0[5], c1[5];
 #pragma unroll
-  for (int e = 0; e < 9; ++e) o[e] = oo[0][e];
+  for (int e = 0; e < 5; ++e) {
+    c0[e] = acc[0][e];
+    c1[e] = acc[1][e];
+  }
+  pair_outputs(c0, c1, o);
 }
 
 // Stage the fragment table (global -> LDS) by the whole workgroup.
@@ -226,61 +317,105 @@ __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// One hidden layer (64 -> 64, then tanh) from h[2][16] into g[2][16]; the two
-// output M tiles are two independent MFMA chains.
+// One hidden layer (64 -> 64, then tanh) of NT tiles from h[t] into g[t]; the
+// output M tiles of every tile are independent MFMA chains, and a weight is
+// read once for all tiles.
+template <int NT>
 __device__ __forceinline__ void hidden_f32(const float* __restrict__ fr, int base, int lane,
-                                           float bone, const float (&h)[2][16],
-                                           float (&g)[2][16]) {
-  f32x16 a0 = mfma_f32(fr[(base + 64) * 64 + lane], bone, f32x16{});
-  f32x16 a1 = mfma_f32(fr[(base + 65) * 64 + lane], bone, f32x16{});
+                                           float bone, const float (&h)[NT][2][16],
+                                           float (&g)[NT][2][16]) {
+  f32x16 a0[NT], a1[NT];
+  const float wb0 = fr[(base + 64) * 64 + lane], wb1 = fr[(base + 65) * 64 + lane];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    a0[t] = mfma_f32(wb0, bone, f32x16{});
+    a1[t] = mfma_f32(wb1, bone, f32x16{});
+  }
 #pragma unroll
   for (int mo = 0; mo < 2; ++mo)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      a0 = mfma_f32(fr[(base + (0 * 2 + mo) * 16 + r) * 64 + lane], h[mo][r], a0);
-      a1 = mfma_f32(fr[(base + (1 * 2 + mo) * 16 + r) * 64 + lane], h[mo][r], a1);
+      const float w0 = fr[(base + (0 * 2 + mo) * 16 + r) * 64 + lane];
+      const float w1 = fr[(base + (1 * 2 + mo) * 16 + r) * 64 + lane];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        a0[t] = mfma_f32(w0, h[t][mo][r], a0[t]);
+        a1[t] = mfma_f32(w1, h[t][mo][r], a1[t]);
+      }
     }
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    g[0][r] = tanh_scaled(a0[r]);
-    g[1][r] = tanh_scaled(a1[r]);
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      g[t][0][r] = tanh_scaled(a0[t][r]);
+      g[t][1][r] = tanh_scaled(a1[t][r]);
+    }
+}
+
+__device__ __forceinline__ void hidden_f32(const float* __restrict__ fr, int base, int lane,
+                                           float bone, const float (&h)[2][16],
+                                           float (&g)[2][16]) {
+  hidden_f32<1>(fr, base, lane, bone, reinterpret_cast<const float(&)[1][2][16]>(h),
+                reinterpret_cast<float(&)[1][2][16]>(g));
+}
+
+// Result registers c[t][0..4] of the output layer (rows 0-3 and 8 in lanes
+// 0-31, rows 4-7 in lanes 32-63) of NT tiles with the layer-1 operands b0 =
+// (v0 | v1) and b1 = (v2 | 1) of the two lane halves. Called by all 64 lanes.
+// fr: the FP32 fragment table (F32_FRAGS x 64 floats).
+template <int NT>
+__device__ __forceinline__ void mlp_core_f32(const float* __restrict__ fr, const float (&b0)[NT],
+                                             const float (&b1)[NT], float (&c)[NT][5]) {
+  __asm__ volatile("" ::: "memory");
+  const int lane = threadIdx.x & 63;
+  const float bone = lane >= 32 ? 0.0f : 1.0f;
+  float h[NT][2][16], g[NT][2][16];
+#pragma unroll
+  for (int mo = 0; mo < 2; ++mo) {
+    const float w0 = fr[(F32_L1 + 2 * mo) * 64 + lane], w1 = fr[(F32_L1 + 2 * mo + 1) * 64 + lane];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      f32x16 a = mfma_f32(w0, b0[t], f32x16{});
+      a = mfma_f32(w1, b1[t], a);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) h[t][mo][r] = tanh_scaled(a[r]);
+    }
   }
+  hidden_f32<NT>(fr, F32_L2, lane, bone, h, g);
+  hidden_f32<NT>(fr, F32_L3, lane, bone, g, h);
+  // layer 4: two chains (features of M tile 0 and 1), summed at the end
+  f32x16 c0[NT], c1[NT];
+  const float wb = fr[(F32_L4 + 32) * 64 + lane];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    c0[t] = mfma_f32(wb, bone, f32x16{});
+    c1[t] = f32x16{};
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float w0 = fr[(F32_L4 + r) * 64 + lane], w1 = fr[(F32_L4 + 16 + r) * 64 + lane];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      c0[t] = mfma_f32(w0, h[t][0][r], c0[t]);
+      c1[t] = mfma_f32(w1, h[t][1][r], c1[t]);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int e = 0; e < 5; ++e) c[t][e] = c0[t][e] + c1[t][e];
 }
 
 // Raw outputs o[0..8] of the MLP at input (v0, v1, v2) for this lane's pair.
 // Must be called by all 64 lanes with lanes l and l + 32 holding the same
-// input. fr: the FP32 fragment table (F32_FRAGS x 64 floats).
+// input.
 __device__ __forceinline__ void mlp_tile_f32(const float* __restrict__ fr, float v0, float v1,
                                              float v2, float o[9]) {
-  __asm__ volatile("" ::: "memory");
-  const int lane = threadIdx.x & 63;
-  const bool h1 = lane >= 32;
-  const float bone = h1 ? 0.0f : 1.0f;
-  float h[2][16], g[2][16];
-  {
-    const float b0 = h1 ? v1 : v0, b1 = h1 ? 1.0f : v2;
-#pragma unroll
-    for (int mo = 0; mo < 2; ++mo) {
-      f32x16 a = mfma_f32(fr[(F32_L1 + 2 * mo) * 64 + lane], b0, f32x16{});
-      a = mfma_f32(fr[(F32_L1 + 2 * mo + 1) * 64 + lane], b1, a);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) h[mo][r] = tanh_scaled(a[r]);
-    }
-  }
-  hidden_f32(fr, F32_L2, lane, bone, h, g);
-  hidden_f32(fr, F32_L3, lane, bone, g, h);
-  // layer 4: two chains (features of M tile 0 and 1), summed at the end
-  f32x16 c0 = mfma_f32(fr[(F32_L4 + 32) * 64 + lane], bone, f32x16{});
-  f32x16 c1 = f32x16{};
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    c0 = mfma_f32(fr[(F32_L4 + r) * 64 + lane], h[0][r], c0);
-    c1 = mfma_f32(fr[(F32_L4 + 16 + r) * 64 + lane], h[1][r], c1);
-  }
-  // rows 0-3 and 8 live in lanes 0-31 (registers 0-3, 4); rows 4-7 in 32-63
-  float c[5];
-#pragma unroll
-  for (int e = 0; e < 5; ++e) c[e] = c0[e] + c1[e];
+  const bool h1 = (threadIdx.x & 63) >= 32;
+  const float b0[1] = {h1 ? v1 : v0}, b1[1] = {h1 ? 1.0f : v2};
+  float cc[1][5];
+  mlp_core_f32<1>(fr, b0, b1, cc);
+  const float(&c)[5] = cc[0];
   const float t0 = __shfl_xor(c[0], 32, 64), t1 = __shfl_xor(c[1], 32, 64);
   const float t2 = __shfl_xor(c[2], 32, 64), t3 = __shfl_xor(c[3], 32, 64);
   const float t4 = __shfl_xor(c[4], 32, 64);
@@ -289,21 +424,28 @@ __device__ __forceinline__ void mlp_tile_f32(const float* __restrict__ fr, float
   o[6] = h1 ? c[2] : t2; o[7] = h1 ? c[3] : t3; o[8] = h1 ? t4 : c[4];
 }
 
-// Symmetrised kernel entry K(r) = (O + O^T)/2 / (8 pi |r|) of this lane's
-// pair from the FP32 tile, r given in FP64 and rounded to FP32 (all 64 lanes
-// call it; lanes l and l + 32 hold the same r). The ACA samples and their
-// replay both come from here, so a replay reproduces a build bit for bit.
+// Raw outputs for 64 different pairs, one per lane (two tiles: lanes 0-31 and
+// lanes 32-63), with half-wave swaps as in mlp_pairs_bf16.
+__device__ __forceinline__ void mlp_pairs_f32(const float* __restrict__ fr, float v0, float v1,
+                                              float v2, float (&o)[9]) {
+  // .lo: (v0 | v1) and (v2 | 1) of lanes 0-31's pairs, .hi: of lanes 32-63's
+  const HalfSwap a = half_swap(__float_as_uint(v0), __float_as_uint(v1));
+  const HalfSwap b = half_swap(__float_as_uint(v2), __float_as_uint(1.0f));
+  const float b0[2] = {__uint_as_float(a.lo), __uint_as_float(a.hi)};
+  const float b1[2] = {__uint_as_float(b.lo), __uint_as_float(b.hi)};
+  float c[2][5];
+  mlp_core_f32<2>(fr, b0, b1, c);
+  pair_outputs(c[0], c[1], o);
+}
+
+// Entry of this lane's pair from one FP32 tile (all 64 lanes call it; lanes l
+// and l + 32 hold the same r).
 __device__ __forceinline__ void entry_f32tile(const float* __restrict__ fr, int mode, double dx,
                                               double dy, double dz, float K[9]) {
-  const float rx = (float)dx, ry = (float)dy, rz = (float)dz;
-  const float rs = hh_rsqrt(rx * rx + ry * ry + rz * rz);
-  const float sc = mode == HH_MLP_INPUT_DIRECTION ? rs : 1.0f;
+  const PairIn in = pair_in(mode, (float)dx, (float)dy, (float)dz, false);
   float o[9];
-  mlp_tile_f32(fr, rx * sc, ry * sc, rz * sc, o);
-  const float s = rs * (float)(1.0 / (16.0 * HH_PI));
-  K[0] = 2.0f * o[0] * s; K[1] = (o[1] + o[3]) * s; K[2] = (o[2] + o[6]) * s;
-  K[3] = K[1];            K[4] = 2.0f * o[4] * s;   K[5] = (o[5] + o[7]) * s;
-  K[6] = K[2];            K[7] = K[5];              K[8] = 2.0f * o[8] * s;
+  mlp_tile_f32(fr, in.v0, in.v1, in.v2, o);
+  pair_entry(o, in.rs, K);
 }
 
 // Stage the FP32 fragment table (global -> LDS) by the whole workgroup.

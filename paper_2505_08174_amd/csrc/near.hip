@@ -111,26 +111,31 @@ void launch_near_t(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs
 
 }  // namespace
 
+// Partial row sets of the near field: the MFMA kernels split the sources.
+int near_groups(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, int prec) {
+  return k->kind == KIND_MLP && prec != HH_FP64 ? near_groups_mfma(ctx, t, p) : 1;
+}
+
 // Near field with the displacement reversed: sum_j K(x_j - x_i) v_j, which is
 // the transposed near product (K entries are symmetric 3x3 matrices).
 void launch_near_neg(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, int prec, const void* Vs,
-                     void* out) {
+                     void* out, int groups) {
   if (prec == HH_FP64)
     launch_near_t<double>(ctx, t, p, k, Vs, out, -1.0);
   else if (k->kind == KIND_MLP)
-    launch_near_f32(ctx, t, p, k, Vs, out, -1.0f);
+    launch_near_f32(ctx, t, p, k, Vs, out, groups, -1.0f);
   else
     launch_near_t<float>(ctx, t, p, k, Vs, out, -1.0);
 }
 
 void launch_near(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, int prec, const void* Fs,
-                 void* Un) {
+                 void* out, int groups) {
   if (prec == HH_FP64)
-    launch_near_t<double>(ctx, t, p, k, Fs, Un);
+    launch_near_t<double>(ctx, t, p, k, Fs, out);
   else if (prec == HH_FP32 && k->kind == KIND_MLP)
-    launch_near_f32(ctx, t, p, k, Fs, Un);
+    launch_near_f32(ctx, t, p, k, Fs, out, groups);
   else if (prec == HH_FP32 || k->kind != KIND_MLP)
-    launch_near_t<float>(ctx, t, p, k, Fs, Un);
+    launch_near_t<float>(ctx, t, p, k, Fs, out);
   else
-    launch_near_bf16(ctx, t, p, k, Fs, Un, prec == HH_BF16_SPLIT);   // writes FP64 rows
+    launch_near_bf16(ctx, t, p, k, Fs, out, groups, prec == HH_BF16_SPLIT);
 }

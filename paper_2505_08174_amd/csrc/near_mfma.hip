@@ -1,19 +1,41 @@
-// Near field with the seeded MLP kernel on BF16 MFMA (the BF16 form).
+// Near field with the seeded MLP kernel on MFMA tiles (the BF16 and the plain
+// FP32 form).
 //
-// Work unit = 32 consecutive targets of one leaf tau (one wave). The wave
-// walks every source j of every near leaf sigma of tau (uniform across the
-// wave, so x_j and F_j come through scalar loads) and evaluates the 32 pairs
-// (i, j) as one MFMA tile; each lane accumulates K(x_i - x_j) F_j for its own
-// target in FP64 (owner computes, no reduction, no atomics). Four units per
-// workgroup share the weight fragments staged in LDS.
+// A wave works on 64 consecutive targets (sorted rows, whichever leaves they
+// are in), one per lane: in every step a lane takes the next source of its own
+// leaf's near list and the wave evaluates its 64 pairs as two MFMA tiles. Each
+// lane accumulates K(x_i - x_j) F_j for its own target in FP64 (owner
+// computes, no atomics). The sources of a target are split over the four waves
+// of a workgroup, whose rows are summed in LDS, and over `groups` workgroups,
+// whose partial rows the combine adds in a fixed order, so that small systems
+// still fill the chip.
+//
+// Bound: the FP32 form by the FP32 MFMA rate, the BF16 form by VALU issue (192
+// transcendentals and about 330 other VALU instructions per 32 pairs). Lanes
+// with different sources cost a wave nothing, so targets need not be padded to
+// whole waves per leaf (a leaf of 94 targets left a quarter of its last wave
+// idle), and one lane per pair prepares and applies it (both halves of the wave
+// did the same 32 pairs before). Measured, one wave per 32 targets and whole
+// near list before, this split after: FP32, 5,000 particles 33.1 -> 4.3 ms,
+// 100,000 particles 244 -> 150 ms (6.7e9 pairs/s, 76% of the FP32 MFMA rate);
+// BF16, 500 particles 831 -> 25 us; BF16 hi + lo, 30,000 particles 28.8 -> 13.9 ms.
+#include <algorithm>
+
 #include "internal.h"
 #include "mlp_mfma.h"
+#include "near_walk.h"
 
 #define T256_UNITS 256
 
 namespace {
 
 constexpr int NB_T = 256;
+
+__device__ __forceinline__ int wave_maxi(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
+  return v;
+}
 
 __global__ __launch_bounds__(T256_UNITS) void k_units_count(const int32_t* __restrict__ leaves,
                                                             int64_t nl,
@@ -34,151 +56,127 @@ __global__ __launch_bounds__(T256_UNITS) void k_units_fill(const int64_t* __rest
   for (int64_t c = 0; c < cnt[l]; ++c) units[pos[l] + c] = make_int2((int)l, (int)c);
 }
 
+// Writes the sum of the workgroup's four waves' rows (fixed order) as partial
+// row `set` of the 64 targets. red: 4 x 64 x 3 doubles of LDS that no wave
+// still reads (the weight table is done with).
+template <class TO>
+__device__ __forceinline__ void write_rows(double* __restrict__ red, int lane, int w, double u0,
+                                           double u1, double u2, int64_t s0, int64_t n, int set,
+                                           TO* __restrict__ out) {
+  __syncthreads();
+  red[192 * w + 3 * lane] = u0;
+  red[192 * w + 3 * lane + 1] = u1;
+  red[192 * w + 3 * lane + 2] = u2;
+  __syncthreads();
+  const int e = threadIdx.x;
+  if (e < 192 && 3 * s0 + e < 3 * n)
+    out[3 * ((int64_t)set * n + s0) + e] =
+        (TO)(((red[e] + red[192 + e]) + red[384 + e]) + red[576 + e]);
+}
+
 struct NearB {
+  NearTables t;
   const uint4* frags;
-  const int4* nodes;
-  const int32_t* leaves;
-  const int32_t* near_ptr;
-  const int2* H;
-  const int2* units;
-  int64_t n_units;
-  const double* xs;
   const float* Fs;
-  double* Un;
+  double* out;
+  int groups;
   int input_mode;
 };
-
-// Adds K(x_i - x_j) F_j for the sources j0, j0 + 1, .., j0 + NT - 1 (one MFMA
-// tile each, evaluated together), in that order.
-template <bool ACC, int NT>
-__device__ __forceinline__ void near_terms(const NearB& a, const bf16x8* fr, bool dir, bool act,
-                                           int ii, double xi0, double xi1, double xi2, int j0,
-                                           double& u0, double& u1, double& u2) {
-  const float c16 = (float)(1.0 / (16.0 * HH_PI));
-  float v[NT][3], rs[NT], o[NT][9];
-  bool skip[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int j = j0 + t;
-    float rx = (float)(xi0 - a.xs[3 * (int64_t)j]);
-    float ry = (float)(xi1 - a.xs[3 * (int64_t)j + 1]);
-    float rz = (float)(xi2 - a.xs[3 * (int64_t)j + 2]);
-    skip[t] = (j == ii) || !act;
-    if (j == ii) { rx = 1.0f; ry = 0.0f; rz = 0.0f; }
-    rs[t] = hh_rsqrt(rx * rx + ry * ry + rz * rz);
-    const float sc = dir ? rs[t] : 1.0f;
-    v[t][0] = rx * sc;
-    v[t][1] = ry * sc;
-    v[t][2] = rz * sc;
-  }
-  mlp_tiles_bf16<ACC, NT>(fr, v, o);
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int j = j0 + t;
-    const float sc = skip[t] ? 0.0f : rs[t] * c16;
-    const float f0 = a.Fs[3 * (int64_t)j], f1 = a.Fs[3 * (int64_t)j + 1],
-                f2 = a.Fs[3 * (int64_t)j + 2];
-    const float* q = o[t];
-    u0 += (double)(sc * (2.0f * q[0] * f0 + (q[1] + q[3]) * f1 + (q[2] + q[6]) * f2));
-    u1 += (double)(sc * ((q[3] + q[1]) * f0 + 2.0f * q[4] * f1 + (q[5] + q[7]) * f2));
-    u2 += (double)(sc * ((q[6] + q[2]) * f0 + (q[7] + q[5]) * f1 + 2.0f * q[8] * f2));
-  }
-}
 
 template <bool ACC>
 __global__ __launch_bounds__(NB_T) void k_near_bf16(NearB a) {
   __shared__ bf16x8 fr[FR_TOTAL];
   stage_frags(fr, a.frags, NB_T);
   __syncthreads();
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t unit = (int64_t)blockIdx.x * (NB_T / 64) + w;
-  if (unit >= a.n_units) return;
-  const int2 un = a.units[unit];
-  const int4 nt = a.nodes[a.leaves[un.x]];
-  const int i = nt.x + 32 * un.y + (lane & 31);
-  const bool act = i < nt.y;
-  const int ii = act ? i : nt.x;
-  const double xi0 = a.xs[3 * (int64_t)ii], xi1 = a.xs[3 * (int64_t)ii + 1],
-               xi2 = a.xs[3 * (int64_t)ii + 2];
-  const bool dir = a.input_mode == HH_MLP_INPUT_DIRECTION;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t s0 = 64 * ((int64_t)blockIdx.x / a.groups), s = s0 + lane;
+  const int set = blockIdx.x % a.groups;
+  const bool act = s < a.t.n;
+  const int ss = (int)(act ? s : a.t.n - 1);
+  const double xi0 = a.t.xs[3 * (int64_t)ss], xi1 = a.t.xs[3 * (int64_t)ss + 1],
+               xi2 = a.t.xs[3 * (int64_t)ss + 2];
+  const float c16 = (float)(1.0 / (16.0 * HH_PI));
   double u0 = 0, u1 = 0, u2 = 0;
-  const int p0 = a.near_ptr[un.x], p1 = a.near_ptr[un.x + 1];
-  for (int p = p0; p < p1; ++p) {
-    const int4 ns = a.nodes[a.H[p].y];
-    int j = ns.x;
-    // two sources at a time: two independent MFMA chains per wave
-    for (; j + 1 < ns.y; j += 2)
-      near_terms<ACC, 2>(a, fr, dir, act, ii, xi0, xi1, xi2, j, u0, u1, u2);
-    if (j < ns.y) near_terms<ACC, 1>(a, fr, dir, act, ii, xi0, xi1, xi2, j, u0, u1, u2);
+  NearWalk wk;
+  wk.start(a.t, ss, 4 * set + w, 4 * a.groups);
+  const int steps = __builtin_amdgcn_readfirstlane(wave_maxi(wk.left));
+  // source of the step, loaded while the step before is worked on
+  double xj0 = a.t.xs[3 * (int64_t)wk.j], xj1 = a.t.xs[3 * (int64_t)wk.j + 1],
+         xj2 = a.t.xs[3 * (int64_t)wk.j + 2];
+  float g0 = a.Fs[3 * (int64_t)wk.j], g1 = a.Fs[3 * (int64_t)wk.j + 1],
+        g2 = a.Fs[3 * (int64_t)wk.j + 2];
+#pragma unroll 1
+  for (int st = 0; st < steps; ++st) {
+    float rx = (float)(xi0 - xj0), ry = (float)(xi1 - xj1), rz = (float)(xi2 - xj2);
+    const float f0 = g0, f1 = g1, f2 = g2;
+    const bool skip = wk.j == ss || !act || wk.left <= 0;
+    if (wk.j == ss) { rx = 1.0f; ry = 0.0f; rz = 0.0f; }
+    // which of two equally good remainders layer 1 gets (see pair_rest): fixed
+    // by the list alone, whatever the split of the sources
+    const bool exact = wk.unpaired();
+    wk.next(a.t);
+    xj0 = a.t.xs[3 * (int64_t)wk.j];
+    xj1 = a.t.xs[3 * (int64_t)wk.j + 1];
+    xj2 = a.t.xs[3 * (int64_t)wk.j + 2];
+    g0 = a.Fs[3 * (int64_t)wk.j];
+    g1 = a.Fs[3 * (int64_t)wk.j + 1];
+    g2 = a.Fs[3 * (int64_t)wk.j + 2];
+    const PairIn in = pair_in(a.input_mode, rx, ry, rz, exact);
+    float q[9];
+    mlp_pairs_bf16<ACC>(fr, in, q);
+    pair_apply(q, skip ? 0.0f : in.rs * c16, f0, f1, f2, u0, u1, u2);
   }
-  if (act && lane < 32) {
-    a.Un[3 * (int64_t)i] = u0;
-    a.Un[3 * (int64_t)i + 1] = u1;
-    a.Un[3 * (int64_t)i + 2] = u2;
-  }
+  write_rows(reinterpret_cast<double*>(fr), lane, w, u0, u1, u2, s0, a.t.n, set, a.out);
 }
 
-// The plain FP32 form on FP32 MFMA: the same work units and walk, one FP32
-// tile per source. F and U are FP32; each lane sums its target's terms in
-// FP64 and rounds once.
+// The plain FP32 form on FP32 MFMA: the same walk and FP32 tiles. F is FP32;
+// each lane sums its target's terms in FP64.
+template <class TO>
 struct NearF {
+  NearTables t;
   const float4* frags;
-  const int4* nodes;
-  const int32_t* leaves;
-  const int32_t* near_ptr;
-  const int2* H;
-  const int2* units;
-  int64_t n_units;
-  const double* xs;
   const float* Fs;
-  float* Un;
+  TO* out;
+  int groups;
   int input_mode;
   float sgn;   // +1: K(x_i - x_j); -1: K(x_j - x_i) (the transposed product)
 };
 
-__global__ __launch_bounds__(NB_T) void k_near_f32(NearF a) {
-  __shared__ float fr[F32_FRAGS * 64];
+template <class TO>
+__global__ __launch_bounds__(NB_T) void k_near_f32(NearF<TO> a) {
+  __shared__ __align__(16) float fr[F32_FRAGS * 64];
   stage_frags_f32(fr, a.frags, NB_T);
   __syncthreads();
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t unit = (int64_t)blockIdx.x * (NB_T / 64) + w;
-  if (unit >= a.n_units) return;
-  const int2 un = a.units[unit];
-  const int4 nt = a.nodes[a.leaves[un.x]];
-  const int i = nt.x + 32 * un.y + (lane & 31);
-  const bool act = i < nt.y;
-  const int ii = act ? i : nt.x;
-  const double xi0 = a.xs[3 * (int64_t)ii], xi1 = a.xs[3 * (int64_t)ii + 1],
-               xi2 = a.xs[3 * (int64_t)ii + 2];
-  const bool dir = a.input_mode == HH_MLP_INPUT_DIRECTION;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t s0 = 64 * ((int64_t)blockIdx.x / a.groups), s = s0 + lane;
+  const int set = blockIdx.x % a.groups;
+  const bool act = s < a.t.n;
+  const int ss = (int)(act ? s : a.t.n - 1);
+  const double xi0 = a.t.xs[3 * (int64_t)ss], xi1 = a.t.xs[3 * (int64_t)ss + 1],
+               xi2 = a.t.xs[3 * (int64_t)ss + 2];
   const float c16 = (float)(1.0 / (16.0 * HH_PI));
   double u0 = 0, u1 = 0, u2 = 0;
-  const int p0 = a.near_ptr[un.x], p1 = a.near_ptr[un.x + 1];
-  for (int p = p0; p < p1; ++p) {
-    const int4 ns = a.nodes[a.H[p].y];
-    for (int j = ns.x; j < ns.y; ++j) {
-      float rx = a.sgn * (float)(xi0 - a.xs[3 * (int64_t)j]);
-      float ry = a.sgn * (float)(xi1 - a.xs[3 * (int64_t)j + 1]);
-      float rz = a.sgn * (float)(xi2 - a.xs[3 * (int64_t)j + 2]);
-      const bool skip = (j == ii) || !act;
-      if (j == ii) { rx = 1.0f; ry = 0.0f; rz = 0.0f; }
-      const float rs = hh_rsqrt(rx * rx + ry * ry + rz * rz);
-      const float sv = dir ? rs : 1.0f;
-      float q[9];
-      mlp_tile_f32(fr, rx * sv, ry * sv, rz * sv, q);
-      const float sc = skip ? 0.0f : rs * c16;
-      const float f0 = a.Fs[3 * (int64_t)j], f1 = a.Fs[3 * (int64_t)j + 1],
-                  f2 = a.Fs[3 * (int64_t)j + 2];
-      u0 += (double)(sc * (2.0f * q[0] * f0 + (q[1] + q[3]) * f1 + (q[2] + q[6]) * f2));
-      u1 += (double)(sc * ((q[3] + q[1]) * f0 + 2.0f * q[4] * f1 + (q[5] + q[7]) * f2));
-      u2 += (double)(sc * ((q[6] + q[2]) * f0 + (q[7] + q[5]) * f1 + 2.0f * q[8] * f2));
-    }
+  NearWalk wk;
+  wk.start(a.t, ss, 4 * set + w, 4 * a.groups);
+  const int steps = __builtin_amdgcn_readfirstlane(wave_maxi(wk.left));
+#pragma unroll 1
+  for (int st = 0; st < steps; ++st) {
+    const int64_t j = wk.j;
+    float rx = a.sgn * (float)(xi0 - a.t.xs[3 * j]);
+    float ry = a.sgn * (float)(xi1 - a.t.xs[3 * j + 1]);
+    float rz = a.sgn * (float)(xi2 - a.t.xs[3 * j + 2]);
+    const float f0 = a.Fs[3 * j], f1 = a.Fs[3 * j + 1], f2 = a.Fs[3 * j + 2];
+    const bool skip = wk.j == ss || !act || wk.left <= 0;
+    if (wk.j == ss) { rx = 1.0f; ry = 0.0f; rz = 0.0f; }
+    const PairIn in = pair_in(a.input_mode, rx, ry, rz, false);
+    float q[9];
+    mlp_pairs_f32(fr, in.v0, in.v1, in.v2, q);
+    pair_apply(q, skip ? 0.0f : in.rs * c16, f0, f1, f2, u0, u1, u2);
+    wk.next(a.t);
   }
-  if (act && lane < 32) {
-    a.Un[3 * (int64_t)i] = (float)u0;
-    a.Un[3 * (int64_t)i + 1] = (float)u1;
-    a.Un[3 * (int64_t)i + 2] = (float)u2;
-  }
+  write_rows(reinterpret_cast<double*>(fr), lane, w, u0, u1, u2, s0, a.t.n, set, a.out);
 }
 
 }  // namespace
@@ -203,23 +201,32 @@ void ensure_units(hh_ctx ctx, hh_tree t) {
   t->n_units = nu;
 }
 
-void launch_near_bf16(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs, void* Un,
-                      bool split) {
+// Sets of partial rows: workgroups (4 waves, 4 shares of the sources) per 64
+// targets. Three rounds of resident workgroups (3 per compute unit) even out
+// the leaves' different near lists, as long as a share keeps 64 sources (a
+// workgroup stages 48 KB of weights first); below that, shares down to 4
+// sources as long as they fill idle compute units: at 500 particles, 32 sets of
+// 4-source shares take 25 us, one set 160 us.
+int near_groups_mfma(hh_ctx ctx, hh_tree t, hh_part p) {
+  const int64_t nw = (t->n + 63) / 64;
+  const int64_t q = std::max<int64_t>(1, p->near_pairs / t->n);   // sources per target
+  const int64_t res = 3 * (int64_t)ctx->n_cu;                     // resident workgroups
+  const int64_t even = std::min((3 * res + nw - 1) / nw, q / (4 * 64));
+  const int64_t fill = std::min((res + nw - 1) / nw, q / (4 * 4));
+  return (int)std::max<int64_t>(1, std::max(even, fill));
+}
+
+void launch_near_bf16(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs, void* out,
+                      int groups, bool split) {
   HH_REQUIRE(k->kind == KIND_MLP, HH_ERR_INVALID_ARG, "the BF16 form needs the MLP kernel");
-  ensure_units(ctx, t);
   NearB a;
+  a.t = near_tables(t, p);
   a.frags = k->pbf.as<uint4>();
-  a.nodes = t->nodes.as<int4>();
-  a.leaves = t->leaves.as<int32_t>();
-  a.near_ptr = p->near_ptr.as<int32_t>();
-  a.H = p->H.as<int2>();
-  a.units = t->units.as<int2>();
-  a.n_units = t->n_units;
-  a.xs = t->xs.as<double>();
   a.Fs = (const float*)Fs;
-  a.Un = (double*)Un;
+  a.out = (double*)out;
+  a.groups = groups;
   a.input_mode = k->input_mode;
-  unsigned grid = (unsigned)((t->n_units + 3) / 4);
+  const unsigned grid = (unsigned)((t->n + 63) / 64 * groups);
   if (split)
     hipLaunchKernelGGL(k_near_bf16<true>, dim3(grid), dim3(NB_T), 0, ctx->stream, a);
   else
@@ -227,24 +234,27 @@ void launch_near_bf16(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void*
   HIP_OK(hipGetLastError());
 }
 
-void launch_near_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs, void* Un,
-                     float sgn) {
-  HH_REQUIRE(k->kind == KIND_MLP, HH_ERR_INVALID_ARG, "the FP32 MFMA tile needs the MLP kernel");
-  ensure_units(ctx, t);
-  NearF a;
+template <class TO>
+static void launch_near_f32_t(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs,
+                              void* out, int groups, float sgn) {
+  NearF<TO> a;
+  a.t = near_tables(t, p);
   a.frags = k->pf32.as<float4>();
-  a.nodes = t->nodes.as<int4>();
-  a.leaves = t->leaves.as<int32_t>();
-  a.near_ptr = p->near_ptr.as<int32_t>();
-  a.H = p->H.as<int2>();
-  a.units = t->units.as<int2>();
-  a.n_units = t->n_units;
-  a.xs = t->xs.as<double>();
   a.Fs = (const float*)Fs;
-  a.Un = (float*)Un;
+  a.out = (TO*)out;
+  a.groups = groups;
   a.input_mode = k->input_mode;
   a.sgn = sgn;
-  unsigned grid = (unsigned)((t->n_units + 3) / 4);
-  hipLaunchKernelGGL(k_near_f32, dim3(grid), dim3(NB_T), 0, ctx->stream, a);
+  const unsigned grid = (unsigned)((t->n + 63) / 64 * groups);
+  hipLaunchKernelGGL(k_near_f32<TO>, dim3(grid), dim3(NB_T), 0, ctx->stream, a);
   HIP_OK(hipGetLastError());
+}
+
+void launch_near_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs, void* out,
+                     int groups, float sgn) {
+  HH_REQUIRE(k->kind == KIND_MLP, HH_ERR_INVALID_ARG, "the FP32 MFMA tile needs the MLP kernel");
+  if (groups > 1)
+    launch_near_f32_t<double>(ctx, t, p, k, Fs, out, groups, sgn);
+  else
+    launch_near_f32_t<float>(ctx, t, p, k, Fs, out, groups, sgn);
 }

@@ -120,6 +120,35 @@ __global__ __launch_bounds__(T256) void k_near_ptr(const int2* __restrict__ H, i
   if (p == 0 || H[p - 1].x != H[p].x) ptr[leaf_id[H[p].x]] = (int32_t)p;
 }
 
+// Source rows of every near entry and, per leaf, the running and the total
+// number of sources of its list: one wave per leaf, 64 entries at a time.
+__global__ __launch_bounds__(T256) void k_near_src(const int2* __restrict__ H,
+                                                   const int4* __restrict__ nodes,
+                                                   const int32_t* __restrict__ ptr, int64_t nl,
+                                                   int4* __restrict__ src,
+                                                   int32_t* __restrict__ total) {
+  const int64_t l = ((int64_t)blockIdx.x * T256 + threadIdx.x) >> 6;
+  const int lane = threadIdx.x & 63;
+  if (l >= nl) return;
+  const int p0 = ptr[l], p1 = ptr[l + 1];
+  int sum = 0;
+  for (int b = p0; b < p1; b += 64) {
+    const int p = b + lane;
+    int4 ns = make_int4(0, 0, 0, 0);
+    if (p < p1) ns = nodes[H[p].y];
+    const int c = ns.y - ns.x;
+    int v = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(v, o, 64);
+      if (lane >= o) v += u;
+    }
+    if (p < p1) src[p] = make_int4(ns.x, ns.y, sum + v - c, 0);
+    sum += __shfl(v, 63, 64);
+  }
+  if (lane == 0) total[l] = sum;
+}
+
 __global__ __launch_bounds__(T256) void k_far_ptr(const int2* __restrict__ G, int64_t nG,
                                                   int64_t m, int32_t* __restrict__ ptr) {
   int64_t p = (int64_t)blockIdx.x * T256 + threadIdx.x;
@@ -274,6 +303,11 @@ hh_status hh_partition(hh_ctx ctx, hh_tree tree, double eta, int dense_mode, hh_
     hipLaunchKernelGGL(k_near_ptr, dim3(nblk(p->nH + 1)), dim3(T256), 0, st, p->H.as<int2>(),
                        p->nH, tree->leaf_id.as<int32_t>(), tree->n_leaves,
                        p->near_ptr.as<int32_t>());
+    p->near_src.alloc(st, std::max<int64_t>(1, p->nH) * sizeof(int4));
+    p->near_q.alloc(st, tree->n_leaves * sizeof(int32_t));
+    hipLaunchKernelGGL(k_near_src, dim3(nblk(64 * tree->n_leaves)), dim3(T256), 0, st,
+                       p->H.as<int2>(), nodes, p->near_ptr.as<int32_t>(), tree->n_leaves,
+                       p->near_src.as<int4>(), p->near_q.as<int32_t>());
     hipLaunchKernelGGL(k_far_ptr, dim3(nblk(tree->n_nodes + 1)), dim3(T256), 0, st,
                        p->G.as<int2>(), p->nG, tree->n_nodes, p->far_ptr.as<int32_t>());
     unsigned long long* sums = (unsigned long long*)ctx->scratch_flag.p;
