@@ -577,14 +577,30 @@ __global__ __launch_bounds__(TB) void k_fallback_bwd(const int2* __restrict__ G,
   }
 }
 
-// dparams[i] += sum over workgroup partials, fixed order.
-__global__ __launch_bounds__(TB) void k_param_reduce(const double* __restrict__ part, int nparts,
-                                                     double* __restrict__ out) {
-  int i = blockIdx.x * TB + threadIdx.x;
-  if (i >= MLP_NP) return;
+// dparams[i] += sum over the partial slots in a fixed order: PR_P parameters
+// per workgroup, its PR_G thread groups taking a run of slots each. Bound by the
+// one read of the slots: one thread per parameter and one serial run over 2,304
+// slots took 570-680 us (36 workgroups in flight).
+constexpr int PR_P = 32, PR_G = 32;
+__global__ __launch_bounds__(PR_P * PR_G) void k_param_reduce(const double* __restrict__ part,
+                                                              int nparts,
+                                                              double* __restrict__ out) {
+  __shared__ double red[PR_G][PR_P];
+  const int x = threadIdx.x % PR_P, g = threadIdx.x / PR_P;
+  const int i = blockIdx.x * PR_P + x;
+  const int run = (nparts + PR_G - 1) / PR_G;
   double s = 0;
-  for (int p = 0; p < nparts; ++p) s += part[(int64_t)p * MLP_NP + i];
-  out[i] += s;
+  if (i < MLP_NP) {
+    const int p1 = min(nparts, (g + 1) * run);
+#pragma unroll 8
+    for (int p = g * run; p < p1; ++p) s += part[(int64_t)p * MLP_NP + i];
+  }
+  red[g][x] = s;
+  __syncthreads();
+  if (g == 0 && i < MLP_NP) {
+    for (int w = 1; w < PR_G; ++w) s += red[w][x];
+    out[i] += s;
+  }
 }
 
 template <class T>
@@ -682,7 +698,10 @@ void backward_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, co
   const int gnear = mf ? (int)vjp_f32_waves(ctx) : (int)t->n_leaves;
   const int gfar = mf ? (int)vjp_f32_waves(ctx)
                       : (int)std::min<int64_t>(std::max<int64_t>(nG, 1), 2048);
-  const int nparts = gnear + gfar + gfb;   // dtheta partial slots: near, far, fallback
+  // dtheta partial slots: near, far, and fallback where a block fell back
+  const int nparts = gnear + gfar + (lr->n_fallback > 0 ? gfb : 0);
+  DevBuf pre;   // items of the MFMA kernels' sequences
+  if (mlp && mf) pre.alloc(st, (vjp_f32_waves(ctx) + 1) * sizeof(int64_t));
   if (mlp) {
     part.alloc(st, (int64_t)nparts * MLP_NP * sizeof(double));
     HIP_OK(hipMemsetAsync(part.p, 0, (int64_t)nparts * MLP_NP * sizeof(double), st));
@@ -699,7 +718,8 @@ void backward_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, co
                        farT.as<double>());
     if (mlp && mf)
       launch_far_vjp_f32(ctx, t, p, lr, k, b0, b1, goff.as<int64_t>(), gpool.as<float>(),
-                         dXs.as<double>(), part.as<double>() + (int64_t)gnear * MLP_NP);
+                         dXs.as<double>(), part.as<double>() + (int64_t)gnear * MLP_NP,
+                         pre.as<int64_t>());
     else if (mlp)
       hipLaunchKernelGGL((k_far_vjp<T>), dim3(gfar), dim3(TB), 0, st, p->G.as<int2>(), b0, b1,
                          t->nodes.as<int4>(), lr->rank.as<int32_t>(), lr->flag.as<int32_t>(),
@@ -741,7 +761,7 @@ void backward_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, co
   if (mlp) {
     if constexpr (mf)
       launch_near_vjp_f32(ctx, t, p, k, Fs.as<float>(), ws.as<float>(), dXs.as<double>(),
-                          part.as<double>());
+                          part.as<double>(), pre.as<int64_t>());
     else
       hipLaunchKernelGGL((k_near_vjp<T>), dim3(gnear), dim3(TB), 0, st, t->nodes.as<int4>(),
                          t->leaves.as<int32_t>(), p->near_ptr.as<int32_t>(), p->H.as<int2>(),
@@ -752,8 +772,8 @@ void backward_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, co
       hipLaunchKernelGGL(k_scatter_dX, dim3(nblk(n)), dim3(TB), 0, st, dXs.as<double>(),
                          t->perm.as<int32_t>(), n, dX);
     if (dparams)
-      hipLaunchKernelGGL(k_param_reduce, dim3((MLP_NP + TB - 1) / TB), dim3(TB), 0, st,
-                         part.as<double>(), nparts, dparams);
+      hipLaunchKernelGGL(k_param_reduce, dim3((MLP_NP + PR_P - 1) / PR_P), dim3(PR_P * PR_G), 0,
+                         st, part.as<double>(), nparts, dparams);
     HIP_OK(hipGetLastError());
   }
 }

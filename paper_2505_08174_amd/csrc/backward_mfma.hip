@@ -20,8 +20,8 @@
 //   input cotangent dL/dv = W1^T D1, then dL/dr through the direction input
 //           and through s.
 // Near pairs: work unit = 32 targets of a leaf against every source of its
-// near list (one source per tile, as the forward near field); the source's
-// dX is the wave sum of its 32 pairs, added with one atomic per component.
+// near list, one source per tile; the source's dX is the wave sum of its 32
+// pairs, added with one atomic per component.
 // Far pairs: the samples of every ACA term of a block, 32 per tile; a column
 // term's samples share x_j and a row term's share x_i, so that side is also
 // summed over the tile before its atomic.
@@ -340,20 +340,101 @@ __device__ __forceinline__ void stage_tables(float* fw, float* bw, const VjpArgs
   for (int i = threadIdx.x; i < BW_FRAGS * 64; i += VB) bw[i] = a.bw[i];
 }
 
-// Near pairs: persistent waves over the work units (fixed assignment, so the
-// slot sums are reproducible).
+// Work items: the tiles of the near units (or of the admissible blocks) are
+// dealt to vjp_f32_waves() sequences, unit u (block b) to sequence u mod that,
+// and every sequence is cut into items of FLUSH tiles, the span over which the
+// parameter gradients are summed in FP32. The items, not the sequences, are
+// spread over the waves: all but one in a row of items take the same time, and
+// a small system has far more items than units. Which tiles share an FP32 sum
+// depends on the sequences alone. Bound by the FP32 MFMA (435 of 64 cycles per
+// tile). One wave per sequence took 39 ms for the near pairs of 2,000 particles
+// (64 of 1,024 waves at work) and 301 ms at 16,000; by items 4.0 and 60 ms. The
+// sampled pairs of 16,000 particles went from 39 to 25 ms.
+// k_items writes the running number of items of the sequences (one thread per
+// sequence; pre[seqs] is the total).
+constexpr int SEQ_MAX = 1024;
+
+template <class Tiles>
+__device__ __forceinline__ void items_scan(int seqs, int64_t n, Tiles tiles,
+                                           int64_t* __restrict__ pre) {
+  __shared__ int64_t sum[SEQ_MAX];
+  // sequences in rounds of SEQ_MAX threads
+  int64_t carry = 0;
+  for (int s0 = 0; s0 < seqs; s0 += SEQ_MAX) {
+    const int v = s0 + threadIdx.x;
+    int64_t t = 0;
+    if (v < seqs)
+      for (int64_t u = v; u < n; u += seqs) t += tiles(u);
+    const int64_t mine = (t + FLUSH - 1) / FLUSH;
+    sum[threadIdx.x] = mine;
+    __syncthreads();
+    for (int o = 1; o < SEQ_MAX; o <<= 1) {
+      const int64_t x = (int)threadIdx.x >= o ? sum[threadIdx.x - o] : 0;
+      __syncthreads();
+      sum[threadIdx.x] += x;
+      __syncthreads();
+    }
+    if (v < seqs) pre[v] = carry + sum[threadIdx.x] - mine;
+    carry += sum[SEQ_MAX - 1];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) pre[seqs] = carry;
+}
+
+__global__ __launch_bounds__(SEQ_MAX) void k_near_items(int seqs, const int2* __restrict__ units,
+                                                        int64_t n_units,
+                                                        const int32_t* __restrict__ near_q,
+                                                        int64_t* __restrict__ pre) {
+  items_scan(seqs, n_units, [&](int64_t u) { return (int64_t)near_q[units[u].x]; }, pre);
+}
+
+__device__ __forceinline__ int64_t block_tiles(const int2* __restrict__ G,
+                                               const int4* __restrict__ nodes,
+                                               const int32_t* __restrict__ rank,
+                                               const int32_t* __restrict__ flag, int64_t b) {
+  if (flag[b]) return 0;
+  const int4 nt = nodes[G[b].x], ns = nodes[G[b].y];
+  return (int64_t)rank[b] * (((nt.y - nt.x) + (ns.y - ns.x) + 31) / 32);
+}
+
+__global__ __launch_bounds__(SEQ_MAX) void k_far_items(int seqs, const int2* __restrict__ G,
+                                                       const int4* __restrict__ nodes,
+                                                       const int32_t* __restrict__ rank,
+                                                       const int32_t* __restrict__ flag,
+                                                       int64_t b0, int64_t b1,
+                                                       int64_t* __restrict__ pre) {
+  items_scan(seqs, b1 - b0,
+             [&](int64_t u) { return block_tiles(G, nodes, rank, flag, b0 + u); }, pre);
+}
+
+// The sequence that item `it` belongs to: the last v with pre[v] <= it (a
+// sequence without items is never the last).
+__device__ __forceinline__ int item_seq(const int64_t* __restrict__ pre, int seqs, int64_t it) {
+  int a = 0, b = seqs - 1;
+  while (a < b) {
+    const int m = (a + b + 1) / 2;
+    if (pre[m] <= it) a = m; else b = m - 1;
+  }
+  return a;
+}
+
+// Near pairs: a tile is 32 targets of one unit and one source.
 __global__ __launch_bounds__(VB) void k_near_vjp_f32(VjpArgs a, const int32_t* __restrict__ leaves,
                                                      const int32_t* __restrict__ near_ptr,
-                                                     const int2* __restrict__ H,
+                                                     const int4* __restrict__ src,
+                                                     const int32_t* __restrict__ near_q,
                                                      const int2* __restrict__ units,
-                                                     int64_t n_units, const float* __restrict__ Fs,
+                                                     int64_t n_units,
+                                                     const int64_t* __restrict__ pre, int seqs,
+                                                     const float* __restrict__ Fs,
                                                      const float* __restrict__ ws) {
   __shared__ float fw[F32_FRAGS * 64];
   __shared__ float bw[BW_FRAGS * 64];
   __shared__ float xbuf[VB / 64][2][64 * XS];
   stage_tables(fw, bw, a);
   __syncthreads();
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, p = lane & 31;
+  const int lane = threadIdx.x & 63, p = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* XD = xbuf[w][0];
   float* XH = xbuf[w][1];
   const int64_t wave = (int64_t)blockIdx.x * (VB / 64) + w, nw = (int64_t)gridDim.x * (VB / 64);
@@ -362,78 +443,99 @@ __global__ __launch_bounds__(VB) void k_near_vjp_f32(VjpArgs a, const int32_t* _
   const float c8 = (float)(1.0 / (8.0 * HH_PI));
   VjpAcc A;
   acc_zero(A);
-  int tiles = 0;
-  for (int64_t u = wave; u < n_units; u += nw) {
-    const int2 un = units[u];
-    const int4 nt = a.nodes[leaves[un.x]];
-    const int i = nt.x + 32 * un.y + p;
-    const bool act = i < nt.y;
-    const int ii = act ? i : nt.x;
-    const double xi0 = a.xs[3 * (int64_t)ii], xi1 = a.xs[3 * (int64_t)ii + 1],
-                 xi2 = a.xs[3 * (int64_t)ii + 2];
-    const float w0 = ws[3 * (int64_t)ii], w1 = ws[3 * (int64_t)ii + 1], w2 = ws[3 * (int64_t)ii + 2];
-    double t0 = 0, t1 = 0, t2 = 0;
-    for (int pp = near_ptr[un.x]; pp < near_ptr[un.x + 1]; ++pp) {
-      const int4 ns = a.nodes[H[pp].y];
-      for (int j = ns.x; j < ns.y; ++j) {
-        float rx = (float)(xi0 - a.xs[3 * (int64_t)j]);
-        float ry = (float)(xi1 - a.xs[3 * (int64_t)j + 1]);
-        float rz = (float)(xi2 - a.xs[3 * (int64_t)j + 2]);
-        const bool skip = (j == ii) || !act;
-        if (j == ii) { rx = 1.0f; ry = 0.0f; rz = 0.0f; }
-        const float rs = hh_rsqrt(rx * rx + ry * ry + rz * rz);
-        const float sv = dir ? rs : 1.0f;
-        const float v0 = rx * sv, v1 = ry * sv, v2 = rz * sv;
-        const float f0 = Fs[3 * (int64_t)j], f1 = Fs[3 * (int64_t)j + 1],
-                    f2 = Fs[3 * (int64_t)j + 2];
-        const float u0 = skip ? 0.0f : w0, u1 = skip ? 0.0f : w1, u2 = skip ? 0.0f : w2;
-        // symmetric part of the cotangent w_i F_j^T
-        const float g[9] = {u0 * f0, 0.5f * (u0 * f1 + u1 * f0), 0.5f * (u0 * f2 + u2 * f0),
-                            0.5f * (u1 * f0 + u0 * f1), u1 * f1, 0.5f * (u1 * f2 + u2 * f1),
-                            0.5f * (u2 * f0 + u0 * f2), 0.5f * (u2 * f1 + u1 * f2), u2 * f2};
-        float gv[3], og, dr[3];
-        vjp_tile_f32(fw, bw, XD, XH, A, v0, v1, v2, g, rs * c8, gv, og);
-        pair_dr(dir, rx, ry, rz, rs, v0, v1, v2, gv, og, dr);
-        if (!skip) { t0 += dr[0]; t1 += dr[1]; t2 += dr[2]; }
-        const float s0 = half0_sum(skip ? 0.0f : dr[0]);
-        const float s1 = half0_sum(skip ? 0.0f : dr[1]);
-        const float s2 = half0_sum(skip ? 0.0f : dr[2]);
-        if (lane == 0) {
-          atomicAdd(a.dXs + 3 * (int64_t)j, -(double)s0);
-          atomicAdd(a.dXs + 3 * (int64_t)j + 1, -(double)s1);
-          atomicAdd(a.dXs + 3 * (int64_t)j + 2, -(double)s2);
-        }
-        if (++tiles == FLUSH) {
-          acc_flush(A, slot);
-          tiles = 0;
+  const int64_t items = pre[seqs];
+  for (int64_t it = wave; it < items; it += nw) {
+    const int v = item_seq(pre, seqs, it);
+    int64_t skip = FLUSH * (it - pre[v]);   // tiles of the sequence before this item
+    int left = FLUSH;
+    for (int64_t u = v; u < n_units && left > 0; u += seqs) {
+      const int2 un = units[u];
+      const int q = near_q[un.x];
+      if (skip >= q) {
+        skip -= q;
+        continue;
+      }
+      const int4 nt = a.nodes[leaves[un.x]];
+      const int i = nt.x + 32 * un.y + p;
+      const bool act = i < nt.y;
+      const int ii = act ? i : nt.x;
+      const double xi0 = a.xs[3 * (int64_t)ii], xi1 = a.xs[3 * (int64_t)ii + 1],
+                   xi2 = a.xs[3 * (int64_t)ii + 2];
+      const float w0 = ws[3 * (int64_t)ii], w1 = ws[3 * (int64_t)ii + 1],
+                  w2 = ws[3 * (int64_t)ii + 2];
+      double t0 = 0, t1 = 0, t2 = 0;
+      // list entry that holds source number `skip` of the unit's list
+      int e0 = near_ptr[un.x], e1 = near_ptr[un.x + 1] - 1;
+      while (e0 < e1) {
+        const int m = (e0 + e1 + 1) / 2;
+        if (src[m].z <= skip) e0 = m; else e1 = m - 1;
+      }
+      int todo = (int)min((int64_t)left, (int64_t)q - skip);
+      left -= todo;
+      for (int pp = e0; todo > 0; ++pp) {
+        const int4 e = src[pp];
+        const int jb = e.x + (int)(skip - e.z), jn = min(e.y - jb, todo);
+        skip += jn;
+        todo -= jn;
+        for (int j = jb; j < jb + jn; ++j) {
+          float rx = (float)(xi0 - a.xs[3 * (int64_t)j]);
+          float ry = (float)(xi1 - a.xs[3 * (int64_t)j + 1]);
+          float rz = (float)(xi2 - a.xs[3 * (int64_t)j + 2]);
+          const bool none = (j == ii) || !act;
+          if (j == ii) { rx = 1.0f; ry = 0.0f; rz = 0.0f; }
+          const float rs = hh_rsqrt(pair_norm2(rx, ry, rz));
+          const float sv = dir ? rs : 1.0f;
+          const float v0 = rx * sv, v1 = ry * sv, v2 = rz * sv;
+          const float f0 = Fs[3 * (int64_t)j], f1 = Fs[3 * (int64_t)j + 1],
+                      f2 = Fs[3 * (int64_t)j + 2];
+          const float u0 = none ? 0.0f : w0, u1 = none ? 0.0f : w1, u2 = none ? 0.0f : w2;
+          // symmetric part of the cotangent w_i F_j^T
+          const float g[9] = {u0 * f0, 0.5f * (u0 * f1 + u1 * f0), 0.5f * (u0 * f2 + u2 * f0),
+                              0.5f * (u1 * f0 + u0 * f1), u1 * f1, 0.5f * (u1 * f2 + u2 * f1),
+                              0.5f * (u2 * f0 + u0 * f2), 0.5f * (u2 * f1 + u1 * f2), u2 * f2};
+          float gv[3], og, dr[3];
+          vjp_tile_f32(fw, bw, XD, XH, A, v0, v1, v2, g, rs * c8, gv, og);
+          pair_dr(dir, rx, ry, rz, rs, v0, v1, v2, gv, og, dr);
+          if (!none) { t0 += dr[0]; t1 += dr[1]; t2 += dr[2]; }
+          const float s0 = half0_sum(none ? 0.0f : dr[0]);
+          const float s1 = half0_sum(none ? 0.0f : dr[1]);
+          const float s2 = half0_sum(none ? 0.0f : dr[2]);
+          if (lane == 0) {
+            atomicAdd(a.dXs + 3 * (int64_t)j, -(double)s0);
+            atomicAdd(a.dXs + 3 * (int64_t)j + 1, -(double)s1);
+            atomicAdd(a.dXs + 3 * (int64_t)j + 2, -(double)s2);
+          }
         }
       }
+      skip = 0;
+      if (act && lane < 32) {
+        atomicAdd(a.dXs + 3 * (int64_t)i, t0);
+        atomicAdd(a.dXs + 3 * (int64_t)i + 1, t1);
+        atomicAdd(a.dXs + 3 * (int64_t)i + 2, t2);
+      }
     }
-    if (act && lane < 32) {
-      atomicAdd(a.dXs + 3 * (int64_t)i, t0);
-      atomicAdd(a.dXs + 3 * (int64_t)i + 1, t1);
-      atomicAdd(a.dXs + 3 * (int64_t)i + 2, t2);
-    }
+    acc_flush(A, slot);
   }
-  acc_flush(A, slot);
 }
 
 // Sampled far pairs: the column samples (i, j_k) and row samples (i_k, j) of
-// every term k of every admissible block, with the cotangents the ACA
-// adjoint left in the pool; persistent waves over the blocks [b0, b1).
+// every term k of every admissible block of [b0, b1), with the cotangents the
+// ACA adjoint left in the pool; a tile is 32 samples of one term.
 __global__ __launch_bounds__(VB) void k_far_vjp_f32(VjpArgs a, const int2* __restrict__ G,
                                                     int64_t b0, int64_t b1,
                                                     const int32_t* __restrict__ rank,
                                                     const int32_t* __restrict__ flag,
                                                     const int32_t* __restrict__ piv,
                                                     const int64_t* __restrict__ goff,
-                                                    const float* __restrict__ gpool) {
+                                                    const float* __restrict__ gpool,
+                                                    const int64_t* __restrict__ pre, int seqs) {
   __shared__ float fw[F32_FRAGS * 64];
   __shared__ float bw[BW_FRAGS * 64];
   __shared__ float xbuf[VB / 64][2][64 * XS];
   stage_tables(fw, bw, a);
   __syncthreads();
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, p = lane & 31;
+  const int lane = threadIdx.x & 63, p = lane & 31;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* XD = xbuf[w][0];
   float* XH = xbuf[w][1];
   const int64_t wave = (int64_t)blockIdx.x * (VB / 64) + w, nw = (int64_t)gridDim.x * (VB / 64);
@@ -442,17 +544,29 @@ __global__ __launch_bounds__(VB) void k_far_vjp_f32(VjpArgs a, const int2* __res
   const float c8 = (float)(1.0 / (8.0 * HH_PI));
   VjpAcc A;
   acc_zero(A);
-  int tiles = 0;
-  for (int64_t b = b0 + wave; b < b1; b += nw) {
-    if (flag[b] || rank[b] == 0) continue;
-    const int2 gb = G[b];
-    const int4 nt = a.nodes[gb.x], ns = a.nodes[gb.y];
-    const int c = nt.y - nt.x, q = ns.y - ns.x, l = rank[b];
-    for (int k = 0; k < l; ++k) {
-      const int ik = piv[b * 2 * LMAX_CAP + k], jk = piv[b * 2 * LMAX_CAP + LMAX_CAP + k];
-      const float* gc = gpool + goff[b] + 9 * (int64_t)k * (c + q);
-      const float* gr = gc + 9 * (int64_t)c;
-      for (int t0 = 0; t0 < c + q; t0 += 32) {
+  const int64_t items = pre[seqs];
+  for (int64_t it = wave; it < items; it += nw) {
+    const int v = item_seq(pre, seqs, it);
+    int64_t skip = FLUSH * (it - pre[v]);   // tiles of the sequence before this item
+    int left = FLUSH;
+    for (int64_t b = b0 + v; b < b1 && left > 0; b += seqs) {
+      const int64_t nt_b = block_tiles(G, a.nodes, rank, flag, b);
+      if (skip >= nt_b) {
+        skip -= nt_b;
+        continue;
+      }
+      const int2 gb = G[b];
+      const int4 nt = a.nodes[gb.x], ns = a.nodes[gb.y];
+      const int c = nt.y - nt.x, q = ns.y - ns.x;
+      const int per = (c + q + 31) / 32;   // tiles of a term
+      const int todo = (int)min((int64_t)left, nt_b - skip);
+      left -= todo;
+      int k = (int)(skip / per), t0 = 32 * (int)(skip % per);
+      skip = 0;
+      for (int n = 0; n < todo; ++n) {
+        const int ik = piv[b * 2 * LMAX_CAP + k], jk = piv[b * 2 * LMAX_CAP + LMAX_CAP + k];
+        const float* gc = gpool + goff[b] + 9 * (int64_t)k * (c + q);
+        const float* gr = gc + 9 * (int64_t)c;
         const int t = t0 + p;
         const bool ok = t < c + q;
         const int tt = ok ? t : 0;
@@ -469,7 +583,7 @@ __global__ __launch_bounds__(VB) void k_far_vjp_f32(VjpArgs a, const int2* __res
         const float rx = (float)(a.xs[3 * (int64_t)i] - a.xs[3 * (int64_t)j]);
         const float ry = (float)(a.xs[3 * (int64_t)i + 1] - a.xs[3 * (int64_t)j + 1]);
         const float rz = (float)(a.xs[3 * (int64_t)i + 2] - a.xs[3 * (int64_t)j + 2]);
-        const float rs = hh_rsqrt(rx * rx + ry * ry + rz * rz);
+        const float rs = hh_rsqrt(pair_norm2(rx, ry, rz));
         const float sv = dir ? rs : 1.0f;
         const float v0 = rx * sv, v1 = ry * sv, v2 = rz * sv;
         float gv[3], og, dr[3];
@@ -493,14 +607,15 @@ __global__ __launch_bounds__(VB) void k_far_vjp_f32(VjpArgs a, const int2* __res
               atomicAdd(a.dXs + 3 * (int64_t)j + d, -(double)dr[d]);
           }
         }
-        if (++tiles == FLUSH) {
-          acc_flush(A, slot);
-          tiles = 0;
+        t0 += 32;
+        if (t0 >= c + q) {
+          t0 = 0;
+          ++k;
         }
       }
     }
+    acc_flush(A, slot);
   }
-  acc_flush(A, slot);
 }
 
 }  // namespace
@@ -522,24 +637,32 @@ static VjpArgs vjp_args(hh_tree t, hh_kernel k, double* dXs, double* slots) {
   return a;
 }
 
-// Near pairs: slots [vjp_f32_waves] x MLP_NP doubles (zeroed by the caller).
+// Near pairs: slots [vjp_f32_waves] x MLP_NP doubles (zeroed by the caller),
+// pre: vjp_f32_waves + 1 int64 of scratch.
 void launch_near_vjp_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const float* Fs,
-                         const float* ws, double* dXs, double* slots) {
+                         const float* ws, double* dXs, double* slots, int64_t* pre) {
   ensure_units(ctx, t);
   const VjpArgs a = vjp_args(t, k, dXs, slots);
-  hipLaunchKernelGGL(k_near_vjp_f32, dim3((unsigned)(vjp_f32_waves(ctx) / 4)), dim3(VB), 0,
-                     ctx->stream, a, t->leaves.as<int32_t>(), p->near_ptr.as<int32_t>(),
-                     p->H.as<int2>(), t->units.as<int2>(), t->n_units, Fs, ws);
+  const int seqs = (int)vjp_f32_waves(ctx);
+  hipLaunchKernelGGL(k_near_items, dim3(1), dim3(SEQ_MAX), 0, ctx->stream, seqs,
+                     t->units.as<int2>(), t->n_units, p->near_q.as<int32_t>(), pre);
+  hipLaunchKernelGGL(k_near_vjp_f32, dim3((unsigned)(seqs / 4)), dim3(VB), 0, ctx->stream, a,
+                     t->leaves.as<int32_t>(), p->near_ptr.as<int32_t>(), p->near_src.as<int4>(),
+                     p->near_q.as<int32_t>(), t->units.as<int2>(), t->n_units, pre, seqs, Fs, ws);
   HIP_OK(hipGetLastError());
 }
 
-// Sampled pairs of the blocks [b0, b1): slots as above (added to).
+// Sampled pairs of the blocks [b0, b1): slots and pre as above (slots added to).
 void launch_far_vjp_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k,
                         int64_t b0, int64_t b1, const int64_t* goff, const float* gpool,
-                        double* dXs, double* slots) {
+                        double* dXs, double* slots, int64_t* pre) {
   const VjpArgs a = vjp_args(t, k, dXs, slots);
-  hipLaunchKernelGGL(k_far_vjp_f32, dim3((unsigned)(vjp_f32_waves(ctx) / 4)), dim3(VB), 0,
-                     ctx->stream, a, p->G.as<int2>(), b0, b1, lr->rank.as<int32_t>(),
-                     lr->flag.as<int32_t>(), lr->piv.as<int32_t>(), goff, gpool);
+  const int seqs = (int)vjp_f32_waves(ctx);
+  hipLaunchKernelGGL(k_far_items, dim3(1), dim3(SEQ_MAX), 0, ctx->stream, seqs, p->G.as<int2>(),
+                     t->nodes.as<int4>(), lr->rank.as<int32_t>(), lr->flag.as<int32_t>(), b0, b1,
+                     pre);
+  hipLaunchKernelGGL(k_far_vjp_f32, dim3((unsigned)(seqs / 4)), dim3(VB), 0, ctx->stream, a,
+                     p->G.as<int2>(), b0, b1, lr->rank.as<int32_t>(), lr->flag.as<int32_t>(),
+                     lr->piv.as<int32_t>(), goff, gpool, pre, seqs);
   HIP_OK(hipGetLastError());
 }

@@ -274,10 +274,10 @@ void launch_near_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* 
 // (backward_mfma.hip); slots: vjp_f32_waves(ctx) x MLP_NP doubles each.
 int64_t vjp_f32_waves(hh_ctx ctx);
 void launch_near_vjp_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const float* Fs,
-                         const float* ws, double* dXs, double* slots);
+                         const float* ws, double* dXs, double* slots, int64_t* pre);
 void launch_far_vjp_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k,
                         int64_t b0, int64_t b1, const int64_t* goff, const float* gpool,
-                        double* dXs, double* slots);
+                        double* dXs, double* slots, int64_t* pre);
 void ensure_units(hh_ctx ctx, hh_tree t);
 void launch_aca(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr, double eps,
                 int32_t l_max, int64_t* pool_top_dev);
