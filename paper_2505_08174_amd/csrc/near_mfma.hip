@@ -29,13 +29,6 @@
 
 namespace {
 
-constexpr int NB_T = 256;
-
-__device__ __forceinline__ int wave_maxi(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-  return v;
-}
 
 __global__ __launch_bounds__(T256_UNITS) void k_units_count(const int32_t* __restrict__ leaves,
                                                             int64_t nl,
@@ -56,24 +49,6 @@ __global__ __launch_bounds__(T256_UNITS) void k_units_fill(const int64_t* __rest
   for (int64_t c = 0; c < cnt[l]; ++c) units[pos[l] + c] = make_int2((int)l, (int)c);
 }
 
-// Writes the sum of the workgroup's four waves' rows (fixed order) as partial
-// row `set` of the 64 targets. red: 4 x 64 x 3 doubles of LDS that no wave
-// still reads (the weight table is done with).
-template <class TO>
-__device__ __forceinline__ void write_rows(double* __restrict__ red, int lane, int w, double u0,
-                                           double u1, double u2, int64_t s0, int64_t n, int set,
-                                           TO* __restrict__ out) {
-  __syncthreads();
-  red[192 * w + 3 * lane] = u0;
-  red[192 * w + 3 * lane + 1] = u1;
-  red[192 * w + 3 * lane + 2] = u2;
-  __syncthreads();
-  const int e = threadIdx.x;
-  if (e < 192 && 3 * s0 + e < 3 * n)
-    out[3 * ((int64_t)set * n + s0) + e] =
-        (TO)(((red[e] + red[192 + e]) + red[384 + e]) + red[576 + e]);
-}
-
 struct NearB {
   NearTables t;
   const uint4* frags;
@@ -84,9 +59,9 @@ struct NearB {
 };
 
 template <bool ACC>
-__global__ __launch_bounds__(NB_T) void k_near_bf16(NearB a) {
+__global__ __launch_bounds__(NEAR_WG) void k_near_bf16(NearB a) {
   __shared__ bf16x8 fr[FR_TOTAL];
-  stage_frags(fr, a.frags, NB_T);
+  stage_frags(fr, a.frags, NEAR_WG);
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -100,7 +75,7 @@ __global__ __launch_bounds__(NB_T) void k_near_bf16(NearB a) {
   double u0 = 0, u1 = 0, u2 = 0;
   NearWalk wk;
   wk.start(a.t, ss, 4 * set + w, 4 * a.groups);
-  const int steps = __builtin_amdgcn_readfirstlane(wave_maxi(wk.left));
+  const int steps = __builtin_amdgcn_readfirstlane(wave_max_i(wk.left));
   // source of the step, loaded while the step before is worked on
   double xj0 = a.t.xs[3 * (int64_t)wk.j], xj1 = a.t.xs[3 * (int64_t)wk.j + 1],
          xj2 = a.t.xs[3 * (int64_t)wk.j + 2];
@@ -127,7 +102,8 @@ __global__ __launch_bounds__(NB_T) void k_near_bf16(NearB a) {
     mlp_pairs_bf16<ACC>(fr, in, q);
     pair_apply(q, skip ? 0.0f : in.rs * c16, f0, f1, f2, u0, u1, u2);
   }
-  write_rows(reinterpret_cast<double*>(fr), lane, w, u0, u1, u2, s0, a.t.n, set, a.out);
+  const double u[3] = {u0, u1, u2};
+  write_rows(reinterpret_cast<double*>(fr), lane, w, u, s0, a.t.n, set, a.out);
 }
 
 // The plain FP32 form on FP32 MFMA: the same walk and FP32 tiles. F is FP32;
@@ -144,9 +120,9 @@ struct NearF {
 };
 
 template <class TO>
-__global__ __launch_bounds__(NB_T) void k_near_f32(NearF<TO> a) {
+__global__ __launch_bounds__(NEAR_WG) void k_near_f32(NearF<TO> a) {
   __shared__ __align__(16) float fr[F32_FRAGS * 64];
-  stage_frags_f32(fr, a.frags, NB_T);
+  stage_frags_f32(fr, a.frags, NEAR_WG);
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -160,7 +136,7 @@ __global__ __launch_bounds__(NB_T) void k_near_f32(NearF<TO> a) {
   double u0 = 0, u1 = 0, u2 = 0;
   NearWalk wk;
   wk.start(a.t, ss, 4 * set + w, 4 * a.groups);
-  const int steps = __builtin_amdgcn_readfirstlane(wave_maxi(wk.left));
+  const int steps = __builtin_amdgcn_readfirstlane(wave_max_i(wk.left));
 #pragma unroll 1
   for (int st = 0; st < steps; ++st) {
     const int64_t j = wk.j;
@@ -176,7 +152,8 @@ __global__ __launch_bounds__(NB_T) void k_near_f32(NearF<TO> a) {
     pair_apply(q, skip ? 0.0f : in.rs * c16, f0, f1, f2, u0, u1, u2);
     wk.next(a.t);
   }
-  write_rows(reinterpret_cast<double*>(fr), lane, w, u0, u1, u2, s0, a.t.n, set, a.out);
+  const double u[3] = {u0, u1, u2};
+  write_rows(reinterpret_cast<double*>(fr), lane, w, u, s0, a.t.n, set, a.out);
 }
 
 }  // namespace
@@ -201,19 +178,13 @@ void ensure_units(hh_ctx ctx, hh_tree t) {
   t->n_units = nu;
 }
 
-// Sets of partial rows: workgroups (4 waves, 4 shares of the sources) per 64
-// targets. Three rounds of resident workgroups (3 per compute unit) even out
-// the leaves' different near lists, as long as a share keeps 64 sources (a
-// workgroup stages 48 KB of weights first); below that, shares down to 4
-// sources as long as they fill idle compute units: at 500 particles, 32 sets of
-// 4-source shares take 25 us, one set 160 us.
+// Three rounds of resident workgroups (3 per compute unit) even out the leaves'
+// different near lists, as long as a share keeps 64 sources (a workgroup stages
+// 48 KB of weights first); below that, shares down to 4 sources as long as they
+// fill idle compute units: at 500 particles, 32 sets of 4-source shares take
+// 25 us, one set 160 us.
 int near_groups_mfma(hh_ctx ctx, hh_tree t, hh_part p) {
-  const int64_t nw = (t->n + 63) / 64;
-  const int64_t q = std::max<int64_t>(1, p->near_pairs / t->n);   // sources per target
-  const int64_t res = 3 * (int64_t)ctx->n_cu;                     // resident workgroups
-  const int64_t even = std::min((3 * res + nw - 1) / nw, q / (4 * 64));
-  const int64_t fill = std::min((res + nw - 1) / nw, q / (4 * 4));
-  return (int)std::max<int64_t>(1, std::max(even, fill));
+  return near_sets(ctx, t, p, 3, 64, 4);
 }
 
 void launch_near_bf16(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs, void* out,
@@ -228,9 +199,9 @@ void launch_near_bf16(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void*
   a.input_mode = k->input_mode;
   const unsigned grid = (unsigned)((t->n + 63) / 64 * groups);
   if (split)
-    hipLaunchKernelGGL(k_near_bf16<true>, dim3(grid), dim3(NB_T), 0, ctx->stream, a);
+    hipLaunchKernelGGL(k_near_bf16<true>, dim3(grid), dim3(NEAR_WG), 0, ctx->stream, a);
   else
-    hipLaunchKernelGGL(k_near_bf16<false>, dim3(grid), dim3(NB_T), 0, ctx->stream, a);
+    hipLaunchKernelGGL(k_near_bf16<false>, dim3(grid), dim3(NEAR_WG), 0, ctx->stream, a);
   HIP_OK(hipGetLastError());
 }
 
@@ -246,7 +217,7 @@ static void launch_near_f32_t(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, con
   a.input_mode = k->input_mode;
   a.sgn = sgn;
   const unsigned grid = (unsigned)((t->n + 63) / 64 * groups);
-  hipLaunchKernelGGL(k_near_f32<TO>, dim3(grid), dim3(NB_T), 0, ctx->stream, a);
+  hipLaunchKernelGGL(k_near_f32<TO>, dim3(grid), dim3(NEAR_WG), 0, ctx->stream, a);
   HIP_OK(hipGetLastError());
 }
 
