@@ -10,28 +10,6 @@
 #include "internal.h"
 #include "mlp_mfma.h"
 
-void DevBuf::release() {
-  if (p) {
-    (void)hipFreeAsync(p, s);
-    p = nullptr;
-    bytes = 0;
-  }
-}
-
-void DevBuf::alloc(hipStream_t stream, size_t nbytes) {
-  release();
-  s = stream;
-  if (nbytes == 0) nbytes = 256;
-  hipError_t e = hipMallocAsync(&p, nbytes, stream);
-  if (e != hipSuccess) {
-    p = nullptr;
-    (void)hipGetLastError();
-    throw hh_error{HH_ERR_OUT_OF_MEMORY,
-                   "device allocation of " + std::to_string(nbytes) + " bytes failed"};
-  }
-  bytes = nbytes;
-}
-
 static hipEvent_t take_event(hh_ctx ctx) {
   if (!ctx->event_pool.empty()) {
     hipEvent_t e = ctx->event_pool.back();
@@ -316,22 +294,15 @@ hh_status hh_ctx_create(int device, void* stream, hh_ctx* out) {
     HIP_OK(hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
     HIP_OK(hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming));
     HIP_OK(hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming));
-    // keep freed blocks in the stream-ordered pool for reuse across steps
-    hipMemPool_t pool;
-    if (hipDeviceGetDefaultMemPool(&pool, device) == hipSuccess) {
-      uint64_t thr = UINT64_MAX;
-      (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr);
-    }
-    size_t fr = 0, tot = 0;
-    HIP_OK(hipMemGetInfo(&fr, &tot));
-    ctx->budget_bytes = (size_t)(0.4 * (double)fr);
+    ctx->budget_bytes = (size_t)(0.4 * (double)devmem_attach(device));
+    ctx->attached = true;
     ctx->scratch_flag.alloc(ctx->stream, 64 * sizeof(int64_t));
     HIP_OK(hipHostMalloc((void**)&ctx->pinned, 64 * sizeof(int64_t), hipHostMallocDefault));
   } catch (const hh_error& e) {
-    delete ctx;
+    hh_ctx_destroy(ctx);
     return e.st;
   } catch (const std::bad_alloc&) {
-    delete ctx;
+    hh_ctx_destroy(ctx);
     return HH_ERR_OUT_OF_MEMORY;
   }
   *out = ctx;
@@ -355,6 +326,11 @@ void hh_ctx_destroy(hh_ctx ctx) {
   if (ctx->fork) (void)hipEventDestroy(ctx->fork);
   if (ctx->join) (void)hipEventDestroy(ctx->join);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+  if (ctx->attached) {
+    // blocks freed on a stream used earlier may still be in use there
+    const bool all = ctx->restreamed && hipDeviceSynchronize() == hipSuccess;
+    devmem_detach(ctx->device, ctx->stream, all);
+  }
   delete ctx;
 }
 
@@ -362,6 +338,7 @@ const char* hh_last_error(hh_ctx ctx) { return ctx ? ctx->last_error.c_str() : "
 
 hh_status hh_ctx_set_stream(hh_ctx ctx, void* stream) {
   if (!ctx) return HH_ERR_INVALID_ARG;
+  ctx->restreamed |= ctx->stream != (hipStream_t)stream;
   ctx->stream = (hipStream_t)stream;
   return HH_OK;
 }

@@ -1,0 +1,147 @@
+// Device memory of the library: blocks of size classes, kept when freed.
+//
+// Every call builds and drops some hundreds of buffers (190 allocations and
+// frees per time step), and the sizes of the large ones (the ACA's factor pool,
+// tens of GiB, its arenas, the block lists) change a little from step to step
+// as the particles move. From hipMallocAsync each of them costs 5 + 14 us of
+// host time, and a pool that is a little larger than the freed one is mapped
+// anew: steps of 90 ms of kernels took 0.8 s, and of 0.4 s took 1.7 s. Freed
+// blocks therefore stay here, one list per size class (eight classes per
+// power of two, so a block is at most an eighth larger than asked for).
+//
+// A block is reused only on the stream it was freed on (stream order then
+// keeps its earlier readers ahead of its next writers), or on any stream once
+// that stream has been waited for. The lists of a device hold at most
+// KEEP_SHARE of its memory (the largest blocks go first), and everything is
+// returned when the last context on the device is destroyed or when an
+// allocation fails. One lock per process: contexts may live in any thread.
+#include <algorithm>
+#include <map>
+#include <mutex>
+#include <vector>
+
+#include "internal.h"
+
+namespace {
+
+constexpr int MAX_DEVICES = 64;
+constexpr double KEEP_SHARE = 0.4;
+
+struct Block {
+  void* p;
+  hipStream_t stream;
+  bool idle;   // nothing queued uses it any more: any stream may take it
+};
+
+struct DeviceBlocks {
+  std::map<size_t, std::vector<Block>> free;
+  size_t kept = 0, limit = 0;
+  int contexts = 0;
+};
+
+std::mutex g_mu;
+// never destroyed: handles may be freed while the process ends
+DeviceBlocks* device_blocks(int dev) {
+  static DeviceBlocks* all = new DeviceBlocks[MAX_DEVICES];
+  return dev >= 0 && dev < MAX_DEVICES ? all + dev : nullptr;
+}
+
+size_t size_class(size_t n) {
+  if (n <= 512) return 512;
+  const size_t step = (size_t)1 << (60 - __builtin_clzll(n - 1));   // an eighth of the power of two below
+  return (n + step - 1) / step * step;
+}
+
+// Returns every kept block to the runtime. The device is idle afterwards.
+void give_back(DeviceBlocks* d) {
+  (void)hipDeviceSynchronize();
+  for (auto& c : d->free)
+    for (Block& b : c.second) (void)hipFreeAsync(b.p, nullptr);
+  d->free.clear();
+  d->kept = 0;
+  (void)hipStreamSynchronize(nullptr);
+  (void)hipGetLastError();
+}
+
+}  // namespace
+
+void DevBuf::release() {
+  if (!p) return;
+  std::lock_guard<std::mutex> lock(g_mu);
+  DeviceBlocks* d = device_blocks(dev);
+  if (!d || d->contexts == 0) {
+    (void)hipFreeAsync(p, s);
+  } else {
+    d->free[bytes].push_back(Block{p, s, false});
+    d->kept += bytes;
+    if (d->kept > d->limit) {
+      (void)hipDeviceSynchronize();
+      while (d->kept > d->limit && !d->free.empty()) {
+        auto it = std::prev(d->free.end());
+        (void)hipFreeAsync(it->second.back().p, nullptr);
+        d->kept -= it->first;
+        it->second.pop_back();
+        if (it->second.empty()) d->free.erase(it);
+      }
+    }
+  }
+  p = nullptr;
+  bytes = 0;
+}
+
+void DevBuf::alloc(hipStream_t stream, size_t nbytes) {
+  release();
+  s = stream;
+  const size_t c = size_class(nbytes);
+  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+  std::lock_guard<std::mutex> lock(g_mu);
+  DeviceBlocks* d = device_blocks(dev);
+  if (d) {
+    // the class itself, or the next ones up to a quarter more memory
+    for (auto it = d->free.lower_bound(c); it != d->free.end() && it->first <= c + c / 4; ++it) {
+      std::vector<Block>& v = it->second;
+      for (size_t i = v.size(); i-- > 0;) {
+        if (!v[i].idle && v[i].stream != stream) continue;
+        p = v[i].p;
+        bytes = it->first;
+        v.erase(v.begin() + i);
+        d->kept -= bytes;
+        if (v.empty()) d->free.erase(it);
+        return;
+      }
+    }
+  }
+  hipError_t e = hipMallocAsync(&p, c, stream);
+  if (e != hipSuccess && d && d->kept > 0) {
+    (void)hipGetLastError();
+    give_back(d);
+    e = hipMallocAsync(&p, c, stream);
+  }
+  if (e != hipSuccess) {
+    p = nullptr;
+    (void)hipGetLastError();
+    throw hh_error{HH_ERR_OUT_OF_MEMORY,
+                   "device allocation of " + std::to_string(nbytes) + " bytes failed"};
+  }
+  bytes = c;
+}
+
+size_t devmem_attach(int dev) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  DeviceBlocks* d = device_blocks(dev);
+  size_t fr = 0, tot = 0;
+  HIP_OK(hipMemGetInfo(&fr, &tot));
+  if (!d) return fr;
+  d->limit = (size_t)(KEEP_SHARE * (double)tot);
+  d->contexts += 1;
+  return fr + d->kept;
+}
+
+void devmem_detach(int dev, hipStream_t stream, bool whole_device) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  DeviceBlocks* d = device_blocks(dev);
+  if (!d) return;
+  for (auto& c : d->free)
+    for (Block& b : c.second) b.idle |= whole_device || b.stream == stream;
+  if (--d->contexts == 0) give_back(d);
+}

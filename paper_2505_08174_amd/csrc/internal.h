@@ -32,12 +32,13 @@ struct hh_error {
 
 // ------------------------------------------------------------- device memory
 
-// A stream-ordered device buffer (hipMallocAsync / hipFreeAsync on the
-// context stream). Freed on the stream in the destructor.
+// A stream-ordered device buffer: allocated for use on `stream`, returned to
+// the kept blocks of its device on that stream (devmem.hip). Not cleared.
 struct DevBuf {
   void* p = nullptr;
-  size_t bytes = 0;
+  size_t bytes = 0;   // of the block, at least what was asked for
   hipStream_t s = nullptr;
+  int dev = -1;
   DevBuf() = default;
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
@@ -52,6 +53,12 @@ struct DevBuf {
   template <class T> T* as() const { return reinterpret_cast<T*>(p); }
 };
 
+// A context on device `dev` exists (returns its free memory, the kept blocks
+// counted as free) or is gone, after a wait for `stream`, or with whole_device
+// for every stream of the device.
+size_t devmem_attach(int dev);
+void devmem_detach(int dev, hipStream_t stream, bool whole_device);
+
 struct PhaseRec {
   int phase;
   hipEvent_t a, b;
@@ -65,6 +72,7 @@ struct hh_ctx_s {
   // runs beside the single-wave kernel, forked from and joined to `stream`
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
+  bool attached = false, restreamed = false;   // counted in devmem; the stream was replaced
   std::string last_error;
   DevBuf scratch_flag;   // small device scratch for readbacks (64 x int64)
   int64_t* pinned = nullptr;  // host pinned mirror for readbacks (64 x int64)

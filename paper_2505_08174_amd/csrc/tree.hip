@@ -471,6 +471,7 @@ void take(DevBuf& dst, DevBuf& src) {
   dst.release();
   dst.p = src.p;
   dst.bytes = src.bytes;
+  dst.dev = src.dev;
   dst.s = src.s;
   src.p = nullptr;
   src.bytes = 0;
