@@ -96,9 +96,8 @@ struct AcaArgs {
   const uint4* frags;   // BF16 MFMA weight fragments (BF16 sampling)
   const float4* frags32;   // FP32 MFMA weight fragments (FP32 sampling)
   int det_pivot;        // pivot magnitude |det| (else squared Frobenius norm)
-  double* gram;         // Gram history A (gram_half doubles) and cross-wave
-  int64_t gram_stride;  // partials, gram_stride doubles per worker
-  int64_t gram_half;
+  double* gram;         // Gram history A, gram_stride doubles per worker
+  int64_t gram_stride;
 };
 
 template <class NT, class T>
@@ -112,25 +111,17 @@ __device__ __forceinline__ NT det3(const T* K) {
 // MFK = 2 FP32 tiles; fr is the matching fragment table in LDS.
 enum { MF_NONE = 0, MF_BF16 = 1, MF_F32 = 2 };
 
-// K(x_i - y_j) of this lane's pair from MFMA MLP tiles. PAIRS: 64 different
-// pairs, one per lane (two tiles); otherwise one tile of 32 pairs, lanes l and
-// l + 32 holding the same one.
-template <bool PAIRS, int MFK>
+// K(x_i - y_j) of this lane's pair from one MFMA MLP tile of 32 pairs, lanes l
+// and l + 32 holding the same one.
+template <int MFK>
 __device__ __forceinline__ void mfma_entry(const void* fr, int mode, double dx, double dy,
                                            double dz, float K[9]) {
-  const PairIn in = pair_in(mode, (float)dx, (float)dy, (float)dz, !PAIRS);
+  const PairIn in = pair_in(mode, (float)dx, (float)dy, (float)dz, true);
   float o[9];
-  if constexpr (MFK == MF_F32) {
-    if constexpr (PAIRS)
-      mlp_pairs_f32((const float*)fr, in.v0, in.v1, in.v2, o);
-    else
-      mlp_tile_f32((const float*)fr, in.v0, in.v1, in.v2, o);
-  } else {
-    if constexpr (PAIRS)
-      mlp_pairs_bf16<true>((const bf16x8*)fr, in, o);
-    else
-      mlp_tile_bf16<true>((const bf16x8*)fr, in, o);
-  }
+  if constexpr (MFK == MF_F32)
+    mlp_tile_f32((const float*)fr, in.v0, in.v1, in.v2, o);
+  else
+    mlp_tile_bf16<true>((const bf16x8*)fr, in, o);
   pair_entry(o, in.rs, K);
 }
 
@@ -143,51 +134,95 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// v + (v of the source lane given by a DPP control), 0 where the source lane
-// is outside the row or the row is masked off
+// v of the source lane given by a DPP control; `old` where the source lane is
+// outside the row or the row is masked off.
 template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_add(double v) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  int slo, shi;
-  if (ROW_MASK == 0xf) {   // every row written; invalid source lanes read 0
-    slo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, true);
-    shi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, true);
-  } else {                 // rows masked off keep the 0 they start from
-    slo = __builtin_amdgcn_update_dpp(0, lo, CTRL, ROW_MASK, 0xf, false);
-    shi = __builtin_amdgcn_update_dpp(0, hi, CTRL, ROW_MASK, 0xf, false);
-  }
-  return v + __hiloint2double(shi, slo);
+__device__ __forceinline__ int dpp(int v, int old) {
+  return __builtin_amdgcn_update_dpp(old, v, CTRL, ROW_MASK, 0xf, false);
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp(double v, double old) {
+  return __hiloint2double(dpp<CTRL, ROW_MASK>(__double2hiint(v), __double2hiint(old)),
+                          dpp<CTRL, ROW_MASK>(__double2loint(v), __double2loint(old)));
+}
+__device__ __forceinline__ double read_lane(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
-// Sum over the wave of each p[e], returned in every lane: scans by row shifts 1, 2,
-// 4, 8 inside each 16-lane row (lane 15 of a row then holds the row sum), row
-// 0 into row 1 and row 2 into row 3 (lane 15 broadcast), rows 0-1 into rows
-// 2-3 (lane 31 broadcast), so lane 63 holds the total. No LDS traffic.
+// (a of lanes 0-31 + a of lanes 32-63) in lanes 0-31, the same of b in lanes
+// 32-63; and per pair of 16-lane rows: a's rows 0 + 1 (2 + 3) in row 0 (2), b's
+// in row 1 (3). One swap of the two operands and one addition do what two
+// shuffles, two selects and two additions would.
+__device__ __forceinline__ double fold32(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+__device__ __forceinline__ double fold16(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+
+// Sums over the wave of N values, four to a register: value e ends in register
+// e / 4, in lane 16 row + 15 with row = sum_row(e) (lane 15 of each 16-lane row
+// holds the row's sum after the scans by row shifts 1, 2, 4, 8). No LDS
+// traffic; 60 instructions for nine values, against 190 for nine separate
+// scans over 64 lanes.
+__host__ __device__ constexpr int sum_row(int e) { return ((e & 1) << 1) | ((e >> 1) & 1); }
+template <int N>
+struct WaveSums {
+  double r[(N + 3) / 4];
+};
+template <int N>
+__device__ __forceinline__ WaveSums<N> wave_sums(const double (&p)[N]) {
+  WaveSums<N> w;
+#pragma unroll
+  for (int g = 0; g < (N + 3) / 4; ++g) {
+    const double a = fold32(p[4 * g], 4 * g + 1 < N ? p[4 * g + 1] : 0.0);
+    double v = 4 * g + 2 < N ? fold32(p[4 * g + 2], 4 * g + 3 < N ? p[4 * g + 3] : 0.0) : 0.0;
+    v = fold16(a, v);
+    v += dpp<0x111, 0xf>(v, 0.0);   // row_shr:1
+    v += dpp<0x112, 0xf>(v, 0.0);   // row_shr:2
+    v += dpp<0x114, 0xf>(v, 0.0);   // row_shr:4
+    v += dpp<0x118, 0xf>(v, 0.0);   // row_shr:8
+    w.r[g] = v;
+  }
+  return w;
+}
+// ... returned in every lane.
 template <int N>
 __device__ __forceinline__ void wave_sumv(double (&p)[N]) {
+  const WaveSums<N> w = wave_sums(p);
 #pragma unroll
-  for (int e = 0; e < N; ++e) {
-    double v = p[e];
-    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
-    v = dpp_add<0x112, 0xf>(v);   // row_shr:2
-    v = dpp_add<0x114, 0xf>(v);   // row_shr:4
-    v = dpp_add<0x118, 0xf>(v);   // row_shr:8
-    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1, 3
-    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2, 3
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-    p[e] = __hiloint2double(hi, lo);
-  }
+  for (int e = 0; e < N; ++e) p[e] = read_lane(w.r[e / 4], 16 * sum_row(e) + 15);
 }
 
-template <class T>
-__device__ __forceinline__ T wave_max(T v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    T w = __shfl_xor(v, o, 64);
-    v = w > v ? w : v;
-  }
-  return v;
+// Largest value over the wave, in every lane.
+__device__ __forceinline__ double wave_max(double v) {
+  v = fmax(v, dpp<0x111, 0xf>(v, v));
+  v = fmax(v, dpp<0x112, 0xf>(v, v));
+  v = fmax(v, dpp<0x114, 0xf>(v, v));
+  v = fmax(v, dpp<0x118, 0xf>(v, v));
+  v = fmax(v, dpp<0x142, 0xa>(v, v));   // row_bcast:15 into rows 1, 3
+  v = fmax(v, dpp<0x143, 0xc>(v, v));   // row_bcast:31 into rows 2, 3
+  return read_lane(v, 63);
+}
+__device__ __forceinline__ int wave_min(int v) {
+  v = min(v, dpp<0x111, 0xf>(v, v));
+  v = min(v, dpp<0x112, 0xf>(v, v));
+  v = min(v, dpp<0x114, 0xf>(v, v));
+  v = min(v, dpp<0x118, 0xf>(v, v));
+  v = min(v, dpp<0x142, 0xa>(v, v));
+  v = min(v, dpp<0x143, 0xc>(v, v));
+  return __builtin_amdgcn_readlane(v, 63);
+}
+// The largest v and the lowest i that comes with it, in every lane.
+__device__ __forceinline__ void wave_best(double& v, int& i) {
+  const double m = wave_max(v);
+  i = wave_min(v == m ? i : 0x7fffffff);
+  v = m;
 }
 
 // K -= A B (3x3, row-major)
@@ -224,27 +259,71 @@ __device__ __forceinline__ void load_hist(const double* __restrict__ h, int m1, 
   }
 }
 
-// Entries 9 i .. 9 i + 8 of f for the rows i = i0 + 64 r (r < RCH), zero past n.
+// Rows of a factor (9 values each) through a buffer resource that ends with the
+// factor: three 16-byte loads (FP32; five in FP64) at fixed offsets from a lane's
+// first row, and rows past the end read as zeros without a test.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 template <class T>
-__device__ __forceinline__ void load_rows(const T* __restrict__ f, int i0, int n, T (&v)[RCH][9]) {
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const T* f, int n) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)f, 0, 9 * (int)sizeof(T) * n, 0x00027000);
+}
+__device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t rs, int i, float (&v)[9]) {
+  const int o = 36 * i;
+  const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0);
+  const u32x4 b = __builtin_amdgcn_raw_buffer_load_b128(rs, o + 16, 0, 0);
+  const uint32_t c = __builtin_amdgcn_raw_buffer_load_b32(rs, o + 32, 0, 0);
 #pragma unroll
-  for (int r = 0; r < RCH; ++r) {
-    const int i = i0 + 64 * r;
-#pragma unroll
-    for (int e = 0; e < 9; ++e) v[r][e] = i < n ? f[9 * (int64_t)i + e] : T(0);
+  for (int e = 0; e < 4; ++e) {
+    v[e] = __uint_as_float(a[e]);
+    v[4 + e] = __uint_as_float(b[e]);
   }
+  v[8] = __uint_as_float(c);
+}
+__device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t rs, int i, double (&v)[9]) {
+  const int o = 72 * i;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(rs, o + 16 * t, 0, 0);
+    v[2 * t] = __hiloint2double((int)a[1], (int)a[0]);
+    v[2 * t + 1] = __hiloint2double((int)a[3], (int)a[2]);
+  }
+  const u32x2 b = __builtin_amdgcn_raw_buffer_load_b64(rs, o + 64, 0, 0);
+  v[8] = __hiloint2double((int)b[1], (int)b[0]);
+}
+// The rows base + lane and base + 64 + lane (zero from end on) of the factor at
+// element off of fb (both uniform over the wave).
+template <class T>
+__device__ __forceinline__ void load_rows(const T* fb, int64_t off, int base, int end,
+                                          T (&v)[RCH][9]) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)off);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(off >> 32));
+  const int64_t o = (int64_t)(((uint64_t)hi << 32) | lo);
+  const __amdgpu_buffer_rsrc_t rs = rows_rsrc(fb + o + 9 * (int64_t)base, end - base);
+#pragma unroll
+  for (int r = 0; r < RCH; ++r) load_row(rs, lane + 64 * r, v[r]);
 }
 
 // Scratch of one worker team (TW waves) for the block it approximates.
+constexpr int AS = 10;   // stride of 3x3 FP64 entries in LDS (16-byte reads)
 template <class T>
-struct TeamSh {
-  T qc[LMAX_CAP * 9];     // q_m(j_k) in the column pass, c_m(i_k) in the row pass
-  int64_t off[LMAX_CAP];  // pool offset of factor m
+struct __align__(16) TeamSh {
+  // stride of the entries of T: 16-byte reads in FP32; in FP64 eight of these
+  // beside the MLP weights leave no room for padding
+  static constexpr int QS = sizeof(T) == 4 ? 12 : 9;
+  T qc[LMAX_CAP * QS];      // q_m(j_k) in the column pass, c_m(i_k) in the row pass
+  double am[LMAX_CAP * AS]; // A_mk = sum_i c_m(i)^T c_k(i), m < k (row pass)
+  int64_t off[LMAX_CAP];    // pool offset of factor m
   int pi[LMAX_CAP];
   int pj[LMAX_CAP + 1];
-  double am[LMAX_CAP * 9];  // A_mk = sum_i c_m(i)^T c_k(i), m < k (row pass)
-  int64_t bo;             // broadcast: claimed block, pool offset
-  int ovf;                // broadcast: pool overflow
+  T piv[9];                 // the pivot entry
+  int64_t bo;               // broadcast: claimed block, pool offset
+  int ovf;                  // broadcast: pool overflow
+};
+// Ghat_m of one wave's rows (a single wave keeps it in am, where A_mk follows).
+struct __align__(16) WaveG {
+  double g[LMAX_CAP * AS];
 };
 
 // Cross-wave partial results of a team of AW waves (one per workgroup).
@@ -261,47 +340,66 @@ __device__ __forceinline__ void team_sync() {
     __syncthreads();
 }
 
-// Raw samples K(sgn (p_i - y)) of `pts`, written to slot[9 i ..]: rows
-// t0 + lane % 32 (one tile), or with PAIRS rows t0 + lane and, for lanes 32-63,
-// t1 + lane - 32 (two tiles, one row per lane).
-template <bool PAIRS, int MFK>
+// Which remainder of its input a row's sample takes (pair_rest): 32-row tiles,
+// dealt to the TW waves of the team and taken in pairs; a tile left without a
+// partner takes the exact one.
+template <int TW>
+__device__ __forceinline__ bool lone_tile(int i, int n) {
+  const int t = i >> 5;
+  return !((t / TW) & 1) && t + TW >= ((n + 31) >> 5);
+}
+
+// Raw samples K(sgn (p_i - y)) of the rows i = base + lane and base + 64 + lane
+// (< end) of `pts` into rs, zero past end: two MFMA tiles of 32 rows per call,
+// one row per lane, or one tile where at most 32 rows are left. They stay in
+// the lane that subtracts the earlier terms from them: written to the factor
+// slot and read back they cost 72 bytes per row and an eighth of the ACA.
+template <int TW, int MFK>
 __device__ __forceinline__ void sample_rows(const void* fr, int mode, const double* pts, int n,
-                                            double y0, double y1, double y2, double sgn,
-                                            float* slot, int t0, int t1) {
+                                            int base, int end, double y0, double y1, double y2,
+                                            double sgn, float (&rs)[RCH][9]) {
   const int lane = threadIdx.x & 63;
-  const int i = (PAIRS && lane >= 32 ? t1 : t0) + (lane & 31);
-  const int ii = i < n ? i : t0;
-  float K[9];
-  mfma_entry<PAIRS, MFK>(fr, mode, sgn * (pts[3 * ii] - y0), sgn * (pts[3 * ii + 1] - y1),
-                         sgn * (pts[3 * ii + 2] - y2), K);
-  if (i < n && (PAIRS || lane < 32)) {
-    float* d = slot + 9 * (int64_t)i;
 #pragma unroll
-    for (int e = 0; e < 9; ++e) d[e] = K[e];
+  for (int r = 0; r < RCH; ++r)
+#pragma unroll
+    for (int e = 0; e < 9; ++e) rs[r][e] = 0.0f;
+#pragma unroll 1
+  for (int r = 0; r < RCH; ++r) {
+    const int t0 = base + 64 * r, rows = end - t0;   // uniform
+    if (rows <= 0) break;
+    const bool one = rows <= 32;
+    const int i = t0 + (one ? lane & 31 : lane);
+    const int ii = i < end ? i : t0;
+    const PairIn in = pair_in(mode, (float)(sgn * (pts[3 * ii] - y0)),
+                              (float)(sgn * (pts[3 * ii + 1] - y1)),
+                              (float)(sgn * (pts[3 * ii + 2] - y2)), lone_tile<TW>(ii, n));
+    float o[9], K[9];
+    if constexpr (MFK == MF_F32) {
+      if (one)
+        mlp_tile_f32((const float*)fr, in.v0, in.v1, in.v2, o);
+      else
+        mlp_pairs_f32((const float*)fr, in.v0, in.v1, in.v2, o);
+    } else {
+      if (one)
+        mlp_tile_bf16<true>((const bf16x8*)fr, in, o);
+      else
+        mlp_pairs_bf16<true>((const bf16x8*)fr, in, o);
+    }
+    pair_entry(o, in.rs, K);
+    const bool keep = t0 + lane < end;
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+      rs[0][e] = r == 0 && keep ? K[e] : rs[0][e];
+      rs[1][e] = r == 1 && keep ? K[e] : rs[1][e];
+    }
   }
 }
 
-// The samples of all rows [0, n): 32-row tiles spread over the TW waves of the
-// team, a wave's tiles in pairs.
-template <int TW, int MFK>
-__device__ __forceinline__ void sample_mfma(const void* fr, int mode, const double* pts, int n,
-                                            double y0, double y1, double y2, double sgn,
-                                            float* slot, int wit) {
-  const int step = 32 * TW;
-  int t0 = 32 * wit;
-#pragma unroll 1
-  for (; t0 + step < n; t0 += 2 * step)
-    sample_rows<true, MFK>(fr, mode, pts, n, y0, y1, y2, sgn, slot, t0, t0 + step);
-  if (t0 < n) sample_rows<false, MFK>(fr, mode, pts, n, y0, y1, y2, sgn, slot, t0, t0);
-}
-
 // Combines the per-wave results of a pass over the team: sums v[0..NV) in
-// wave order, max of the two magnitudes, argmax (ties to the lowest index),
-// and sums the per-m partials (lane m of every wave) through global scratch.
+// wave order, max of the two magnitudes, argmax (ties to the lowest index).
 template <int TW, int NV>
-__device__ __forceinline__ void team_combine(TeamRed* tr, double* gx, int wit, int k,
-                                             double (&v)[NV], double& mx1, double& mx2,
-                                             double& best, int& bi, double (&G)[9]) {
+__device__ __forceinline__ void team_combine(TeamRed* tr, int wit, double (&v)[NV], double& mx1,
+                                             double& mx2, double& best, int& bi) {
   if constexpr (TW > 1) {
     const int lane = threadIdx.x & 63;
     if (lane == 0) {
@@ -311,11 +409,6 @@ __device__ __forceinline__ void team_combine(TeamRed* tr, double* gx, int wit, i
       tr->v[wit][NV + 1] = mx2;
       tr->v[wit][NV + 2] = best;
       tr->i[wit] = bi;
-    }
-    if (lane < k) {
-      double* d = gx + 9 * (64 * wit + lane);
-#pragma unroll
-      for (int e = 0; e < 9; ++e) d[e] = G[e];
     }
     __syncthreads();
 #pragma unroll
@@ -335,15 +428,6 @@ __device__ __forceinline__ void team_combine(TeamRed* tr, double* gx, int wit, i
       const int iw = tr->i[w];
       if (bw > best || (bw == best && iw < bi)) { best = bw; bi = iw; }
     }
-    if (lane < k) {
-#pragma unroll
-      for (int e = 0; e < 9; ++e) G[e] = 0;
-      for (int w = 0; w < TW; ++w) {
-        const double* s = gx + 9 * (64 * w + lane);
-#pragma unroll
-        for (int e = 0; e < 9; ++e) G[e] += s[e];
-      }
-    }
     __syncthreads();
   }
 }
@@ -362,14 +446,23 @@ __device__ __forceinline__ void team_combine(TeamRed* tr, double* gx, int wit, i
 //     sum_{m<k} tr(A_mk B_km) = sum_j <V(j), q_k(j)>_F (B_km = sum_j q_k(j) q_m(j)^T)
 //     take one scalar reduction; B_kk = sum_j q_k(j) q_k(j)^T;
 //   nu^2 = tr(A_kk B_kk), lambda^2 += nu^2 + 2 sum_{m<k} tr(A_mk B_km).
-// So the Gram terms cost no extra pass over the factors. Every wave of a team
+// So the Gram terms cost no extra pass over the factors. Raw samples never leave
+// the lane that subtracts from them, and a column of at most 128 rows stays in
+// registers up to its normalisation. Bound by VALU issue (78% busy at 250,000
+// particles in the BF16 form) and by the re-reading of the factors (3.2 TB/s
+// there, 5.4 TB/s in the 6N form, more than a large copy's rate). With the sums
+// over the wave two swaps per value instead of six shuffles' worth of DPP moves,
+// samples kept in registers, factor rows read through buffer resources and used
+// pivots in a bit mask, the ACA went from 415 to 374 ms at 250,000 particles
+// (BF16), from 61 to 52 ms in the 6N form (40,000), from 1.55 to 1.17 ms at 2,000
+// particles in FP64. Every wave of a team
 // computes the per-step scalars itself from the same combined values, so all
 // decisions are uniform over the team. Fused apply: u(i) += c_{k-1}(i) t_{k-1}
 // rides on the next column pass (or a final pass).
 template <class T, int KIND, int MF, int TW>
 __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, const void* fr,
-                                           TeamSh<T>& sh, TeamRed* tr, int wit, int64_t slot,
-                                           int* counter, int64_t r0, int64_t r1, T* fbase,
+                                           TeamSh<T>& sh, WaveG* wg, TeamRed* tr, int wit,
+                                           int64_t slot, int* counter, int64_t r0, int64_t r1, T* fbase,
                                            int64_t fcap) {
   using NT = double;
   const int lane = threadIdx.x & 63;
@@ -377,7 +470,8 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
   const int stride = 64 * TW;   // threads of the team
   const int tid = 64 * wit + lane;
   double* hA = a.gram + slot * a.gram_stride;
-  double* gx = hA + a.gram_half;   // cross-wave partials, [AW][64][9]
+  double* gw = TW > 1 ? wg[wit].g : sh.am;   // this wave's Ghat_m
+  constexpr int QS = TeamSh<T>::QS;
 #pragma unroll 1
   for (;;) {
     if (lead) sh.bo = atomicAdd(counter, 1);
@@ -392,6 +486,15 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
     const double* xt = a.xs + 3 * (int64_t)nt.x;
     const double* xsr = a.xs + 3 * (int64_t)ns.x;
     const int kmax = min(min(c, q), a.l_max);
+    // rows of a wave's chunk: 128, or 64 where that leaves no wave of a team idle
+    const int chc = TW > 1 && c <= 64 * TW ? 64 : CH, chq = TW > 1 && q <= 64 * TW ? 64 : CH;
+    // one chunk holds the whole column: it stays in registers up to its
+    // normalisation
+    const bool whole = TW == 1 && c <= CH;
+    // used pivot rows and columns of this lane, one bit per 64 rows (larger
+    // blocks and teams look them up)
+    const bool bits = TW == 1 && max(c, q) <= 64 * 64;
+    uint64_t usedi = 0, usedj = 0;
     // factor storage: the worker's own arena (fcap elements; offsets restart
     // with every block), or the shared pool, bump-allocated (fbase == null)
     const bool own = fbase != nullptr;
@@ -434,35 +537,35 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
 #pragma unroll 1
       for (int t = tid; t < 9 * k; t += stride) {
         const int m = t / 9, e = t - 9 * m;
-        sh.qc[t] = fb[sh.off[m] + 9 * (int64_t)c + 9 * (int64_t)j + e];
+        sh.qc[QS * m + e] = fb[sh.off[m] + 9 * (int64_t)c + 9 * (int64_t)j + e];
       }
       T* Ck = fb + offv;
       T* Qk = Ck + 9 * (int64_t)c;
       const double yj0 = xsr[3 * j], yj1 = xsr[3 * j + 1], yj2 = xsr[3 * j + 2];
-      if (MF) sample_mfma<TW, MF>(fr, a.kp.input_mode, xt, c, yj0, yj1, yj2, 1.0, (float*)Ck, wit);
+      if (lane == (j & 63)) usedj |= 1ull << ((j >> 6) & 63);
       team_sync<TW>();
       // ---- column pass: residual, Ghat, pivot search, sum a^T a
       NT best = -1, bestf = -1, graw = 0;
       int bi = 0x7fffffff;
-      double G[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
       double S[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+      T rs[RCH][9];
 #pragma unroll 1
-      for (int base = CH * wit; base < c; base += CH * TW) {
-        T rs[RCH][9];
+      for (int base = chc * wit; base < c; base += chc * TW) {
+        const int end = min(base + chc, c);
+        if constexpr (MF)
+          sample_rows<TW, MF>(fr, a.kp.input_mode, xt, c, base, end, yj0, yj1, yj2, 1.0,
+                              (float(&)[RCH][9])rs);
 #pragma unroll
         for (int r = 0; r < RCH; ++r) {
           const int i = base + 64 * r + lane;
-          if (i < c) {
-            if (MF) {
-#pragma unroll
-              for (int e = 0; e < 9; ++e) rs[r][e] = Ck[9 * (int64_t)i + e];
-            } else {
+          if constexpr (!MF) {
+            if (i < end) {
               kernel_entry<T>(a.kp, wl, (T)(xt[3 * i] - yj0), (T)(xt[3 * i + 1] - yj1),
                               (T)(xt[3 * i + 2] - yj2), rs[r], i & 1, j & 1);
-            }
-          } else {
+            } else {
 #pragma unroll
-            for (int e = 0; e < 9; ++e) rs[r][e] = 0;
+              for (int e = 0; e < 9; ++e) rs[r][e] = 0;
+            }
           }
           if (sizeof(T) == 4) {
             NT g2s = 0;
@@ -473,7 +576,7 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
         }
         // c_m(i) of the next m is loaded while m is worked on
         T cn[RCH][9];
-        if (k > 0) load_rows<T>(fb + sh.off[0], base + lane, c, cn);
+        if (k > 0) load_rows<T>(fb, sh.off[0], base, end, cn);
 #pragma unroll 1
         for (int m = 0; m < k; ++m) {
           T cc[RCH][9];
@@ -481,10 +584,10 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
           for (int r = 0; r < RCH; ++r)
 #pragma unroll
             for (int e = 0; e < 9; ++e) cc[r][e] = cn[r][e];
-          if (m + 1 < k) load_rows<T>(fb + sh.off[m + 1], base + lane, c, cn);
+          if (m + 1 < k) load_rows<T>(fb, sh.off[m + 1], base, end, cn);
           T qv[9];
 #pragma unroll
-          for (int e = 0; e < 9; ++e) qv[e] = sh.qc[9 * m + e];
+          for (int e = 0; e < 9; ++e) qv[e] = sh.qc[QS * m + e];
           // this lane's rows of c_m(i)^T r_m(i): products of the working type
           // (FP32 in the single-precision forms), summed over the wave in FP64
           T pl[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -498,7 +601,7 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
               for (int y = 0; y < 3; ++y)
                 pl[3 * x + y] += cv[x] * rs[r][y] + cv[3 + x] * rs[r][3 + y] + cv[6 + x] * rs[r][6 + y];
             sub_mm<T>(rs[r], cv, qv);
-            if (fuse && m == k - 1 && i < c) {
+            if (fuse && m == k - 1 && i < end) {
               ub[3 * i] += (double)cv[0] * tp0 + (double)cv[1] * tp1 + (double)cv[2] * tp2;
               ub[3 * i + 1] += (double)cv[3] * tp0 + (double)cv[4] * tp1 + (double)cv[5] * tp2;
               ub[3 * i + 2] += (double)cv[6] * tp0 + (double)cv[7] * tp1 + (double)cv[8] * tp2;
@@ -507,21 +610,27 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
           double p[9];
 #pragma unroll
           for (int e = 0; e < 9; ++e) p[e] = (double)pl[e];
-          wave_sumv(p);
-          if (lane == m) {
-#pragma unroll
-            for (int e = 0; e < 9; ++e) G[e] += p[e];
+          const WaveSums<9> g = wave_sums(p);
+          // lane 15 of a 16-lane row holds the sums of that row's values
+          if ((lane & 15) == 15) {
+            const int row = lane >> 4, e0 = ((row & 1) << 1) | (row >> 1);   // sum_row inverted
+            double* d = gw + AS * m;
+            const bool first = base == chc * wit;
+            d[e0] = first ? g.r[0] : d[e0] + g.r[0];
+            d[4 + e0] = first ? g.r[1] : d[4 + e0] + g.r[1];
+            if (row == 0) d[8] = first ? g.r[2] : d[8] + g.r[2];
           }
         }
 #pragma unroll
         for (int r = 0; r < RCH; ++r) {
           const int i = base + 64 * r + lane;
-          if (i >= c) continue;
+          if (i >= end) continue;
           NT nrm = 0;
 #pragma unroll
-          for (int e = 0; e < 9; ++e) {
-            Ck[9 * (int64_t)i + e] = rs[r][e];
-            nrm += (NT)rs[r][e] * (NT)rs[r][e];
+          for (int e = 0; e < 9; ++e) nrm += (NT)rs[r][e] * (NT)rs[r][e];
+          if (!whole) {
+#pragma unroll
+            for (int e = 0; e < 9; ++e) Ck[9 * (int64_t)i + e] = rs[r][e];
           }
 #pragma unroll
           for (int x = 0; x < 3; ++x)
@@ -532,8 +641,12 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
                               (double)rs[r][6 + x] * (double)rs[r][6 + y];
           NT sel = a.det_pivot ? det3<NT>(rs[r]) : nrm;
           bool used = false;
+          if (bits) {
+            used = (usedi >> (i >> 6)) & 1;
+          } else {
 #pragma unroll 1
-          for (int m = 0; m < k; ++m) used |= (sh.pi[m] == i);
+            for (int m = 0; m < k; ++m) used |= (sh.pi[m] == i);
+          }
           if (used) { nrm = -1; sel = -1; }
           if (sel > best || (sel == best && i < bi)) { best = sel; bi = i; }
           bestf = nrm > bestf ? nrm : bestf;
@@ -542,9 +655,16 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
       pending = false;   // the term k-1 is applied
       wave_sumv(S);
       if (sizeof(T) == 4) graw = wave_max(graw);
-      wave_argmax(best, bi);
-      bestf = wave_max(bestf);
-      team_combine<TW>(tr, gx, wit, k, S, graw, bestf, best, bi, G);
+      wave_best(best, bi);
+      bestf = a.det_pivot ? wave_max(bestf) : best;
+      if (TW > 1 && chc * wit >= c) {
+        // no rows of this wave
+        if (lane < k) {
+#pragma unroll
+          for (int e = 0; e < 9; ++e) gw[AS * lane + e] = 0;
+        }
+      }
+      team_combine<TW>(tr, wit, S, graw, bestf, best, bi);
       if (!a.det_pivot) bestf = best;
       // no usable row (all used or non-finite): stop without a new term
       if (!(best >= NT(0)) || bi < 0 || bi >= c) { fallback = true; break; }
@@ -552,17 +672,22 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
       // single precision: a residual at the rounding level of the raw column
       // (32 units of roundoff) carries no information; the block is converged
       if (sizeof(T) == 4 && bestf <= NT(3.6e-12) * graw) { converged = true; break; }
+      const int ik = bi;
+      if (whole && lane == (ik & 63)) {
+#pragma unroll
+        for (int e = 0; e < 9; ++e) sh.piv[e] = ik >= 64 ? rs[1][e] : rs[0][e];
+      }
       team_sync<TW>();
       // pivot entry, determinant test and inverse in FP64 (every lane)
       double P[9];
 #pragma unroll
-      for (int e = 0; e < 9; ++e) P[e] = (double)Ck[9 * (int64_t)bi + e];
+      for (int e = 0; e < 9; ++e) P[e] = (double)(whole ? sh.piv[e] : Ck[9 * (int64_t)ik + e]);
       // stored factors keep the pivot entry P_k = a(i_k) after q_k (the
       // backward differentiates c_k = a P_k^-1 with the P_k that was used)
       if (!fuse && lead) {
         T* ps = Ck + 9 * (int64_t)(c + q);
 #pragma unroll
-        for (int e = 0; e < 9; ++e) ps[e] = Ck[9 * (int64_t)bi + e];
+        for (int e = 0; e < 9; ++e) ps[e] = (T)P[e];
       }
       // every wave of a team holds P before the normalisation below
       // overwrites row i_k (a single wave loads it before it stores)
@@ -585,8 +710,8 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
       Pi[6] = (P[3] * P[7] - P[4] * P[6]) * id;
       Pi[7] = (P[1] * P[6] - P[0] * P[7]) * id;
       Pi[8] = (P[0] * P[4] - P[1] * P[3]) * id;
-      const int ik = bi;
       if (lead) sh.pi[k] = ik;
+      if (lane == (ik & 63)) usedi |= 1ull << ((ik >> 6) & 63);
       // A_kk = Pi^T S Pi; A_mk = (Ghat_m - sum_m' A_mm' q_m'(j)) Pi (lane m)
       double Akk[9];
       {
@@ -599,12 +724,23 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
         mul_mm(PiT, SP, Akk);
       }
       if (lane < k) {
+        double G[9];   // Ghat_m of all rows, m = lane
+#pragma unroll
+        for (int e = 0; e < 9; ++e) G[e] = gw[AS * lane + e];
+        if constexpr (TW > 1) {
+#pragma unroll
+          for (int e = 0; e < 9; ++e) {
+            double v = wg[0].g[AS * lane + e];
+            for (int w = 1; w < TW; ++w) v += wg[w].g[AS * lane + e];
+            G[e] = v;
+          }
+        }
 #pragma unroll 1
         for (int m2 = lane; m2 < k; ++m2) {
           double Am[9], qd[9];
           load_hist(hA, lane, m2, Am);
 #pragma unroll
-          for (int e = 0; e < 9; ++e) qd[e] = (double)sh.qc[9 * m2 + e];
+          for (int e = 0; e < 9; ++e) qd[e] = (double)sh.qc[QS * m2 + e];
           sub_mm<double>(G, Am, qd);
         }
         double Amk[9];
@@ -614,7 +750,7 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
 #pragma unroll
           for (int e = 0; e < 9; ++e) {
             d[e] = Amk[e];
-            sh.am[9 * lane + e] = Amk[e];
+            sh.am[AS * lane + e] = Amk[e];
           }
         }
       }
@@ -626,26 +762,31 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
       // normalisation: c_k = a P^-1 in FP64, rounded to T once (P^-1 rounded
       // to single precision first would carry its rounding into c_k times the
       // condition number of P)
-#pragma unroll 1
-      for (int i = tid; i < c; i += stride) {
+      auto normalise = [&](const T* v9, int i) {
         double v[9];
 #pragma unroll
-        for (int e = 0; e < 9; ++e) v[e] = (double)Ck[9 * (int64_t)i + e];
+        for (int e = 0; e < 9; ++e) v[e] = (double)v9[e];
 #pragma unroll
         for (int r = 0; r < 3; ++r)
 #pragma unroll
           for (int cc = 0; cc < 3; ++cc)
             Ck[9 * (int64_t)i + 3 * r + cc] =
                 (T)(v[3 * r] * Pi[cc] + v[3 * r + 1] * Pi[3 + cc] + v[3 * r + 2] * Pi[6 + cc]);
+      };
+      if (whole) {
+        if (lane < c) normalise(rs[0], lane);
+        if (lane + 64 < c) normalise(rs[1], lane + 64);
+      } else {
+#pragma unroll 1
+        for (int i = tid; i < c; i += stride) normalise(Ck + 9 * (int64_t)i, i);
       }
       team_sync<TW>();   // A side done with sh.qc; c_k written
 #pragma unroll 1
       for (int t = tid; t < 9 * k; t += stride) {
         const int m = t / 9, e = t - 9 * m;
-        sh.qc[t] = fb[sh.off[m] + 9 * (int64_t)ik + e];
+        sh.qc[QS * m + e] = fb[sh.off[m] + 9 * (int64_t)ik + e];
       }
       const double xi0 = xt[3 * ik], xi1 = xt[3 * ik + 1], xi2 = xt[3 * ik + 2];
-      if (MF) sample_mfma<TW, MF>(fr, a.kp.input_mode, xsr, q, xi0, xi1, xi2, -1.0, (float*)Qk, wit);
       team_sync<TW>();
       // ---- row pass: residual, Bhat, next column pivot, sum q_k q_k^T, t_k
       best = -1;
@@ -656,24 +797,23 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
 #pragma unroll
       for (int e = 0; e < 13; ++e) SB[e] = 0;
 #pragma unroll 1
-      for (int base = CH * wit; base < q; base += CH * TW) {
-        T rs[RCH][9];
+      for (int base = chq * wit; base < q; base += chq * TW) {
+        const int end = min(base + chq, q);
+        if constexpr (MF)
+          sample_rows<TW, MF>(fr, a.kp.input_mode, xsr, q, base, end, xi0, xi1, xi2, -1.0,
+                              (float(&)[RCH][9])rs);
+        else
 #pragma unroll
-        for (int r = 0; r < RCH; ++r) {
-          const int jj = base + 64 * r + lane;
-          if (jj < q) {
-            if (MF) {
-#pragma unroll
-              for (int e = 0; e < 9; ++e) rs[r][e] = Qk[9 * (int64_t)jj + e];
-            } else {
+          for (int r = 0; r < RCH; ++r) {
+            const int jj = base + 64 * r + lane;
+            if (jj < end) {
               kernel_entry<T>(a.kp, wl, (T)(xi0 - xsr[3 * jj]), (T)(xi1 - xsr[3 * jj + 1]),
                               (T)(xi2 - xsr[3 * jj + 2]), rs[r], ik & 1, jj & 1);
-            }
-          } else {
+            } else {
 #pragma unroll
-            for (int e = 0; e < 9; ++e) rs[r][e] = 0;
+              for (int e = 0; e < 9; ++e) rs[r][e] = 0;
+            }
           }
-        }
         double V[RCH][9];   // sum_{m<k} A_mk^T q_m(j)
 #pragma unroll
         for (int r = 0; r < RCH; ++r)
@@ -681,7 +821,7 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
           for (int e = 0; e < 9; ++e) V[r][e] = 0;
         // q_m(j) of the next m is loaded while m is worked on
         T qn[RCH][9];
-        if (k > 0) load_rows<T>(fb + sh.off[0] + 9 * (int64_t)c, base + lane, q, qn);
+        if (k > 0) load_rows<T>(fb, sh.off[0] + 9 * (int64_t)c, base, end, qn);
 #pragma unroll 1
         for (int m = 0; m < k; ++m) {
           T qq[RCH][9];
@@ -689,13 +829,13 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
           for (int r = 0; r < RCH; ++r)
 #pragma unroll
             for (int e = 0; e < 9; ++e) qq[r][e] = qn[r][e];
-          if (m + 1 < k) load_rows<T>(fb + sh.off[m + 1] + 9 * (int64_t)c, base + lane, q, qn);
+          if (m + 1 < k) load_rows<T>(fb, sh.off[m + 1] + 9 * (int64_t)c, base, end, qn);
           T cv[9];
           double am[9];
 #pragma unroll
           for (int e = 0; e < 9; ++e) {
-            cv[e] = sh.qc[9 * m + e];
-            am[e] = sh.am[9 * m + e];
+            cv[e] = sh.qc[QS * m + e];
+            am[e] = sh.am[AS * m + e];
           }
 #pragma unroll
           for (int r = 0; r < RCH; ++r) {
@@ -712,7 +852,7 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
 #pragma unroll
         for (int r = 0; r < RCH; ++r) {
           const int jj = base + 64 * r + lane;
-          if (jj >= q) continue;
+          if (jj >= end) continue;
           NT nrm = 0;
 #pragma unroll
           for (int e = 0; e < 9; ++e) {
@@ -737,17 +877,21 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
           }
           NT sel = a.det_pivot ? det3<NT>(rs[r]) : nrm;
           bool used = false;
+          if (bits) {
+            used = (usedj >> (jj >> 6)) & 1;
+          } else {
 #pragma unroll 1
-          for (int m = 0; m <= k; ++m) used |= (sh.pj[m] == jj);
+            for (int m = 0; m <= k; ++m) used |= (sh.pj[m] == jj);
+          }
           if (used) sel = -1;
           if (sel > best || (sel == best && jj < bi)) { best = sel; bi = jj; }
         }
       }
       wave_sumv(SB);
-      wave_argmax(best, bi);
+      wave_best(best, bi);
       {
         double d1 = 0, d2 = 0;
-        team_combine<TW>(tr, gx, wit, 0, SB, d1, d2, best, bi, G);
+        team_combine<TW>(tr, wit, SB, d1, d2, best, bi);
       }
       const int jn = (bi >= 0 && bi < q) ? bi : -1;   // -1 only when every column is used
       const double cross = SB[12];
@@ -794,7 +938,7 @@ __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, con
 #pragma unroll 1
         for (int jj = 0; jj < q; ++jj) {
           float K[9];
-          mfma_entry<false, MF>(fr, a.kp.input_mode, x0 - xsr[3 * jj], x1 - xsr[3 * jj + 1],
+          mfma_entry<MF>(fr, a.kp.input_mode, x0 - xsr[3 * jj], x1 - xsr[3 * jj + 1],
                      x2 - xsr[3 * jj + 2], K);
           const T* f = a.Fs + 3 * ((int64_t)ns.x + jj);
           v0 += (double)(K[0] * (float)f[0] + K[1] * (float)f[1] + K[2] * (float)f[2]);
@@ -857,6 +1001,7 @@ __global__ __launch_bounds__(AW_T) void k_aca_team(AcaArgs<T> a) {
   __shared__ bf16x8 frb[MF == MF_BF16 ? FR_TOTAL : 1];
   __shared__ float frf[MF == MF_F32 ? F32_FRAGS * 64 : 1];
   __shared__ TeamSh<T> sh;
+  __shared__ WaveG wgr[AW];
   __shared__ TeamRed tr;
   const void* fr = MF == MF_F32 ? (const void*)frf : (const void*)frb;
   if (MF == MF_BF16) {
@@ -881,14 +1026,14 @@ __global__ __launch_bounds__(AW_T) void k_aca_team(AcaArgs<T> a) {
       // a smaller size class may still need more (a thin block's rank bound
       // is larger); such a tier is left to its own workgroups
       if (a.tier_cap[tt] > a.tier_cap[t0]) continue;
-      aca_worker<T, KIND, MF, AW>(a, wl, fr, sh, &tr, wv, wg * AW, a.work_huge + tt,
+      aca_worker<T, KIND, MF, AW>(a, wl, fr, sh, wgr, &tr, wv, wg * AW, a.work_huge + tt,
                                   a.b0 + a.tier_b[tt], a.b0 + a.tier_b[tt + 1], own,
                                   a.tier_cap[t0]);
       __syncthreads();   // sh.bo of the last fetch is read by every wave
     }
   }
   __syncthreads();
-  aca_worker<T, KIND, MF, AW>(a, wl, fr, sh, &tr, wv, wg * AW, a.work_big, r1, r2,
+  aca_worker<T, KIND, MF, AW>(a, wl, fr, sh, wgr, &tr, wv, wg * AW, a.work_big, r1, r2,
                               ar ? a.arena + wg * AW * a.arena_elems : nullptr,
                               AW * a.arena_elems);
 }
@@ -915,7 +1060,7 @@ __global__ __launch_bounds__(AW_T) void k_aca(AcaArgs<T> a) {
   const int64_t wg = blockIdx.x;
   const bool ar = a.arena != nullptr;
   const int64_t slot = a.slot0_w + wg * AW + wv;
-  aca_worker<T, KIND, MF, 1>(a, wl, fr, shw[wv], nullptr, 0, slot, a.work,
+  aca_worker<T, KIND, MF, 1>(a, wl, fr, shw[wv], nullptr, nullptr, 0, slot, a.work,
                              a.b0 + a.nhuge + a.nbig, a.b1,
                              ar ? a.arena + slot * a.arena_elems : nullptr, a.arena_elems);
 }
@@ -1004,10 +1149,8 @@ void launch_aca_t(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr,
   // kernels in turn share the slots
   const int64_t workers = split ? (grid_t + grid_w) * AW : std::max(grid_t, grid_w) * AW;
   a.slot0_w = split ? grid_t * AW : 0;
-  // per worker: Gram history A (l_max (l_max + 1) / 2 3x3 matrices), then the
-  // cross-wave partials of a workgroup team [AW][64][9]
-  const int64_t half = 9 * ((int64_t)lr->l_max * (lr->l_max + 1) / 2);
-  const int64_t stride = half + (int64_t)AW * 64 * 9;
+  // per worker: Gram history A (l_max (l_max + 1) / 2 3x3 matrices)
+  const int64_t stride = 9 * ((int64_t)lr->l_max * (lr->l_max + 1) / 2);
   if (lr->gram_workers < workers || lr->gram_stride != stride) {
     lr->gram.alloc(ctx->stream, std::max<int64_t>(1, workers * stride) * sizeof(double));
     lr->gram_workers = workers;
@@ -1015,7 +1158,6 @@ void launch_aca_t(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr,
   }
   a.gram = lr->gram.as<double>();
   a.gram_stride = stride;
-  a.gram_half = half;
   a.arena = nullptr;
   a.arena_elems = 0;
   a.huge = nullptr;
