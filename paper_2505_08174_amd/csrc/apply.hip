@@ -3,15 +3,17 @@
 //
 // The low-rank product of an admissible block is applied right to left as in
 // Sec. 3: t_k = sum_j q_k(j) F_j for every term (one workgroup per block),
-// then u_i += sum_k c_k(i) t_k. The second half runs per target particle: a
-// thread walks from the particle's leaf up to the root and adds the terms of
-// every admissible block whose target cluster contains it, in a fixed order,
-// so the sum is deterministic without atomics. The same walk adds blocks that
-// fell back to dense evaluation, the near-field partial sum and the self term
-// alpha_1 F_i (Eq. (2)), and writes U in the caller's particle order.
+// then u_i += sum_k c_k(i) t_k. The second half runs per target row: lanes walk
+// from the row's leaf up to the root and add the terms of every admissible
+// block whose target cluster contains it, in a fixed order, so the sum is
+// deterministic without atomics. The same walk adds blocks that fell back to
+// dense evaluation; the near-field rows and the self term alpha_1 F_i (Eq. (2))
+// are added with it or after it, and U is written in the caller's order.
 #include "api_guard.h"
 #include "devmath.h"
 #include "internal.h"
+#include "near_walk.h"
+#include "wave.h"
 
 void plan_aca(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, int force_streamed);
 void run_aca_stored(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr);
@@ -39,9 +41,17 @@ __global__ __launch_bounds__(T256) void k_gather_rows(const TI* __restrict__ F,
   Fs[3 * s + 2] = (TO)F[3 * o + 2];
 }
 
-// t[toff[b] + k] = sum_j q_k(j) F_sigma(j) for every non-fallback block.
+// t[toff[b] + k] = sum_j q_k(j) F_sigma(j) for every non-fallback block, blocks
+// taken largest first (`order`; a replay has none and takes them as they come). One workgroup per block, its waves take the
+// terms four at a time, lanes over the sources; the four terms' twelve sums
+// share three registers in the wave sums. Bound by the one read of the factors'
+// q halves. (One term at a time by the whole workgroup left most lanes of a
+// block of 64-128 sources idle and took two barriers and three shuffled sums
+// per term: 3.26 ms at 40,000 particles of the 6N form, now
+// 2.55 ms, 4.9 TB/s.)
 template <class T>
 __global__ __launch_bounds__(T256) void k_far_t(const int2* __restrict__ G, int64_t nG,
+                                                const int32_t* __restrict__ order,
                                                 const int4* __restrict__ nodes,
                                                 const int32_t* __restrict__ rank,
                                                 const int32_t* __restrict__ flag,
@@ -50,35 +60,43 @@ __global__ __launch_bounds__(T256) void k_far_t(const int2* __restrict__ G, int6
                                                 const T* __restrict__ pool,
                                                 const T* __restrict__ Fs,
                                                 double* __restrict__ tbuf) {
-  __shared__ double red[T256 / 64][3];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int64_t b = blockIdx.x; b < nG; b += gridDim.x) {
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int64_t o = blockIdx.x; o < nG; o += gridDim.x) {
+    const int64_t b = order ? order[o] : o;
     if (flag[b]) continue;
     const int2 g = G[b];
     const int4 nt = nodes[g.x], ns = nodes[g.y];
     const int c = nt.y - nt.x, q = ns.y - ns.x;
     const int l = rank[b];
-    for (int k = 0; k < l; ++k) {
-      const T* Qk = pool + fptr[b * LMAX_CAP + k] + 9 * (int64_t)c;
-      double s0 = 0, s1 = 0, s2 = 0;
-      for (int j = threadIdx.x; j < q; j += T256) {
-        const T* e = Qk + 9 * (int64_t)j;
-        double f0 = Fs[3 * (int64_t)(ns.x + j)], f1 = Fs[3 * (int64_t)(ns.x + j) + 1],
-               f2 = Fs[3 * (int64_t)(ns.x + j) + 2];
-        s0 += (double)e[0] * f0 + (double)e[1] * f1 + (double)e[2] * f2;
-        s1 += (double)e[3] * f0 + (double)e[4] * f1 + (double)e[5] * f2;
-        s2 += (double)e[6] * f0 + (double)e[7] * f1 + (double)e[8] * f2;
+    const T* F = Fs + 3 * (int64_t)ns.x;
+    for (int k0 = 4 * w; k0 < l; k0 += 4 * (T256 / 64)) {
+      const T* Q[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)   // a term past the rank repeats the last one, unused
+        Q[u] = pool + fptr[b * LMAX_CAP + min(k0 + u, l - 1)] + 9 * (int64_t)c;
+      double v[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+      for (int j = lane; j < q; j += 64) {
+        T e[4][9];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int d = 0; d < 9; ++d) e[u][d] = Q[u][9 * (int64_t)j + d];
+        const double f0 = F[3 * j], f1 = F[3 * j + 1], f2 = F[3 * j + 2];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int d = 0; d < 3; ++d)
+            v[3 * u + d] += (double)e[u][3 * d] * f0 + (double)e[u][3 * d + 1] * f1 +
+                            (double)e[u][3 * d + 2] * f2;
       }
-      s0 = wave_sum(s0);
-      s1 = wave_sum(s1);
-      s2 = wave_sum(s2);
-      __syncthreads();
-      if (lane == 0) { red[w][0] = s0; red[w][1] = s1; red[w][2] = s2; }
-      __syncthreads();
-      if (threadIdx.x < 3) {
-        double v = 0;
-        for (int ww = 0; ww < T256 / 64; ++ww) v += red[ww][threadIdx.x];
-        tbuf[3 * (toff[b] + k) + threadIdx.x] = v;
+      const WaveSums<12> s = wave_sums(v);
+      if ((lane & 15) == 15) {
+        const int row = lane >> 4, e0 = ((row & 1) << 1) | (row >> 1);
+        double* t = tbuf + 3 * (toff[b] + k0);
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+          if (k0 + (4 * r + e0) / 3 < l) t[4 * r + e0] = s.r[r];
       }
     }
   }
@@ -97,66 +115,112 @@ __device__ __forceinline__ void near_sum(const TU* __restrict__ Un, int groups, 
   }
 }
 
-template <class T, class TU, class TO, int KIND>
-__global__ __launch_bounds__(T256) void k_combine(
-    int64_t n, const int32_t* __restrict__ perm, const int32_t* __restrict__ leaf_of,
-    const int32_t* __restrict__ parent, const int4* __restrict__ nodes,
-    const int32_t* __restrict__ far_ptr, const int2* __restrict__ G,
-    const int32_t* __restrict__ rank, const int32_t* __restrict__ flag,
-    const int64_t* __restrict__ fptr, const int64_t* __restrict__ toff,
-    const T* __restrict__ pool, const double* __restrict__ tbuf, const double* __restrict__ xs,
-    const T* __restrict__ Fs, const TU* __restrict__ Un, int groups, KParams kp,
-    TO* __restrict__ U) {
-  __shared__ T wl[KIND == KIND_MLP ? MLP_NP : 1];
-  if (KIND == KIND_MLP) {
-    const T* w = (const T*)kp.w;
+template <class T>
+struct FarArgs {
+  const int32_t *leaf_of, *parent, *far_ptr;
+  const int4* nodes;
+  const int2* G;
+  const int32_t *rank, *flag;
+  const int64_t *fptr, *toff;
+  const T* pool;
+  const double* tbuf;
+  const double* xs;
+  const T* Fs;
+  KParams kp;
+  int64_t n;
+  int sets;   // workgroups per 64 rows (sets of partial rows when > 1)
+};
+
+// Far field of 64 rows per workgroup, one lane per row and share: a lane walks
+// from its row's leaf to the root and adds c_k(i) t_k of every admissible block
+// whose target cluster holds the row, the blocks of a node dealt to the shares
+// in turn (four waves, and `sets` workgroups). Every share adds in a fixed order.
+// FB: blocks that fell back to dense evaluation exist. FINAL (one set): also adds
+// the near-field rows and the self term and writes U in the caller's order;
+// otherwise the rows of the set go to `part`. Bound by the one read of the
+// factors' c halves (one lane per row walked alone, n/64 waves in all: 9.0 ms at
+// 40,000 particles of the 6N form, now 3.2 ms; 2.9 to 0.39 ms at 30,000 BF16).
+template <class T, class TU, class TO, int KIND, bool FB, bool FINAL>
+__global__ __launch_bounds__(T256) void k_far_apply(FarArgs<T> a, const int32_t* __restrict__ perm,
+                                                    const TU* __restrict__ Un, int groups,
+                                                    TO* __restrict__ U, double* __restrict__ part) {
+  __shared__ T wl[FB && KIND == KIND_MLP ? MLP_NP : 1];
+  __shared__ double red[4 * 64 * 3];
+  if (FB && KIND == KIND_MLP) {
+    const T* w = (const T*)a.kp.w;
     for (int i = threadIdx.x; i < MLP_NP; i += T256) wl[i] = w[i];
     __syncthreads();
   }
-  int64_t s = (int64_t)blockIdx.x * T256 + threadIdx.x;
-  if (s >= n) return;
-  double u0 = 0, u1 = 0, u2 = 0;
-  near_sum(Un, groups, n, s, u0, u1, u2);
-  const double x0 = xs[3 * s], x1 = xs[3 * s + 1], x2 = xs[3 * s + 2];
-  for (int tau = leaf_of[s]; tau >= 0; tau = parent[tau]) {
-    const int il = (int)(s - nodes[tau].x);
-    const int p1 = far_ptr[tau + 1];
-    for (int p = far_ptr[tau]; p < p1; ++p) {
-      if (flag[p]) {
-        // dense fallback: evaluate the block row directly
-        const int4 ns = nodes[G[p].y];
-        T v0 = 0, v1 = 0, v2 = 0;
-        for (int j = ns.x; j < ns.y; ++j) {
-          T K[9];
-          kernel_entry<T>(kp, wl, (T)(x0 - xs[3 * (int64_t)j]), (T)(x1 - xs[3 * (int64_t)j + 1]),
-                          (T)(x2 - xs[3 * (int64_t)j + 2]), K, (int)(s & 1), j & 1);
-          T f0 = Fs[3 * (int64_t)j], f1 = Fs[3 * (int64_t)j + 1], f2 = Fs[3 * (int64_t)j + 2];
-          v0 += K[0] * f0 + K[1] * f1 + K[2] * f2;
-          v1 += K[3] * f0 + K[4] * f1 + K[5] * f2;
-          v2 += K[6] * f0 + K[7] * f1 + K[8] * f2;
-        }
-        u0 += v0; u1 += v1; u2 += v2;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t s0 = 64 * ((int64_t)blockIdx.x / a.sets), s = s0 + lane;
+  const int set = blockIdx.x % a.sets;
+  const int share = 4 * set + w, shares = 4 * a.sets;
+  double u[3] = {0, 0, 0};
+  if (s < a.n) {
+    // blocks are dealt round robin over the whole walk
+    int turn = share;
+    for (int tau = a.leaf_of[s]; tau >= 0; tau = a.parent[tau]) {
+      const int p0 = a.far_ptr[tau], p1 = a.far_ptr[tau + 1];
+      if (p0 + turn >= p1) {
+        turn -= p1 - p0;
         continue;
       }
-      const int l = rank[p];
-      const double* tb = tbuf + 3 * toff[p];
-      for (int k = 0; k < l; ++k) {
-        const T* e = pool + fptr[(int64_t)p * LMAX_CAP + k] + 9 * (int64_t)il;
-        const double t0 = tb[3 * k], t1 = tb[3 * k + 1], t2 = tb[3 * k + 2];
-        u0 += (double)e[0] * t0 + (double)e[1] * t1 + (double)e[2] * t2;
-        u1 += (double)e[3] * t0 + (double)e[4] * t1 + (double)e[5] * t2;
-        u2 += (double)e[6] * t0 + (double)e[7] * t1 + (double)e[8] * t2;
+      const int il = (int)(s - a.nodes[tau].x);
+      int p = p0 + turn;
+      for (; p < p1; p += shares) {
+        if (FB && a.flag[p]) {
+          // dense fallback: evaluate the block row directly
+          const int4 ns = a.nodes[a.G[p].y];
+          const double x0 = a.xs[3 * s], x1 = a.xs[3 * s + 1], x2 = a.xs[3 * s + 2];
+          T v0 = 0, v1 = 0, v2 = 0;
+          for (int j = ns.x; j < ns.y; ++j) {
+            T K[9];
+            kernel_entry<T>(a.kp, wl, (T)(x0 - a.xs[3 * (int64_t)j]),
+                            (T)(x1 - a.xs[3 * (int64_t)j + 1]), (T)(x2 - a.xs[3 * (int64_t)j + 2]),
+                            K, (int)(s & 1), j & 1);
+            T f0 = a.Fs[3 * (int64_t)j], f1 = a.Fs[3 * (int64_t)j + 1], f2 = a.Fs[3 * (int64_t)j + 2];
+            v0 += K[0] * f0 + K[1] * f1 + K[2] * f2;
+            v1 += K[3] * f0 + K[4] * f1 + K[5] * f2;
+            v2 += K[6] * f0 + K[7] * f1 + K[8] * f2;
+          }
+          u[0] += v0; u[1] += v1; u[2] += v2;
+          continue;
+        }
+        const int l = a.rank[p];
+        const double* tb = a.tbuf + 3 * a.toff[p];
+        const int64_t* fp = a.fptr + (int64_t)p * LMAX_CAP;
+        const T* row = a.pool + 9 * (int64_t)il;
+#pragma unroll 4
+        for (int k = 0; k < l; ++k) {
+          const T* e = row + fp[k];
+          const double t0 = tb[3 * k], t1 = tb[3 * k + 1], t2 = tb[3 * k + 2];
+          u[0] += (double)e[0] * t0 + (double)e[1] * t1 + (double)e[2] * t2;
+          u[1] += (double)e[3] * t0 + (double)e[4] * t1 + (double)e[5] * t2;
+          u[2] += (double)e[6] * t0 + (double)e[7] * t1 + (double)e[8] * t2;
+        }
       }
+      turn = p - p1;
     }
   }
-  const double a1 = (s & 1) ? kp.alpha2 : kp.alpha1;
-  u0 += a1 * (double)Fs[3 * s];
-  u1 += a1 * (double)Fs[3 * s + 1];
-  u2 += a1 * (double)Fs[3 * s + 2];
-  const int64_t o = perm[s];
-  U[3 * o] = (TO)u0;
-  U[3 * o + 1] = (TO)u1;
-  U[3 * o + 2] = (TO)u2;
+  if (!FINAL) {
+    write_rows(red, lane, w, u, s0, a.n, set, part);
+    return;
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) red[192 * w + 3 * lane + d] = u[d];
+  __syncthreads();
+  const int64_t r = s0 + threadIdx.x;
+  if (threadIdx.x >= 64 || r >= a.n) return;
+  double v[3] = {0, 0, 0};
+  near_sum(Un, groups, a.n, r, v[0], v[1], v[2]);
+  const double a1 = (r & 1) ? a.kp.alpha2 : a.kp.alpha1;
+  const int64_t o = perm[r];
+  const double* e = red + 3 * threadIdx.x;
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+    U[3 * o + d] = (TO)((v[d] + (((e[d] + e[192 + d]) + e[384 + d]) + e[576 + d])) +
+                        a1 * (double)a.Fs[3 * r + d]);
 }
 
 // Streamed mode: add the rows of the admissible blocks of launch r that
@@ -190,7 +254,7 @@ template <class T, class TU, class TO>
 __global__ __launch_bounds__(T256) void k_final(int64_t n, const int32_t* __restrict__ perm,
                                                 const T* __restrict__ Fs, const TU* __restrict__ Un,
                                                 int groups, const double* __restrict__ Uf,
-                                                double alpha1, double alpha2,
+                                                int far_sets, double alpha1, double alpha2,
                                                 TO* __restrict__ U) {
   int64_t s = (int64_t)blockIdx.x * T256 + threadIdx.x;
   if (s >= n) return;
@@ -198,21 +262,39 @@ __global__ __launch_bounds__(T256) void k_final(int64_t n, const int32_t* __rest
   const double a1 = (s & 1) ? alpha2 : alpha1;   // odd rows: rotational rows of a 6N kernel
   double u[3] = {0, 0, 0};
   near_sum(Un, groups, n, s, u[0], u[1], u[2]);
+  double f[3] = {0, 0, 0};
+  near_sum(Uf, far_sets, n, s, f[0], f[1], f[2]);
 #pragma unroll
-  for (int d = 0; d < 3; ++d)
-    U[3 * o + d] = (TO)((u[d] + Uf[3 * s + d]) + a1 * (double)Fs[3 * s + d]);
+  for (int d = 0; d < 3; ++d) U[3 * o + d] = (TO)((u[d] + f[d]) + a1 * (double)Fs[3 * s + d]);
 }
 
-// Bytes of `groups` sets of near-field rows.
+// Sets of partial rows of a product: near-field groups and far-field sets (1: the
+// far field adds everything itself and needs no rows), and the bytes they take.
+struct RowSets {
+  int near = 1, far = 1;
+};
 int64_t near_bytes(hh_tree t, hh_kernel k, int prec, int groups) {
   return 3 * t->n * (int64_t)groups * (near_rows_f64(k, prec, groups) ? 8 : 4);
 }
+int64_t set_bytes(hh_tree t, hh_kernel k, int prec, RowSets r) {
+  return (near_bytes(t, k, prec, r.near) + 255) / 256 * 256 +
+         (r.far > 1 ? 3 * t->n * (int64_t)r.far * 8 : 0);
+}
+// Far-field sets: the walks of 64 rows by four waves, split further while that
+// leaves compute units idle (8 resident workgroups each).
+RowSets row_sets(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, int prec) {
+  RowSets r;
+  r.near = near_groups(ctx, t, p, k, prec);
+  const int64_t nw = (t->n + 63) / 64;
+  if (p->nG > 0) r.far = (int)std::min<int64_t>(16, (8 * (int64_t)ctx->n_cu + nw - 1) / nw);
+  return r;
+}
 
-// Stored mode. Fs_ws and Un_ws hold the sorted forces (3 n T) and the
-// near-field rows (`groups` sets); timed = false records no phase events.
+// Stored mode. Fs_ws holds the sorted forces (3 n T), rows_ws the sets of partial
+// rows; timed = false records no phase events.
 template <class T, class TO>
 void matvec_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, const void* F,
-              void* U, void* Fs_ws, void* Un_ws, int groups, bool timed) {
+              void* U, void* Fs_ws, void* rows_ws, RowSets r, bool timed) {
   hipStream_t st = ctx->stream;
   const int64_t n = t->n;
   T* Fs = (T*)Fs_ws;
@@ -220,34 +302,71 @@ void matvec_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, cons
                      t->perm.as<int32_t>(), n, Fs);
   {
     PhaseTimer timer(ctx, HH_PHASE_NEAR, timed);
-    launch_near(ctx, t, p, k, lr->prec, Fs, Un_ws, groups);
+    launch_near(ctx, t, p, k, lr->prec, Fs, rows_ws, r.near);
   }
   int64_t nG = p->nG;
   if (nG > 0) {
     PhaseTimer timer(ctx, HH_PHASE_FAR, timed);
     int grid = (int)std::min<int64_t>(nG, 8192);
     hipLaunchKernelGGL((k_far_t<T>), dim3(grid), dim3(T256), 0, st, p->G.as<int2>(), nG,
-                       t->nodes.as<int4>(), lr->rank.as<int32_t>(), lr->flag.as<int32_t>(),
-                       lr->fptr.as<int64_t>(), lr->toff.as<int64_t>(), lr->pool.as<T>(), Fs,
-                       lr->tbuf.as<double>());
+                       lr->order.as<int32_t>(), t->nodes.as<int4>(), lr->rank.as<int32_t>(),
+                       lr->flag.as<int32_t>(), lr->fptr.as<int64_t>(), lr->toff.as<int64_t>(),
+                       lr->pool.as<T>(), Fs, lr->tbuf.as<double>());
   }
-  KParams kp = make_kparams(k, sizeof(T) == 8);
-#define COMBINE(TU_, KIND_)                                                                   \
-  hipLaunchKernelGGL((k_combine<T, TU_, TO, KIND_>), dim3(nblk(n)), dim3(T256), 0, st, n,      \
-                     t->perm.as<int32_t>(), t->leaf_of.as<int32_t>(), t->parent.as<int32_t>(), \
-                     t->nodes.as<int4>(), p->far_ptr.as<int32_t>(), p->G.as<int2>(),           \
-                     lr->rank.as<int32_t>(), lr->flag.as<int32_t>(), lr->fptr.as<int64_t>(),   \
-                     lr->toff.as<int64_t>(), lr->pool.as<T>(), lr->tbuf.as<double>(),          \
-                     t->xs.as<double>(), Fs, (const TU_*)Un_ws, groups, kp, (TO*)U)
-  {
-    PhaseTimer timer(ctx, HH_PHASE_COMBINE, timed);
-    if (near_rows_f64(k, lr->prec, groups)) {
-      if (k->kind == KIND_MLP) COMBINE(double, KIND_MLP); else COMBINE(double, KIND_RPY);
+  PhaseTimer timer(ctx, HH_PHASE_COMBINE, timed);
+  double* part = (double*)((char*)rows_ws + (near_bytes(t, k, lr->prec, r.near) + 255) / 256 * 256);
+  const bool f64 = near_rows_f64(k, lr->prec, r.near);
+  if (nG > 0) {
+    FarArgs<T> a;
+    a.leaf_of = t->leaf_of.as<int32_t>();
+    a.parent = t->parent.as<int32_t>();
+    a.far_ptr = p->far_ptr.as<int32_t>();
+    a.nodes = t->nodes.as<int4>();
+    a.G = p->G.as<int2>();
+    a.rank = lr->rank.as<int32_t>();
+    a.flag = lr->flag.as<int32_t>();
+    a.fptr = lr->fptr.as<int64_t>();
+    a.toff = lr->toff.as<int64_t>();
+    a.pool = lr->pool.as<T>();
+    a.tbuf = lr->tbuf.as<double>();
+    a.xs = t->xs.as<double>();
+    a.Fs = Fs;
+    a.kp = make_kparams(k, sizeof(T) == 8);
+    a.n = n;
+    a.sets = r.far;
+    const dim3 grid((unsigned)((n + 63) / 64 * r.far));
+    const int32_t* perm = t->perm.as<int32_t>();
+    // <near-row type, kernel (read in fallbacks only), fallbacks, final>
+#define FAR_APPLY(TU_, TO_, KIND_, FB_, FIN_)                                                  \
+  hipLaunchKernelGGL((k_far_apply<T, TU_, TO_, KIND_, FB_, FIN_>), grid, dim3(T256), 0, st, a, \
+                     perm, (const TU_*)rows_ws, r.near, (TO_*)U, part)
+    const bool fb = lr->n_fallback > 0, mlp = k->kind == KIND_MLP;
+    if (r.far > 1) {
+      if (!fb) FAR_APPLY(double, double, KIND_RPY, false, false);
+      else if (mlp) FAR_APPLY(double, double, KIND_MLP, true, false);
+      else FAR_APPLY(double, double, KIND_RPY, true, false);
+    } else if (f64) {
+      if (!fb) FAR_APPLY(double, TO, KIND_RPY, false, true);
+      else if (mlp) FAR_APPLY(double, TO, KIND_MLP, true, true);
+      else FAR_APPLY(double, TO, KIND_RPY, true, true);
     } else {
-      if (k->kind == KIND_MLP) COMBINE(T, KIND_MLP); else COMBINE(T, KIND_RPY);
+      if (!fb) FAR_APPLY(T, TO, KIND_RPY, false, true);
+      else if (mlp) FAR_APPLY(T, TO, KIND_MLP, true, true);
+      else FAR_APPLY(T, TO, KIND_RPY, true, true);
     }
+#undef FAR_APPLY
   }
-#undef COMBINE
+  if (nG == 0 || r.far > 1) {
+    const int far = nG == 0 ? 0 : r.far;
+    if (f64)
+      hipLaunchKernelGGL((k_final<T, double, TO>), dim3(nblk(n)), dim3(T256), 0, st, n,
+                         t->perm.as<int32_t>(), Fs, (const double*)rows_ws, r.near, part, far,
+                         k->alpha1, k->alpha2, (TO*)U);
+    else
+      hipLaunchKernelGGL((k_final<T, T, TO>), dim3(nblk(n)), dim3(T256), 0, st, n,
+                         t->perm.as<int32_t>(), Fs, (const T*)rows_ws, r.near, part, far,
+                         k->alpha1, k->alpha2, (TO*)U);
+  }
   HIP_OK(hipGetLastError());
 }
 
@@ -256,10 +375,10 @@ void matvec_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, cons
 template <class T, class TO>
 void matvec_ws_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, const void* F,
                  void* U) {
-  const int groups = near_groups(ctx, t, p, k, lr->prec);
+  const RowSets r = row_sets(ctx, t, p, k, lr->prec);
   lr->ws_f.ensure(ctx->stream, 3 * t->n * sizeof(T));
-  lr->ws_near.ensure(ctx->stream, near_bytes(t, k, lr->prec, groups));
-  matvec_t<T, TO>(ctx, t, p, lr, k, F, U, lr->ws_f.p, lr->ws_near.p, groups, true);
+  lr->ws_near.ensure(ctx->stream, set_bytes(t, k, lr->prec, r));
+  matvec_t<T, TO>(ctx, t, p, lr, k, F, U, lr->ws_f.p, lr->ws_near.p, r, true);
 }
 
 // Bytes of the sorted forces in the static scratch of the allocation-free
@@ -270,14 +389,15 @@ int64_t noalloc_forces(int64_t n, int prec) {
 
 // The allocation-free product: the same launches with the workspaces in the
 // device's static scratch (base, HH_NOALLOC_SCRATCH_BYTES); the near-field
-// sources are split only as far as the partial rows fit.
+// sources and the far-field walks are split only if the partial rows fit.
 template <class T, class TO>
 void matvec_noalloc_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k,
                       const void* F, void* U, char* base) {
   const int64_t bf = noalloc_forces(t->n, lr->prec);
-  int groups = near_groups(ctx, t, p, k, lr->prec);
-  if (bf + near_bytes(t, k, lr->prec, groups) > (int64_t)HH_NOALLOC_SCRATCH_BYTES) groups = 1;
-  matvec_t<T, TO>(ctx, t, p, lr, k, F, U, base, base + bf, groups, false);
+  RowSets r = row_sets(ctx, t, p, k, lr->prec);
+  if (bf + set_bytes(t, k, lr->prec, r) > (int64_t)HH_NOALLOC_SCRATCH_BYTES) r.far = 1;
+  if (bf + near_bytes(t, k, lr->prec, r.near) > (int64_t)HH_NOALLOC_SCRATCH_BYTES) r.near = 1;
+  matvec_t<T, TO>(ctx, t, p, lr, k, F, U, base, base + bf, r, false);
 }
 
 template <class T, class TO>
@@ -323,10 +443,10 @@ void matvec_streamed_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kerne
     if (near_rows_f64(k, lr->prec, groups))
       hipLaunchKernelGGL((k_final<T, double, TO>), dim3(nblk(n)), dim3(T256), 0, st, n,
                          t->perm.as<int32_t>(), Fs.as<T>(), Un.as<double>(), groups,
-                         Uf.as<double>(), k->alpha1, k->alpha2, (TO*)U);
+                         Uf.as<double>(), 1, k->alpha1, k->alpha2, (TO*)U);
     else
       hipLaunchKernelGGL((k_final<T, T, TO>), dim3(nblk(n)), dim3(T256), 0, st, n,
-                         t->perm.as<int32_t>(), Fs.as<T>(), Un.as<T>(), groups, Uf.as<double>(),
+                         t->perm.as<int32_t>(), Fs.as<T>(), Un.as<T>(), groups, Uf.as<double>(), 1,
                          k->alpha1, k->alpha2, (TO*)U);
   }
   HIP_OK(hipGetLastError());
