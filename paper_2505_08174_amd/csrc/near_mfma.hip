@@ -158,7 +158,8 @@ __global__ __launch_bounds__(NEAR_WG) void k_near_f32(NearF<TO> a) {
 
 }  // namespace
 
-// Work units (leaf rank, chunk of 32 targets), built once per tree.
+// Work units of the FP32 backward (leaf rank, chunk of 32 targets), built once per
+// tree.
 void ensure_units(hh_ctx ctx, hh_tree t) {
   if (t->n_units > 0) return;
   hipStream_t st = ctx->stream;

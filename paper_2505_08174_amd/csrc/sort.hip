@@ -1,6 +1,6 @@
 // Device-wide exclusive scan and stable LSD radix sort (8-bit digits).
 //
-// Radix pass: (1) each 256-thread block counts the digits of its 4096-item
+// Radix pass of the tiled sort: (1) each 256-thread block counts the digits of its 4096-item
 // tile in LDS and writes a digit-major histogram; (2) one exclusive scan over
 // all (digit, tile) counts gives every tile its output base per digit;
 // (3) each block re-reads its tile in 16 rounds of 256 consecutive items and
@@ -88,6 +88,142 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_down(const int64_t* __restrict_
   }
 }
 
+// Exclusive scan of up to SCAN_ONE values by one workgroup: one launch for the
+// histograms and lists of small systems, where each of the three launches above
+// costs more than the scan (the line lies where the one workgroup's rounds take
+// as long as two launches).
+constexpr int SCAN_ONE = 16384;
+__global__ __launch_bounds__(1024) void k_scan_one(const int64_t* __restrict__ in, int n,
+                                                   int64_t* __restrict__ out) {
+  __shared__ int64_t wsum[16];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int64_t carry = 0;
+  for (int b = 0; b < n; b += 4096) {
+    const int i0 = b + 4 * (int)threadIdx.x;
+    int64_t v[4], s = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = i0 + e < n ? in[i0 + e] : 0;
+      s += v[e];
+    }
+    const int64_t inc = wave_incl_scan(s, lane);
+    if (lane == 63) wsum[w] = inc;
+    __syncthreads();
+    int64_t off = carry, tot = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      if (i < w) off += wsum[i];
+      tot += wsum[i];
+    }
+    int64_t ex = off + inc - s;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (i0 + e < n) out[i0 + e] = ex;
+      ex += v[e];
+    }
+    carry += tot;
+    __syncthreads();
+  }
+}
+
+// Stable LSD radix sort of up to SS_N pairs by one workgroup, all passes in one
+// launch: the pairs stay in registers, LDS holds them between passes. Up to here
+// the 5 launches per pass of the tiled sort (40 for Morton keys) cost more than
+// sorting on one compute unit: 35 us for 2,000 Morton keys and 72 us for 5,000,
+// against 130 us of kernels and as much of launches.
+constexpr int SS_T = 1024, SS_E = 8, SS_N = SS_T * SS_E;
+__global__ __launch_bounds__(SS_T) void k_sort_small(uint64_t* __restrict__ keys,
+                                                     uint32_t* __restrict__ vals, int n,
+                                                     int passes) {
+  __shared__ uint64_t sk[SS_N];
+  __shared__ uint32_t sv[SS_N];
+  __shared__ int base[256];
+  __shared__ int wcnt[SS_T / 64][256];
+  __shared__ int wtot[4];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  uint64_t key[SS_E];
+  uint32_t val[SS_E];
+#pragma unroll
+  for (int r = 0; r < SS_E; ++r) {
+    const int i = r * SS_T + tid;
+    key[r] = i < n ? keys[i] : 0;
+    val[r] = i < n ? vals[i] : 0;
+  }
+  for (int i = tid; i < (SS_T / 64) * 256; i += SS_T) (&wcnt[0][0])[i] = 0;
+  for (int p = 0; p < passes; ++p) {
+    const int shift = 8 * p;
+    if (tid < 256) base[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < SS_E; ++r)
+      if (r * SS_T + tid < n) atomicAdd(&base[(key[r] >> shift) & 255], 1);
+    __syncthreads();
+    int c = 0, inc = 0;
+    if (tid < 256) {
+      c = base[tid];
+      inc = (int)wave_incl_scan(c, lane);
+      if (lane == 63) wtot[w] = inc;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      int off = 0;
+      for (int i = 0; i < w; ++i) off += wtot[i];
+      base[tid] = off + inc - c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < SS_E; ++r) {
+      if (r * SS_T >= n) break;   // uniform
+      const bool valid = r * SS_T + tid < n;
+      const int d = (int)((key[r] >> shift) & 255);
+      const uint64_t vb = __ballot(valid);
+      uint64_t m = valid ? vb : ~vb;
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        const uint64_t bal = __ballot((d >> b) & 1);
+        m &= ((d >> b) & 1) ? bal : ~bal;
+      }
+      const int rank = __popcll(m & lt);
+      if (valid && rank == 0) wcnt[w][d] = __popcll(m);
+      __syncthreads();
+      if (valid) {
+        int pos = base[d] + rank;
+        for (int ww = 0; ww < w; ++ww) pos += wcnt[ww][d];
+        sk[pos] = key[r];
+        sv[pos] = val[r];
+      }
+      __syncthreads();
+      if (tid < 256) {
+        int add = 0;
+        for (int ww = 0; ww < SS_T / 64; ++ww) {
+          add += wcnt[ww][tid];
+          wcnt[ww][tid] = 0;
+        }
+        base[tid] += add;
+      }
+      __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < SS_E; ++r) {
+      const int i = r * SS_T + tid;
+      if (i < n) {
+        key[r] = sk[i];
+        val[r] = sv[i];
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < SS_E; ++r) {
+    const int i = r * SS_T + tid;
+    if (i < n) {
+      keys[i] = key[r];
+      vals[i] = val[r];
+    }
+  }
+}
+
 constexpr int RS_T = 256;
 constexpr int RS_ROUNDS = 16;
 constexpr int RS_TILE = RS_T * RS_ROUNDS;
@@ -158,6 +294,11 @@ __global__ __launch_bounds__(RS_T) void k_radix_scatter(
 
 void scan_exclusive_i64(hh_ctx ctx, const int64_t* in, int64_t* out, int64_t n) {
   if (n <= 0) return;
+  if (n <= SCAN_ONE) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(1024), 0, ctx->stream, in, (int)n, out);
+    HIP_OK(hipGetLastError());
+    return;
+  }
   int64_t tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
   DevBuf sums;
   sums.alloc(ctx->stream, tiles * sizeof(int64_t));
@@ -173,6 +314,12 @@ void scan_exclusive_i64(hh_ctx ctx, const int64_t* in, int64_t* out, int64_t n) 
 void radix_sort_u64(hh_ctx ctx, uint64_t* keys, uint32_t* vals, int64_t n, int bits) {
   if (n <= 1) return;
   int passes = (bits + 7) / 8;
+  if (n <= SS_N) {
+    hipLaunchKernelGGL(k_sort_small, dim3(1), dim3(SS_T), 0, ctx->stream, keys, vals, (int)n,
+                       passes);
+    HIP_OK(hipGetLastError());
+    return;
+  }
   int64_t nblocks = (n + RS_TILE - 1) / RS_TILE;
   DevBuf k2, v2, hist;
   k2.alloc(ctx->stream, n * sizeof(uint64_t));

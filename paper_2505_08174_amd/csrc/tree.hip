@@ -83,6 +83,34 @@ __global__ __launch_bounds__(T256) void k_minmax_sys(const double* __restrict__ 
   }
 }
 
+// The same for one system: a few workgroups over all particles, so that only
+// their waves meet at the six atomics (one wave per 64 particles took 270 us at
+// 250,000 particles, all of it at the atomics).
+__global__ __launch_bounds__(T256) void k_minmax_one(const double* __restrict__ X, int64_t n,
+                                                     unsigned long long* __restrict__ mm,
+                                                     int* __restrict__ bad) {
+  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  bool nonfinite = false;
+  for (int64_t i = (int64_t)blockIdx.x * T256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * T256)
+    for (int d = 0; d < 3; ++d) {
+      const double v = X[3 * i + d];
+      nonfinite |= !isfinite(v);
+      lo[d] = fmin(lo[d], v);
+      hi[d] = fmax(hi[d], v);
+    }
+  if (nonfinite) atomicOr(bad, 1);
+  for (int d = 0; d < 3; ++d)
+    for (int o = 32; o > 0; o >>= 1) {
+      lo[d] = fmin(lo[d], __shfl_xor(lo[d], o, 64));
+      hi[d] = fmax(hi[d], __shfl_xor(hi[d], o, 64));
+    }
+  if ((threadIdx.x & 63) == 0 && lo[0] <= hi[0])
+    for (int d = 0; d < 3; ++d) {
+      atomicMin(&mm[d], ord64(lo[d]));
+      atomicMax(&mm[3 + d], ord64(hi[d]));
+    }
+}
+
 __global__ void k_mm_init(unsigned long long* __restrict__ mm, int nsys) {
   int i = blockIdx.x * 256 + threadIdx.x;
   if (i < 6 * nsys) mm[i] = (i % 6) < 3 ? ~0ull : 0ull;
@@ -504,8 +532,12 @@ static void build_tree_impl(hh_ctx ctx, hh_tree_s* t, const double* X, int64_t n
   HIP_OK(hipMemsetAsync(flags, 0, 4 * sizeof(int), st));
   hipLaunchKernelGGL(k_mm_init, dim3((6 * nsys + 255) / 256), dim3(256), 0, st,
                      mm.as<unsigned long long>(), nsys);
-  hipLaunchKernelGGL(k_minmax_sys, dim3(nblk(n)), dim3(T256), 0, st, X, n, off, nsys,
-                     mm.as<unsigned long long>(), flags);
+  if (nsys == 1)
+    hipLaunchKernelGGL(k_minmax_one, dim3(std::min(nblk(n), 128u)), dim3(T256), 0, st, X, n,
+                       mm.as<unsigned long long>(), flags);
+  else
+    hipLaunchKernelGGL(k_minmax_sys, dim3(nblk(n)), dim3(T256), 0, st, X, n, off, nsys,
+                       mm.as<unsigned long long>(), flags);
   hipLaunchKernelGGL(k_sys_final, dim3((nsys + 255) / 256), dim3(256), 0, st,
                      mm.as<unsigned long long>(), nsys, qc.as<double>());
   t->keys.alloc(st, n * sizeof(uint64_t));
@@ -599,9 +631,6 @@ static void build_tree_impl(hh_ctx ctx, hh_tree_s* t, const double* X, int64_t n
   hipLaunchKernelGGL(k_inner_box, dim3(nblk(m * 64)), dim3(T256), 0, st, t->nodes.as<int4>(), m,
                      t->leaves.as<int32_t>(), nl, t->bbox.as<double>());
   HIP_OK(hipGetLastError());
-  // work units of the MFMA near field (32-target chunks of every leaf), so
-  // that no product on this tree allocates
-  ensure_units(ctx, t);
 }
 
 extern "C" {
@@ -668,7 +697,6 @@ hh_status hh_build_tree6(hh_ctx ctx, const double* X, int64_t n, int32_t c_leaf,
     take(t->leaf_id, one.leaf_id);
     take(t->leaves, one.leaves);
     take(t->roots, one.roots);
-    ensure_units(ctx, t);
     ctx_sync(ctx);   // the host values above stay valid until the copies ran
   } catch (...) {
     delete t;
