@@ -38,6 +38,8 @@
 // two-row share of Ghat_m is formed in T before the FP64 wave sum). In the
 // BF16 form the samples come from the MFMA MLP tile (activations carried as
 // BF16 hi + lo).
+#include <math.h>
+
 #include <algorithm>
 #include <iterator>
 
@@ -1251,13 +1253,21 @@ void plan_aca(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, int force_streame
   std::vector<int32_t> cs, qs;
   block_sizes(ctx, t, p, cs, qs);
   const size_t es = lr->prec == HH_FP64 ? 8 : 4;
-  int64_t est = 0;
+  // est decides between stored and streamed factors (20 terms a block). The first
+  // pool takes the terms that the tolerance suggests (20 at 1e-4, more below it),
+  // or every block's worst case where that is no more than a GiB: an ACA that
+  // overflows its pool runs again as a whole.
+  const int rank_guess =
+      (int)std::min<double>(lr->l_max, std::max(20.0, -5.0 * log10(std::max(lr->eps, 1e-30))));
+  int64_t est = 0, guess = 0, worst = 0;
   std::vector<int32_t> big, small;
   int64_t arena = 0;
   for (int64_t b = 0; b < nG; ++b) {
     const int64_t cq = (int64_t)cs[b] + qs[b];
     const int64_t kc = std::min<int64_t>(std::min(cs[b], qs[b]), lr->l_max);
     est += 9 * (cq + 1) * std::min<int64_t>(kc, 20);
+    guess += 9 * (cq + 1) * std::min<int64_t>(kc, rank_guess);
+    worst += 9 * (cq + 1) * kc;
     if (size_cls(cs[b], qs[b]) >= ctx->team_cls) {
       big.push_back((int32_t)b);
     } else {
@@ -1265,7 +1275,9 @@ void plan_aca(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, int force_streame
       arena = std::max(arena, 9 * cq * kc);
     }
   }
-  lr->est_elems = est;
+  lr->pool_first = (double)worst * es <= (double)(1ll << 30)
+                       ? worst
+                       : std::max(est, std::min(guess, (int64_t)(0.5 * (double)ctx->budget_bytes / es)));
   lr->streamed = force_streamed || (double)est * es > 0.5 * (double)ctx->budget_bytes;
   std::vector<int32_t> ord;
   ord.reserve(std::max<int64_t>(nG, 1));
@@ -1377,7 +1389,7 @@ void run_aca_stored(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr
   hipStream_t st = ctx->stream;
   int64_t nG = p->nG;
   size_t es = lr->prec == HH_FP64 ? 8 : 4;
-  int64_t want = lr->est_elems;
+  int64_t want = lr->pool_first;
   int* flags = (int*)ctx->scratch_flag.p;  // [0] overflow, [1] work counter
   int64_t* top = (int64_t*)ctx->scratch_flag.p + 4;
   for (int attempt = 0; attempt < 6; ++attempt) {

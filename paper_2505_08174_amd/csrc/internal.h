@@ -150,7 +150,7 @@ struct hh_tree_s {
   DevBuf leaf_id;   // int32 [n_nodes] rank among leaves, -1 for internal
   DevBuf leaves;    // int32 [n_leaves] node id of each leaf, in order
   DevBuf leaf_of;   // int32 [n] leaf node of sorted position s
-  DevBuf units;     // int2 [n_units] (leaf rank, chunk of 32 targets), built with the tree
+  DevBuf units;     // int2 [n_units] (leaf rank, chunk of 32 targets), built by the first FP32 backward
   int64_t n_units = 0;
   int n_sys = 1;                    // independent systems (batched build)
   std::vector<int64_t> offs_host;   // particle offsets of the systems [n_sys+1]
@@ -218,7 +218,7 @@ struct hh_lowrank_s {
   bool streamed = false;
   bool stats_dirty = true;
   hh_kernel kern = nullptr;
-  int64_t est_elems = 0;
+  int64_t pool_first = 0;        // elements of the factor pool the ACA starts with
   std::vector<int64_t> bounds;   // launch ranges of the work order
   int64_t ub_elems = 0;          // largest launch sum of c
   DevBuf uoff;                   // int64 [nG+1] prefix sums of c over the work order
