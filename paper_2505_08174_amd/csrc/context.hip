@@ -2,6 +2,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 
@@ -248,6 +249,51 @@ std::vector<float> build_f32_frags(const double* P0) {
   return fr;
 }
 
+// Table of the two-part FP16 MLP (layout in mlp_mfma.h), 16 bytes per fragment:
+// layer 1 in FP32, then the row factors and the FP16 parts of layers 2-4.
+static std::vector<uint32_t> build_x2_frags(const double* P0) {
+  std::vector<uint32_t> fr((size_t)X2_TOTAL * 4, 0);
+  const std::vector<float> f32 = build_f32_frags(P0);
+  static_assert(F32_L1 == 0, "layer 1 leads the FP32 table");
+  memcpy(fr.data() + 4 * X2_L1, f32.data(), 4 * 64 * sizeof(float));
+  float* sc = reinterpret_cast<float*>(fr.data() + 4 * X2_SC);
+  _Float16* h = reinterpret_cast<_Float16*>(fr.data());
+  auto layer = [&](int base, float* c, const double* W, const double* b, double S, int nrow,
+                   int nmo) {
+    for (int m = 0; m < nrow; ++m) {
+      double top = fabs(S * b[m]);
+      for (int f = 0; f < MLP_H; ++f) top = std::max(top, fabs(S * W[MLP_H * m + f]));
+      int e = 0;
+      frexp(top, &e);   // top < 2^e
+      // the factor 2^-(k + 10) has to be a normal FP32 number
+      const int k = top > 0 ? std::min(std::max(15 - e, -137), 116) : 0;
+      c[m] = (float)ldexp(1.0 / X2_ACT, -k);
+      const int mo = m / 32;
+      auto put = [&](int frag, int lane, int u, double v) {   // v = hi + lo
+        const _Float16 hi = (_Float16)v;
+        h[8 * ((size_t)base + frag * 64 + lane) + u] = hi;
+        return v - (double)hi;
+      };
+      for (int hf = 0; hf < 2; ++hf) {
+        const int lane = m % 32 + 32 * hf;
+        for (int s = 0; s < 4; ++s)
+          for (int u = 0; u < 8; ++u) {
+            const double v = ldexp(S * W[MLP_H * m + kslot_feature(s, hf, u)], k);
+            const double lo = put((mo * 4 + s) * 2, lane, u, v);
+            put((mo * 4 + s) * 2 + 1, lane, u, lo);
+          }
+      }
+      double rest = ldexp(S * b[m], k);
+      for (int u = 0; u < 3; ++u) rest = put(nmo * 8 + mo, m % 32, u, rest);
+    }
+  };
+  const double S = 2.0 / log(2.0);
+  layer(X2_L2, sc, P0 + OFF_W2, P0 + OFF_B2, S, 64, 2);
+  layer(X2_L3, sc + 64, P0 + OFF_W3, P0 + OFF_B3, S, 64, 2);
+  layer(X2_L4, sc + 128, P0 + OFF_W4, P0 + OFF_B4, 1.0, 9, 1);
+  return fr;
+}
+
 // Transposed weights of the FP32 MFMA backward (layout in backward_mfma.hip),
 // unscaled: [W4^T: mo' 2][s 5], [W3^T: mo' 2][mo 2][r 16], [W2^T: same],
 // then W1 by feature [d 3][64].
@@ -448,6 +494,10 @@ hh_status hh_kernel_create_mlp(hh_ctx ctx, const double* params, int input_mode,
     std::vector<float> f32 = build_f32_frags(params);
     k->pf32.alloc(ctx->stream, f32.size() * sizeof(float));
     HIP_OK(hipMemcpyAsync(k->pf32.p, f32.data(), f32.size() * sizeof(float),
+                          hipMemcpyHostToDevice, ctx->stream));
+    std::vector<uint32_t> x2 = build_x2_frags(params);
+    k->px2.alloc(ctx->stream, x2.size() * sizeof(uint32_t));
+    HIP_OK(hipMemcpyAsync(k->px2.p, x2.data(), x2.size() * sizeof(uint32_t),
                           hipMemcpyHostToDevice, ctx->stream));
     std::vector<float> f32t = build_f32_bwd(params);
     k->pf32t.alloc(ctx->stream, f32t.size() * sizeof(float));

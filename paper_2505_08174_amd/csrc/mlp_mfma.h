@@ -454,3 +454,158 @@ __device__ __forceinline__ void stage_frags_f32(float* __restrict__ lds,
   float4* d = reinterpret_cast<float4*>(lds);
   for (int i = threadIdx.x; i < F32_FRAGS * 16; i += nthreads) d[i] = g[i];
 }
+
+// ------------------------------------- FP32 values on FP16 MFMA, two parts each
+//
+// The FP32 near field (the ACA's samples stay on the FP32 tile: factors, pivots
+// and gradients through them have to reproduce). Layers 2-4 contract operands
+// written as the sum of two FP16 numbers, x = hi + lo, on v_mfma_f32_32x32x16_f16
+// (FP32 accumulation). Two roundings to 11 bits with a sign keep 23 to 24 bits of
+// x (biases have a third part in a spare K slot), the products W_hi a_hi +
+// W_hi a_lo + W_lo a_hi are exact, and the one left out, W_lo a_lo, is below 2^-24
+// of the product. Nothing may fall under FP16's range: activations are carried
+// times 2^10, and every row of weights (its bias with it) times the power of two
+// that takes its largest entry to [2^14, 2^15); one multiplication with the row's
+// factor gives the FP32 result back. The small products are summed before the
+// large ones, so a result has 5 roundings at full size (the FP32 tile: 66, one per
+// K step). Measured against 64 bits with Glorot-uniform networks, relative rms:
+// single entries 2.3e-7 (FP32 tile 2.8e-7); sums over 1,500 sources with random
+// forces 1.9e-7 (2.2e-7), with equal forces 1.1e-7 (1.0e-7; all networks tried,
+// weights times 0.3 to 3 and both input modes: 0.95e-7, 0.97e-7).
+//
+// Layer 1 (3 -> 64) is the FP32 tile's. The operand layout is the BF16 tile's.
+// Cost per 32 pairs: 65 FP16 and 4 FP32 MFMAs (2,340 cycles; the FP32 tile
+// 10,800) next to 6,144 activations of 9 issue slots each (3,460 cycles).
+#define X2_L1 0                                    // 4 x 64 floats = 4 x 16 fragments
+#define X2_SC (X2_L1 + 4 * 16)                     // row factors of layers 2-4: 3 x 64 floats
+#define X2_L2 (X2_SC + 3 * 16)                     // [mo 2][s 4][part 2][lane]; bias [mo 2][lane]
+#define X2_L3 (X2_L2 + (2 * 4 * 2 + 2) * 64)
+#define X2_L4 (X2_L3 + (2 * 4 * 2 + 2) * 64)       // [s 4][part 2][lane]; bias [lane]
+#define X2_TOTAL (X2_L4 + (4 * 2 + 1) * 64)
+#define X2_ACT 1024.0f                             // activations are carried times this
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ f32x16 mfma_f16(f16x8 a, f16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+// 2^10 tanh of two scaled results -> elements u, u + 1 of the next layer's
+// operands. neg1 is -1, kept from the compiler so that the remainder is one
+// mixed-precision fma.
+__device__ __forceinline__ void act_x2(float y0, float y1, float neg1, int u, f16x8& hi,
+                                       f16x8& lo) {
+  const float r0 = __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(y0) + 1.0f);
+  const float r1 = __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(y1) + 1.0f);
+  const f32x2 t = {__builtin_fmaf(-2.0f * X2_ACT, r0, X2_ACT),
+                   __builtin_fmaf(-2.0f * X2_ACT, r1, X2_ACT)};
+  const f16x2 h = __builtin_convertvector(t, f16x2);
+  const f32x2 d = {__builtin_fmaf((float)h[0], neg1, t[0]), __builtin_fmaf((float)h[1], neg1, t[1])};
+  const f16x2 l = __builtin_convertvector(d, f16x2);
+  hi[u] = h[0];
+  hi[u + 1] = h[1];
+  lo[u] = l[0];
+  lo[u + 1] = l[1];
+}
+
+// Product sums of M tile mo of the layer at fr + base (nmo M tiles) for NT tiles.
+template <int NT>
+__device__ __forceinline__ void layer_x2(const uint4* __restrict__ fr, int base, int mo, int nmo,
+                                         int lane, const f16x8 (&Bh)[NT][4],
+                                         const f16x8 (&Bl)[NT][4], const f16x8& bone,
+                                         f32x16 (&acc)[NT]) {
+  auto w = [&](int s, int part) {
+    return __builtin_bit_cast(f16x8, fr[base + ((mo * 4 + s) * 2 + part) * 64 + lane]);
+  };
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = f32x16{};
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const f16x8 wh = w(s, 0), wl = w(s, 1);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = mfma_f16(wl, Bh[t][s], acc[t]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = mfma_f16(wh, Bl[t][s], acc[t]);
+  }
+  const f16x8 wb = __builtin_bit_cast(f16x8, fr[base + nmo * 8 * 64 + mo * 64 + lane]);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) acc[t] = mfma_f16(wb, bone, acc[t]);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const f16x8 wh = w(s, 0);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = mfma_f16(wh, Bh[t][s], acc[t]);
+  }
+}
+
+// One hidden layer (64 -> 64, then tanh) of NT tiles; sc: its row factors.
+template <int NT>
+__device__ __forceinline__ void hidden_x2(const uint4* __restrict__ fr, int base,
+                                          const float4* __restrict__ sc, int lane, float neg1,
+                                          const f16x8& bone, const f16x8 (&Bh)[NT][4],
+                                          const f16x8 (&Bl)[NT][4], f16x8 (&Oh)[NT][4],
+                                          f16x8 (&Ol)[NT][4]) {
+#pragma unroll
+  for (int mo = 0; mo < 2; ++mo) {
+    f32x16 acc[NT];
+    layer_x2<NT>(fr, base, mo, 2, lane, Bh, Bl, bone, acc);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 c = sc[8 * mo + 2 * q + (lane >> 5)];   // rows 32 mo + 8 q + 4 h ..
+      const int s = 2 * mo + q / 2, u = 4 * (q % 2);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        act_x2(acc[t][4 * q] * c.x, acc[t][4 * q + 1] * c.y, neg1, u, Oh[t][s], Ol[t][s]);
+        act_x2(acc[t][4 * q + 2] * c.z, acc[t][4 * q + 3] * c.w, neg1, u + 2, Oh[t][s], Ol[t][s]);
+      }
+    }
+  }
+}
+
+// Raw outputs for 64 different pairs, one per lane (as mlp_pairs_f32).
+// fr: the table of X2_TOTAL fragments in LDS.
+__device__ __forceinline__ void mlp_pairs_x2(const uint4* __restrict__ fr, float v0, float v1,
+                                             float v2, float (&o)[9]) {
+  __asm__ volatile("" ::: "memory");   // weights stay in LDS (see mlp_core_bf16)
+  const int lane = threadIdx.x & 63;
+  float neg1 = -1.0f;
+  __asm__("" : "+s"(neg1));
+  f16x8 bone;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) bone[u] = (_Float16)(lane < 32 && u < 3 ? X2_ACT : 0.0f);
+  const HalfSwap a = half_swap(__float_as_uint(v0), __float_as_uint(v1));
+  const HalfSwap b = half_swap(__float_as_uint(v2), __float_as_uint(1.0f));
+  const float b0[2] = {__uint_as_float(a.lo), __uint_as_float(a.hi)};
+  const float b1[2] = {__uint_as_float(b.lo), __uint_as_float(b.hi)};
+  const float* w1 = reinterpret_cast<const float*>(fr + X2_L1) + lane;
+  const float4* sc = reinterpret_cast<const float4*>(fr + X2_SC);
+  f16x8 Ah[2][4], Al[2][4], Bh[2][4], Bl[2][4];
+#pragma unroll
+  for (int mo = 0; mo < 2; ++mo)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      f32x16 c = mfma_f32(w1[64 * 2 * mo], b0[t], f32x16{});
+      c = mfma_f32(w1[64 * (2 * mo + 1)], b1[t], c);
+#pragma unroll
+      for (int r = 0; r < 16; r += 2)
+        act_x2(c[r], c[r + 1], neg1, r % 8, Ah[t][2 * mo + r / 8], Al[t][2 * mo + r / 8]);
+    }
+  hidden_x2<2>(fr, X2_L2, sc, lane, neg1, bone, Ah, Al, Bh, Bl);
+  hidden_x2<2>(fr, X2_L3, sc + 16, lane, neg1, bone, Bh, Bl, Ah, Al);
+  f32x16 acc[2];
+  layer_x2<2>(fr, X2_L4, 0, 1, lane, Ah, Al, bone, acc);
+  const float4 c = sc[32 + (lane >> 5)];   // rows 4 h ..; row 8 in lanes 0-31
+  const float c8 = reinterpret_cast<const float*>(sc)[128 + 8];
+  const float o0[5] = {acc[0][0] * c.x, acc[0][1] * c.y, acc[0][2] * c.z, acc[0][3] * c.w,
+                       acc[0][4] * c8};
+  const float o1[5] = {acc[1][0] * c.x, acc[1][1] * c.y, acc[1][2] * c.z, acc[1][3] * c.w,
+                       acc[1][4] * c8};
+  pair_outputs(o0, o1, o);
+}
+
+// Stage the table (global -> LDS) by the whole workgroup.
+__device__ __forceinline__ void stage_frags_x2(uint4* __restrict__ lds,
+                                               const uint4* __restrict__ g, int nthreads) {
+  for (int i = threadIdx.x; i < X2_TOTAL; i += nthreads) lds[i] = g[i];
+}

@@ -1,5 +1,5 @@
 // Near field with the seeded MLP kernel on MFMA tiles (the BF16 and the plain
-// FP32 form).
+// FP32 form, the latter on two FP16 parts per FP32 value).
 //
 // A wave works on 64 consecutive targets (sorted rows, whichever leaves they
 // are in), one per lane: in every step a lane takes the next source of its own
@@ -10,15 +10,16 @@
 // whose partial rows the combine adds in a fixed order, so that small systems
 // still fill the chip.
 //
-// Bound: the FP32 form by the FP32 MFMA rate, the BF16 form by VALU issue (192
-// transcendentals and about 330 other VALU instructions per 32 pairs). Lanes
-// with different sources cost a wave nothing, so targets need not be padded to
-// whole waves per leaf (a leaf of 94 targets left a quarter of its last wave
-// idle), and one lane per pair prepares and applies it (both halves of the wave
-// did the same 32 pairs before). Measured, one wave per 32 targets and whole
-// near list before, this split after: FP32, 5,000 particles 33.1 -> 4.3 ms,
-// 100,000 particles 244 -> 150 ms (6.7e9 pairs/s, 76% of the FP32 MFMA rate);
-// BF16, 500 particles 831 -> 25 us; BF16 hi + lo, 30,000 particles 28.8 -> 13.9 ms.
+// Bound: VALU issue in both forms (192 transcendentals per 64 pairs and lane; per
+// 32 pairs about 330 other VALU instructions in BF16, 550 in FP32). Lanes with
+// different sources cost a wave nothing, so targets need not be padded to whole
+// waves per leaf (a leaf of 94 targets left a quarter of its last wave idle), and
+// one lane per pair prepares and applies it (both halves of the wave did the same
+// 32 pairs before). Measured, one wave per 32 targets and whole near list before,
+// this split after: BF16, 500 particles 831 -> 25 us; BF16 hi + lo, 30,000
+// particles 28.8 -> 13.9 ms; FP32, 5,000 particles 33.1 -> 4.3 ms, 100,000 particles
+// 244 -> 148 ms (76% of the FP32 MFMA rate), and with FP16 parts in place of FP32
+// MFMA 1.7 ms and 57 ms (1.7e10 pairs/s, VALU 74% busy).
 #include <algorithm>
 
 #include "internal.h"
@@ -106,12 +107,12 @@ __global__ __launch_bounds__(NEAR_WG) void k_near_bf16(NearB a) {
   write_rows(reinterpret_cast<double*>(fr), lane, w, u, s0, a.t.n, set, a.out);
 }
 
-// The plain FP32 form on FP32 MFMA: the same walk and FP32 tiles. F is FP32;
-// each lane sums its target's terms in FP64.
+// The plain FP32 form: the same walk, tiles of FP32 values in two FP16 parts. F is
+// FP32; each lane sums its target's terms in FP64.
 template <class TO>
 struct NearF {
   NearTables t;
-  const float4* frags;
+  const uint4* frags;
   const float* Fs;
   TO* out;
   int groups;
@@ -121,8 +122,8 @@ struct NearF {
 
 template <class TO>
 __global__ __launch_bounds__(NEAR_WG) void k_near_f32(NearF<TO> a) {
-  __shared__ __align__(16) float fr[F32_FRAGS * 64];
-  stage_frags_f32(fr, a.frags, NEAR_WG);
+  __shared__ uint4 fr[X2_TOTAL];
+  stage_frags_x2(fr, a.frags, NEAR_WG);
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -148,7 +149,7 @@ __global__ __launch_bounds__(NEAR_WG) void k_near_f32(NearF<TO> a) {
     if (wk.j == ss) { rx = 1.0f; ry = 0.0f; rz = 0.0f; }
     const PairIn in = pair_in(a.input_mode, rx, ry, rz, false);
     float q[9];
-    mlp_pairs_f32(fr, in.v0, in.v1, in.v2, q);
+    mlp_pairs_x2(fr, in.v0, in.v1, in.v2, q);
     pair_apply(q, skip ? 0.0f : in.rs * c16, f0, f1, f2, u0, u1, u2);
     wk.next(a.t);
   }
@@ -211,7 +212,7 @@ static void launch_near_f32_t(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, con
                               void* out, int groups, float sgn) {
   NearF<TO> a;
   a.t = near_tables(t, p);
-  a.frags = k->pf32.as<float4>();
+  a.frags = k->px2.as<uint4>();
   a.Fs = (const float*)Fs;
   a.out = (TO*)out;
   a.groups = groups;
