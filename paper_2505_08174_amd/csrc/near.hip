@@ -158,7 +158,7 @@ void launch_near_t(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs
 // first source and its partial row than it fills.
 int near_groups(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, int prec) {
   return k->kind == KIND_MLP && prec != HH_FP64 ? near_groups_mfma(ctx, t, p)
-                                                : near_sets(ctx, t, p, 4, 64, 16);
+                                                : near_sets(ctx, t, p, 4, 32, 16);
 }
 
 // Near field with the displacement reversed: sum_j K(x_j - x_i) v_j, which is

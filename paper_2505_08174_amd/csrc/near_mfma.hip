@@ -17,9 +17,9 @@
 // one lane per pair prepares and applies it (both halves of the wave did the same
 // 32 pairs before). Measured, one wave per 32 targets and whole near list before,
 // this split after: BF16, 500 particles 831 -> 25 us; BF16 hi + lo, 30,000
-// particles 28.8 -> 13.9 ms; FP32, 5,000 particles 33.1 -> 4.3 ms, 100,000 particles
-// 244 -> 148 ms (76% of the FP32 MFMA rate), and with FP16 parts in place of FP32
-// MFMA 1.7 ms and 57 ms (1.7e10 pairs/s, VALU 74% busy).
+// particles 28.8 -> 12.5 ms; FP32, 5,000 particles 33.1 -> 4.3 ms, 100,000
+// particles 244 -> 148 ms (76% of the FP32 MFMA rate), and with FP16 parts in
+// place of FP32 MFMA 1.5 ms and 55 ms (1.8e10 pairs/s, VALU 77% busy).
 #include <algorithm>
 
 #include "internal.h"
@@ -180,13 +180,12 @@ void ensure_units(hh_ctx ctx, hh_tree t) {
   t->n_units = nu;
 }
 
-// Three rounds of resident workgroups (3 per compute unit) even out the leaves'
-// different near lists, as long as a share keeps 64 sources (a workgroup stages
-// 48 KB of weights first); below that, shares down to 4 sources as long as they
-// fill idle compute units: at 500 particles, 32 sets of 4-source shares take
-// 25 us, one set 160 us.
+// A share of 32 sources takes some 100 us, staging a workgroup's 48 KB of weights
+// about 2. Below that, shares down to 4 sources as long as they fill idle compute
+// units: at 500 particles, 32 sets of 4-source shares take 25 us, one set 160 us (a
+// product 27.1 us; with shares of 2 sources 31.4, of 1 source 28.8).
 int near_groups_mfma(hh_ctx ctx, hh_tree t, hh_part p) {
-  return near_sets(ctx, t, p, 3, 64, 4);
+  return near_sets(ctx, t, p, 3, 32, 4);
 }
 
 void launch_near_bf16(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs, void* out,

@@ -90,14 +90,18 @@ __device__ __forceinline__ void write_rows(double* __restrict__ red, int lane, i
           (TO)(((red[e] + red[64 * N + e]) + red[128 * N + e]) + red[192 * N + e]);
 }
 
-// Sets of partial rows: workgroups per 64 targets. Three rounds of resident
-// workgroups (`res` per compute unit) as long as a share keeps `keep` sources,
-// and shares down to `least` sources while they fill idle compute units.
+// Sets of partial rows: workgroups per 64 targets. Twelve rounds of resident
+// workgroups (`res` per compute unit) as long as a wave's share keeps `keep`
+// sources (near lists differ by up to 2.5 times their mean, and with three rounds
+// the last one ran half empty: near field of 21,504 beads 10.1 -> 8.9 ms, of
+// 250,000 particles 102.6 -> 96.8 ms, of 60,000 with the RPY kernel 1.26 -> 1.10 ms;
+// 6 and 24 rounds are within 3% of 12), and shares down to `least` sources while
+// they fill idle compute units.
 inline int near_sets(hh_ctx ctx, hh_tree t, hh_part p, int res, int keep, int least) {
   const int64_t nw = (t->n + 63) / 64;
   const int64_t q = std::max<int64_t>(1, p->near_pairs / t->n);   // sources per target
   const int64_t r = (int64_t)res * ctx->n_cu;
-  const int64_t even = std::min((3 * r + nw - 1) / nw, q / (4 * keep));
+  const int64_t even = std::min((12 * r + nw - 1) / nw, q / (4 * keep));
   const int64_t fill = std::min((r + nw - 1) / nw, q / (4 * least));
   return (int)std::max<int64_t>(1, std::max(even, fill));
 }
