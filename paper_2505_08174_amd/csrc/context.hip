@@ -3,6 +3,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <new>
 
@@ -249,6 +250,25 @@ std::vector<float> build_f32_frags(const double* P0) {
   return fr;
 }
 
+// Nearest FP16 number of |v| < 65520 as bits (ties to even), and its value in hi.
+static uint16_t f16_rne(double v, double& hi) {
+  const double a = fabs(v);
+  const uint16_t sign = std::signbit(v) ? 0x8000 : 0;
+  if (a < 0x1p-14) {   // subnormal: multiples of 2^-24
+    const double q = nearbyint(a * 0x1p24);
+    hi = copysign(q * 0x1p-24, v);
+    return (uint16_t)(sign | (uint16_t)q);   // 2^10 is the first normal number
+  }
+  uint64_t u;
+  memcpy(&u, &a, 8);
+  u += ((1ull << 41) - 1) + ((u >> 42) & 1);
+  u &= ~((1ull << 42) - 1);
+  double r;
+  memcpy(&r, &u, 8);
+  hi = copysign(r, v);
+  return (uint16_t)(sign | (uint16_t)((u >> 42) - ((uint64_t)(1023 - 15) << 10)));
+}
+
 // Table of the two-part FP16 MLP (layout in mlp_mfma.h), 16 bytes per fragment:
 // layer 1 in FP32, then the row factors and the FP16 parts of layers 2-4.
 static std::vector<uint32_t> build_x2_frags(const double* P0) {
@@ -257,33 +277,36 @@ static std::vector<uint32_t> build_x2_frags(const double* P0) {
   static_assert(F32_L1 == 0, "layer 1 leads the FP32 table");
   memcpy(fr.data() + 4 * X2_L1, f32.data(), 4 * 64 * sizeof(float));
   float* sc = reinterpret_cast<float*>(fr.data() + 4 * X2_SC);
-  _Float16* h = reinterpret_cast<_Float16*>(fr.data());
+  uint16_t* h = reinterpret_cast<uint16_t*>(fr.data());
   auto layer = [&](int base, float* c, const double* W, const double* b, double S, int nrow,
                    int nmo) {
     for (int m = 0; m < nrow; ++m) {
       double top = fabs(S * b[m]);
       for (int f = 0; f < MLP_H; ++f) top = std::max(top, fabs(S * W[MLP_H * m + f]));
-      int e = 0;
-      frexp(top, &e);   // top < 2^e
-      // the factor 2^-(k + 10) has to be a normal FP32 number
+      int e = 1024;
+      if (std::isfinite(top)) frexp(top, &e);   // top < 2^e
+      // The factor 2^-(k + 10) has to be a normal FP32 number; rows above 2^152 (past
+      // FP32 by themselves) are cut off at FP16's largest value.
       const int k = top > 0 ? std::min(std::max(15 - e, -137), 116) : 0;
+      const double up = ldexp(S, k), cap = 65504.0;
+      auto scaled = [&](double v) { return std::min(std::max(up * v, -cap), cap); };
       c[m] = (float)ldexp(1.0 / X2_ACT, -k);
       const int mo = m / 32;
       auto put = [&](int frag, int lane, int u, double v) {   // v = hi + lo
-        const _Float16 hi = (_Float16)v;
-        h[8 * ((size_t)base + frag * 64 + lane) + u] = hi;
-        return v - (double)hi;
+        double hi;
+        h[8 * ((size_t)base + frag * 64 + lane) + u] = f16_rne(v, hi);
+        return v - hi;
       };
       for (int hf = 0; hf < 2; ++hf) {
         const int lane = m % 32 + 32 * hf;
         for (int s = 0; s < 4; ++s)
           for (int u = 0; u < 8; ++u) {
-            const double v = ldexp(S * W[MLP_H * m + kslot_feature(s, hf, u)], k);
+            const double v = scaled(W[MLP_H * m + kslot_feature(s, hf, u)]);
             const double lo = put((mo * 4 + s) * 2, lane, u, v);
             put((mo * 4 + s) * 2 + 1, lane, u, lo);
           }
       }
-      double rest = ldexp(S * b[m], k);
+      double rest = scaled(b[m]);
       for (int u = 0; u < 3; ++u) rest = put(nmo * 8 + mo, m % 32, u, rest);
     }
   };
