@@ -91,6 +91,9 @@ typedef enum { HH_MLP_INPUT_DIRECTION = 0, HH_MLP_INPUT_DISPLACEMENT = 1 } hh_ml
  * stream (default priority, non-blocking) and two events: the ACA runs its
  * workgroup-team kernel there, forked from `stream` and joined back before
  * any later work on `stream`, so callers only ever order against `stream`.
+ * Device memory that handles free is kept per device by size class for later
+ * calls (at most 0.4 of the device's memory) until the last context on the
+ * device is destroyed or an allocation of this library would fail otherwise.
  * Released by hh_ctx_destroy. */
 hh_status hh_ctx_create(int device, void* stream, hh_ctx* out);
 void hh_ctx_destroy(hh_ctx ctx);
@@ -258,8 +261,9 @@ hh_status hh_matvec(hh_ctx ctx, hh_tree tree, hh_part part, hh_lowrank lr, hh_ke
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * product of hh_matvec (same kernels, same result bit for bit) with its
- * workspaces -- the sorted forces and the near-field rows, 3 n values each --
- * in a file-scope device array of HH_NOALLOC_SCRATCH_BYTES instead of device
+ * workspaces -- the sorted forces, 3 n values, and the sets of near-field and
+ * far-field rows, 3 n values each (several sets up to some 600,000 rows, for
+ * which there is always room) -- in a file-scope device array of HH_NOALLOC_SCRATCH_BYTES instead of device
  * memory kept in lr; it calls no allocating routine and records no phase
  * events. Stored factors only (a streamed-mode lr -> HH_ERR_INVALID_ARG). A
  * product that needs more scratch than HH_NOALLOC_SCRATCH_BYTES (about 1.4M
