@@ -17,6 +17,7 @@
 #include "api_guard.h"
 #include "devmath.h"
 #include "internal.h"
+#include "wave.h"
 
 void block_sizes(hh_ctx ctx, hh_tree t, hh_part p, std::vector<int32_t>& cs,
                  std::vector<int32_t>& qs);
@@ -277,6 +278,13 @@ __global__ __launch_bounds__(TB) void k_near_vjp(const int4* __restrict__ nodes,
 // the blocks [b0, b1). Writes the cotangents of the sampled columns and rows
 // of block b into the cotangent pool at goff[b] (term k: 9 (c + q) values,
 // column then row), and adds Q^T (C^T w) to dFs.
+//
+// Bound by the latency of the loads of each step's earlier terms (k of them, 27
+// values per row each). A row stays with one lane, whose next term's values are in
+// flight while the present one's are used; the terms' sums over the rows are read
+// by no one before the step ends, so the waves leave them in LDS and meet once per
+// step, not three times per term. FP32, 2,000 particles 1.75 -> 0.34 ms, 16,000
+// 15.1 -> 6.0 ms.
 template <class T>
 __global__ __launch_bounds__(TB) void k_aca_adjoint(
     const int2* __restrict__ G, int64_t b0, int64_t b1, const int4* __restrict__ nodes,
@@ -285,22 +293,27 @@ __global__ __launch_bounds__(TB) void k_aca_adjoint(
     const int64_t* __restrict__ goff, const T* __restrict__ pool, T* __restrict__ gpool,
     const T* __restrict__ Fs, const T* __restrict__ ws, double* __restrict__ dFs) {
   __shared__ double s_t[LMAX_CAP][3], s_tb[LMAX_CAP][3];
-  __shared__ double red[TB / 64][9];
-  __shared__ double s_M[9];
+  __shared__ double red[LMAX_CAP][TB / 64][9];   // the waves' sums, one row per term
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  // block-wide sum of 9 doubles, result in s_M (all threads may read after)
-  auto reduce9 = [&](double (&v)[9]) {
-    for (int e = 0; e < 9; ++e) v[e] = wave_sum(v[e]);
-    __syncthreads();
-    if (lane == 0)
-      for (int e = 0; e < 9; ++e) red[wv][e] = v[e];
-    __syncthreads();
-    if (threadIdx.x < 9) {
-      double a = 0;
-      for (int w = 0; w < TB / 64; ++w) a += red[w][threadIdx.x];
-      s_M[threadIdx.x] = a;
+  // this wave's sums of nine values as row m of red (or added to it)
+  auto put9 = [&](int m, const double (&v)[9], bool add) {
+    const WaveSums<9> w = wave_sums(v);
+    if ((lane & 15) == 15) {
+      const int row = lane >> 4, e0 = ((row & 1) << 1) | (row >> 1);   // sum_row inverted
+      double* r = red[m][wv];
+      r[e0] = add ? r[e0] + w.r[0] : w.r[0];
+      r[4 + e0] = add ? r[4 + e0] + w.r[1] : w.r[1];
+      if (row == 0) r[8] = add ? r[8] + w.r[2] : w.r[2];
     }
-    __syncthreads();
+  };
+  auto total = [&](int m, int e) {
+    double t = 0;
+#pragma unroll
+    for (int w = 0; w < TB / 64; ++w) t += red[m][w][e];
+    return t;
+  };
+  auto zero = [&](int k) {   // a wave without rows
+    for (int t = lane; t < 9 * k; t += 64) red[t / 9][wv][t % 9] = 0.0;
   };
   for (int64_t b = b0 + blockIdx.x; b < b1; b += gridDim.x) {
     if (flag[b] || rank[b] == 0) continue;
@@ -328,11 +341,12 @@ __global__ __launch_bounds__(TB) void k_aca_adjoint(
         for (int a = 0; a < 3; ++a)
           v[3 + a] += (double)e[a] * w[0] + (double)e[3 + a] * w[1] + (double)e[6 + a] * w[2];
       }
-      reduce9(v);
-      if (threadIdx.x < 3) {
-        s_t[k][threadIdx.x] = s_M[threadIdx.x];
-        s_tb[k][threadIdx.x] = s_M[3 + threadIdx.x];
-      }
+      put9(k, v, false);
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < 6 * l; t += TB) {
+      const int k = t / 6, e = t % 6;
+      (e < 3 ? s_t[k][e] : s_tb[k][e - 3]) = total(k, e);
     }
     __syncthreads();
     // initial cotangents and dF_sigma += sum_k q_k(j)^T tb_k
@@ -360,28 +374,41 @@ __global__ __launch_bounds__(TB) void k_aca_adjoint(
       const int ik = pi[k], jk = pj[k];
       // q_k = G(i_k, :) - sum_{m<k} c_m(i_k) q_m: the row cotangent stays in
       // place; c_m(i_k) -= sum_j qb_k(j) q_m(j)^T, qb_m(j) -= c_m(i_k)^T qb_k(j)
-      for (int m = 0; m < k; ++m) {
-        double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (int j = threadIdx.x; j < q; j += TB) {
-          const T* x = Qb(k) + 9 * (int64_t)j;
-          const T* y = Qp(m) + 9 * (int64_t)j;
-          for (int a = 0; a < 3; ++a)
-            for (int cc = 0; cc < 3; ++cc)
-              v[3 * a + cc] += (double)x[3 * a] * y[3 * cc] + (double)x[3 * a + 1] * y[3 * cc + 1] +
-                               (double)x[3 * a + 2] * y[3 * cc + 2];
+      // (nothing in the loop over m reads the sums: they wait in red)
+      if (64 * wv >= q) zero(k);
+      for (int j0 = 64 * wv; j0 < q; j0 += TB) {
+        const bool act = j0 + lane < q;
+        const int64_t j9 = 9 * (int64_t)(act ? j0 + lane : q - 1);
+        T x[9], y[9], z[9];
+        for (int e = 0; e < 9; ++e) x[e] = act ? Qb(k)[j9 + e] : (T)0;
+        if (k > 0) {
+          for (int e = 0; e < 9; ++e) y[e] = Qp(0)[j9 + e];
+          for (int e = 0; e < 9; ++e) z[e] = Qb(0)[j9 + e];
         }
-        reduce9(v);
-        if (threadIdx.x < 9) Cb(m)[9 * (int64_t)ik + threadIdx.x] -= (T)s_M[threadIdx.x];
-        const T* cm = Cp(m) + 9 * (int64_t)ik;
-        for (int j = threadIdx.x; j < q; j += TB) {
-          const T* x = Qb(k) + 9 * (int64_t)j;
-          T* y = Qb(m) + 9 * (int64_t)j;
+#pragma unroll 1
+        for (int m = 0; m < k; ++m) {
+          T y1[9], z1[9];   // the next term's rows, in flight during this one
+          const int mn = min(m + 1, k - 1);
+          for (int e = 0; e < 9; ++e) y1[e] = Qp(mn)[j9 + e];
+          for (int e = 0; e < 9; ++e) z1[e] = Qb(mn)[j9 + e];
+          const T* cm = Cp(m) + 9 * (int64_t)ik;
+          double v[9];
           for (int a = 0; a < 3; ++a)
-            for (int cc = 0; cc < 3; ++cc)
-              y[3 * a + cc] -= cm[a] * x[cc] + cm[3 + a] * x[3 + cc] + cm[6 + a] * x[6 + cc];
+            for (int cc = 0; cc < 3; ++cc) {
+              v[3 * a + cc] = (double)x[3 * a] * y[3 * cc] + (double)x[3 * a + 1] * y[3 * cc + 1] +
+                              (double)x[3 * a + 2] * y[3 * cc + 2];
+              z[3 * a + cc] -= cm[a] * x[cc] + cm[3 + a] * x[3 + cc] + cm[6 + a] * x[6 + cc];
+            }
+          if (act)
+            for (int e = 0; e < 9; ++e) Qb(m)[j9 + e] = z[e];
+          put9(m, v, j0 >= TB);
+          for (int e = 0; e < 9; ++e) { y[e] = y1[e]; z[e] = z1[e]; }
         }
-        __syncthreads();
       }
+      __syncthreads();
+      for (int t = threadIdx.x; t < 9 * k; t += TB)
+        Cb(t / 9)[9 * (int64_t)ik + t % 9] -= (T)total(t / 9, t % 9);
+      __syncthreads();
       // c_k = a_k P^-1, P = q_k(j_k), a_k(i) = c_k(i) P:
       //   ab(i) = cb_k(i) P^-T, ab(i_k) -= P^-T S P^-T, S = sum_i a_k(i)^T cb_k(i)
       double Pm[9], Pi[9];
@@ -415,10 +442,11 @@ __global__ __launch_bounds__(TB) void k_aca_adjoint(
             for (int bb = 0; bb < 3; ++bb)
               v[3 * a + bb] += A[a] * cb[bb] + A[3 + a] * cb[3 + bb] + A[6 + a] * cb[6 + bb];
         }
-        reduce9(v);
+        put9(0, v, false);
       }
+      __syncthreads();
       double Sm[9];
-      for (int e = 0; e < 9; ++e) Sm[e] = s_M[e];
+      for (int e = 0; e < 9; ++e) Sm[e] = total(0, e);
       __syncthreads();
       // corr = P^-T S P^-T
       double T1[9], corr[9];
@@ -439,28 +467,43 @@ __global__ __launch_bounds__(TB) void k_aca_adjoint(
           for (int e = 0; e < 9; ++e) o[e] -= corr[e];
         for (int e = 0; e < 9; ++e) cb[e] = (T)o[e];   // column cotangent of step k
       }
-      __syncthreads();
       // a_k = G(:, j_k) - sum_{m<k} c_m q_m(j_k):
       //   cb_m(i) -= ab(i) q_m(j_k)^T,  qb_m(j_k) -= sum_i c_m(i)^T ab(i)
-      for (int m = 0; m < k; ++m) {
-        const T* qm = Qp(m) + 9 * (int64_t)jk;
-        double v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (int i = threadIdx.x; i < c; i += TB) {
-          const T* ab = Cb(k) + 9 * (int64_t)i;
-          const T* cm = Cp(m) + 9 * (int64_t)i;
-          T* cbm = Cb(m) + 9 * (int64_t)i;
+      if (64 * wv >= c) zero(k);
+      for (int i0 = 64 * wv; i0 < c; i0 += TB) {
+        const bool act = i0 + lane < c;
+        const int64_t i9 = 9 * (int64_t)(act ? i0 + lane : c - 1);
+        T ab[9], y[9], z[9];
+        for (int e = 0; e < 9; ++e) ab[e] = act ? Cb(k)[i9 + e] : (T)0;
+        if (k > 0) {
+          for (int e = 0; e < 9; ++e) y[e] = Cp(0)[i9 + e];
+          for (int e = 0; e < 9; ++e) z[e] = Cb(0)[i9 + e];
+        }
+#pragma unroll 1
+        for (int m = 0; m < k; ++m) {
+          T y1[9], z1[9];
+          const int mn = min(m + 1, k - 1);
+          for (int e = 0; e < 9; ++e) y1[e] = Cp(mn)[i9 + e];
+          for (int e = 0; e < 9; ++e) z1[e] = Cb(mn)[i9 + e];
+          const T* qm = Qp(m) + 9 * (int64_t)jk;
+          double v[9];
           for (int a = 0; a < 3; ++a)
             for (int bb = 0; bb < 3; ++bb) {
-              cbm[3 * a + bb] -= ab[3 * a] * qm[3 * bb] + ab[3 * a + 1] * qm[3 * bb + 1] +
-                                 ab[3 * a + 2] * qm[3 * bb + 2];
-              v[3 * a + bb] += (double)cm[a] * ab[bb] + (double)cm[3 + a] * ab[3 + bb] +
-                               (double)cm[6 + a] * ab[6 + bb];
+              z[3 * a + bb] -= ab[3 * a] * qm[3 * bb] + ab[3 * a + 1] * qm[3 * bb + 1] +
+                               ab[3 * a + 2] * qm[3 * bb + 2];
+              v[3 * a + bb] = (double)y[a] * ab[bb] + (double)y[3 + a] * ab[3 + bb] +
+                              (double)y[6 + a] * ab[6 + bb];
             }
+          if (act)
+            for (int e = 0; e < 9; ++e) Cb(m)[i9 + e] = z[e];
+          put9(m, v, i0 >= TB);
+          for (int e = 0; e < 9; ++e) { y[e] = y1[e]; z[e] = z1[e]; }
         }
-        reduce9(v);
-        if (threadIdx.x < 9) Qb(m)[9 * (int64_t)jk + threadIdx.x] -= (T)s_M[threadIdx.x];
-        __syncthreads();
       }
+      __syncthreads();
+      for (int t = threadIdx.x; t < 9 * k; t += TB)
+        Qb(t / 9)[9 * (int64_t)jk + t % 9] -= (T)total(t / 9, t % 9);
+      __syncthreads();
     }
     __syncthreads();
   }
