@@ -42,8 +42,9 @@ MLP_TANH = 3 * 64                                  # activations per kernel quer
 TANH_PER_CLK_CU = 16
 CU, CLK = 256, 2.4e9
 # sources whose change invalidates the stored HBM traffic of a kernel
-KERNEL_SOURCES = {"k_aca": ["aca.hip", "mlp_mfma.h", "devmath.h", "internal.h"],
-                  "k_near": ["near_mfma.hip", "near.hip", "mlp_mfma.h", "devmath.h", "internal.h"],
+KERNEL_SOURCES = {"k_aca": ["aca.hip", "wave.h", "mlp_mfma.h", "devmath.h", "internal.h"],
+                  "k_near": ["near_mfma.hip", "near.hip", "near_walk.h", "mlp_mfma.h", "devmath.h",
+                             "internal.h"],
                   "far": ["apply.hip", "internal.h"]}
 
 
