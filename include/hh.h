@@ -92,7 +92,8 @@ typedef enum { HH_MLP_INPUT_DIRECTION = 0, HH_MLP_INPUT_DISPLACEMENT = 1 } hh_ml
  * workgroup-team kernel there, forked from `stream` and joined back before
  * any later work on `stream`, so callers only ever order against `stream`.
  * Device memory that handles free is kept per device by size class for later
- * calls (at most 0.4 of the device's memory) until the last context on the
+ * calls (at most 0.4 of the device's memory, or a larger budget set by
+ * hh_ctx_set_budget up to 0.75 of it) until the last context on the
  * device is destroyed or an allocation of this library would fail otherwise.
  * Released by hh_ctx_destroy. */
 hh_status hh_ctx_create(int device, void* stream, hh_ctx* out);

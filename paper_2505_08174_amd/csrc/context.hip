@@ -416,6 +416,7 @@ hh_status hh_ctx_set_budget(hh_ctx ctx, size_t bytes) {
   HH_API_BEGIN(ctx)
   HH_REQUIRE(bytes >= 4096, HH_ERR_INVALID_ARG, "budget must be at least 4096 bytes");
   ctx->budget_bytes = bytes;
+  devmem_grant(ctx->device, bytes);
   HH_API_END(ctx)
 }
 

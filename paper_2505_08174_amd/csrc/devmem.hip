@@ -12,7 +12,10 @@
 // A block is reused only on the stream it was freed on (stream order then
 // keeps its earlier readers ahead of its next writers), or on any stream once
 // that stream has been waited for. The lists of a device hold at most
-// KEEP_SHARE of its memory (the largest blocks go first), and everything is
+// KEEP_SHARE of its memory, or the largest budget a caller granted a context up to
+// KEEP_MOST of it (the largest blocks go first: with KEEP_SHARE alone, a budget of
+// 280 GB and a factor pool above 115 GB, the pool was mapped anew in every other
+// step, 3.9 s of a 4.2 s training step at 200,000 particles), and everything is
 // returned when the last context on the device is destroyed or when an
 // allocation fails. One lock per process: contexts may live in any thread.
 #include <algorithm>
@@ -25,7 +28,7 @@
 namespace {
 
 constexpr int MAX_DEVICES = 64;
-constexpr double KEEP_SHARE = 0.4;
+constexpr double KEEP_SHARE = 0.4, KEEP_MOST = 0.75;
 
 struct Block {
   void* p;
@@ -35,7 +38,7 @@ struct Block {
 
 struct DeviceBlocks {
   std::map<size_t, std::vector<Block>> free;
-  size_t kept = 0, limit = 0;
+  size_t kept = 0, limit = 0, most = 0;
   int contexts = 0;
 };
 
@@ -132,9 +135,16 @@ size_t devmem_attach(int dev) {
   size_t fr = 0, tot = 0;
   HIP_OK(hipMemGetInfo(&fr, &tot));
   if (!d) return fr;
-  d->limit = (size_t)(KEEP_SHARE * (double)tot);
+  if (d->contexts == 0) d->limit = (size_t)(KEEP_SHARE * (double)tot);
+  d->most = (size_t)(KEEP_MOST * (double)tot);
   d->contexts += 1;
   return fr + d->kept;
+}
+
+void devmem_grant(int dev, size_t bytes) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  DeviceBlocks* d = device_blocks(dev);
+  if (d) d->limit = std::max(d->limit, std::min(bytes, d->most));
 }
 
 void devmem_detach(int dev, hipStream_t stream, bool whole_device) {

@@ -55,8 +55,10 @@ struct DevBuf {
 
 // A context on device `dev` exists (returns its free memory, the kept blocks
 // counted as free) or is gone, after a wait for `stream`, or with whole_device
-// for every stream of the device.
+// for every stream of the device. devmem_grant: a caller's budget, which the kept
+// blocks may fill.
 size_t devmem_attach(int dev);
+void devmem_grant(int dev, size_t bytes);
 void devmem_detach(int dev, hipStream_t stream, bool whole_device);
 
 struct PhaseRec {
