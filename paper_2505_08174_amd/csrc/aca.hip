@@ -1032,7 +1032,7 @@ void launch_aca_t(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr,
   // per worker: Gram history A (l_max (l_max + 1) / 2 3x3 matrices)
   const int64_t stride = 9 * ((int64_t)lr->l_max * (lr->l_max + 1) / 2);
   if (lr->gram_workers < workers || lr->gram_stride != stride) {
-    lr->gram.alloc(ctx->stream, std::max<int64_t>(1, workers * stride) * sizeof(double));
+    lr->gram.alloc(ctx, std::max<int64_t>(1, workers * stride) * sizeof(double));
     lr->gram_workers = workers;
     lr->gram_stride = stride;
   }
@@ -1046,7 +1046,7 @@ void launch_aca_t(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr,
     // streamed mode: a factor arena per wave; huge blocks go to the first
     // workgroups of the team grid, in tiers of arenas sized per size class
     if (lr->arena_workers < workers) {
-      lr->arena.alloc(ctx->stream, workers * lr->arena_elems * sizeof(T));
+      lr->arena.alloc(ctx, workers * lr->arena_elems * sizeof(T));
       lr->arena_workers = workers;
     }
     a.arena = lr->arena.as<T>();
@@ -1098,7 +1098,7 @@ void launch_aca_t(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr,
       HH_REQUIRE(wgs <= grid_t, HH_ERR_CAPACITY, "more huge tiers than team workgroups");
       HH_REQUIRE(b == nhuge, HH_ERR_CAPACITY, "huge tiers do not cover the huge blocks");
       if (lr->huge_elems < off) {
-        lr->huge.alloc(ctx->stream, off * sizeof(T));
+        lr->huge.alloc(ctx, off * sizeof(T));
         lr->huge_elems = off;
       }
       a.huge = lr->huge.as<T>();
@@ -1225,7 +1225,7 @@ static void append_desc(const std::vector<int32_t>& cs, const std::vector<int32_
 }
 
 static void upload_i32(hh_ctx ctx, DevBuf& d, const std::vector<int32_t>& v) {
-  d.alloc(ctx->stream, std::max<size_t>(v.size(), 1) * sizeof(int32_t));
+  d.alloc(ctx, std::max<size_t>(v.size(), 1) * sizeof(int32_t));
   if (!v.empty())
     HIP_OK(hipMemcpyAsync(d.p, v.data(), v.size() * sizeof(int32_t), hipMemcpyHostToDevice,
                           ctx->stream));
@@ -1245,11 +1245,11 @@ static void upload_i32(hh_ctx ctx, DevBuf& d, const std::vector<int32_t>& v) {
 void plan_aca(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, int force_streamed) {
   hipStream_t st = ctx->stream;
   int64_t nG = p->nG;
-  lr->rank.alloc(st, std::max<int64_t>(1, nG) * sizeof(int32_t));
-  lr->flag.alloc(st, std::max<int64_t>(1, nG) * sizeof(int32_t));
-  lr->piv.alloc(st, std::max<int64_t>(1, nG) * 2 * LMAX_CAP * sizeof(int32_t));
-  lr->fptr.alloc(st, std::max<int64_t>(1, nG) * LMAX_CAP * sizeof(int64_t));
-  lr->toff.alloc(st, (std::max<int64_t>(1, nG) + 1) * sizeof(int64_t));
+  lr->rank.alloc(ctx, std::max<int64_t>(1, nG) * sizeof(int32_t));
+  lr->flag.alloc(ctx, std::max<int64_t>(1, nG) * sizeof(int32_t));
+  lr->piv.alloc(ctx, std::max<int64_t>(1, nG) * 2 * LMAX_CAP * sizeof(int32_t));
+  lr->fptr.alloc(ctx, std::max<int64_t>(1, nG) * LMAX_CAP * sizeof(int64_t));
+  lr->toff.alloc(ctx, (std::max<int64_t>(1, nG) + 1) * sizeof(int64_t));
   std::vector<int32_t> cs, qs;
   block_sizes(ctx, t, p, cs, qs);
   const size_t es = lr->prec == HH_FP64 ? 8 : 4;
@@ -1377,7 +1377,7 @@ void plan_aca(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, int force_streame
   upload_i32(ctx, lr->order, ord);
   upload_i32(ctx, lr->lid, lid);
   upload_i32(ctx, lr->pos, pos);
-  lr->uoff.alloc(st, uoff.size() * sizeof(int64_t));
+  lr->uoff.alloc(ctx, uoff.size() * sizeof(int64_t));
   HIP_OK(hipMemcpyAsync(lr->uoff.p, uoff.data(), uoff.size() * sizeof(int64_t),
                         hipMemcpyHostToDevice, st));
   ctx_sync(ctx);
@@ -1394,7 +1394,7 @@ void run_aca_stored(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr
   int64_t* top = (int64_t*)ctx->scratch_flag.p + 4;
   for (int attempt = 0; attempt < 6; ++attempt) {
     lr->pool_elems = std::max<int64_t>(want, 1024);
-    lr->pool.alloc(st, lr->pool_elems * es);
+    lr->pool.alloc(ctx, lr->pool_elems * es);
     HIP_OK(hipMemsetAsync(ctx->scratch_flag.p, 0, 8 * sizeof(int64_t), st));
     if (nG > 0) {
       PhaseTimer timer(ctx, HH_PHASE_ACA);
@@ -1420,7 +1420,7 @@ void run_aca_stored(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr
     want = std::max<int64_t>(2 * want, used + used / 4);
   }
   lowrank_stats(ctx, t, p, lr, true);
-  lr->tbuf.alloc(st, std::max<int64_t>(1, lr->rank_sum) * 3 * sizeof(double));
+  lr->tbuf.alloc(ctx, std::max<int64_t>(1, lr->rank_sum) * 3 * sizeof(double));
 }
 
 // Streamed mode, launch i: ACA with the apply fused in; per-block rows go to

@@ -376,8 +376,8 @@ template <class T, class TO>
 void matvec_ws_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, const void* F,
                  void* U) {
   const RowSets r = row_sets(ctx, t, p, k, lr->prec);
-  lr->ws_f.ensure(ctx->stream, 3 * t->n * sizeof(T));
-  lr->ws_near.ensure(ctx->stream, set_bytes(t, k, lr->prec, r));
+  lr->ws_f.ensure(ctx, 3 * t->n * sizeof(T));
+  lr->ws_near.ensure(ctx, set_bytes(t, k, lr->prec, r));
   matvec_t<T, TO>(ctx, t, p, lr, k, F, U, lr->ws_f.p, lr->ws_near.p, r, true);
 }
 
@@ -409,10 +409,10 @@ void matvec_streamed_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kerne
   DevBuf& Un = lr->ws_near;
   DevBuf& Uf = lr->ws_far;
   DevBuf& counters = lr->ws_cnt;
-  Fs.ensure(st, 3 * n * sizeof(T));
+  Fs.ensure(ctx, 3 * n * sizeof(T));
   const int groups = near_groups(ctx, t, p, k, lr->prec);
-  Un.ensure(st, near_bytes(t, k, lr->prec, groups));
-  Uf.ensure(st, 3 * n * sizeof(double));
+  Un.ensure(ctx, near_bytes(t, k, lr->prec, groups));
+  Uf.ensure(ctx, 3 * n * sizeof(double));
   hipLaunchKernelGGL((k_gather_rows<T, T>), dim3(nblk(n)), dim3(T256), 0, st, (const T*)F,
                      t->perm.as<int32_t>(), n, Fs.as<T>());
   {
@@ -421,10 +421,10 @@ void matvec_streamed_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kerne
   }
   zero_words(ctx, Uf.p, 3 * n);
   const size_t nb = lr->bounds.size() - 1;
-  counters.ensure(st, ACA_COUNTERS * nb * sizeof(int64_t));
+  counters.ensure(ctx, ACA_COUNTERS * nb * sizeof(int64_t));
   zero_words(ctx, counters.p, ACA_COUNTERS * (int64_t)nb);
-  if (!lr->pool.p) lr->pool.alloc(st, lr->pool_elems * (lr->prec == HH_FP64 ? 8 : 4));
-  if (!lr->ublk.p) lr->ublk.alloc(st, lr->ub_elems * 3 * sizeof(double));
+  if (!lr->pool.p) lr->pool.alloc(ctx, lr->pool_elems * (lr->prec == HH_FP64 ? 8 : 4));
+  if (!lr->ublk.p) lr->ublk.alloc(ctx, lr->ub_elems * 3 * sizeof(double));
   for (size_t i = 0; i < nb; ++i) {
     {
       PhaseTimer timer(ctx, HH_PHASE_ACA);

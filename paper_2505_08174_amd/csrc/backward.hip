@@ -690,13 +690,13 @@ void backward_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, co
   hipStream_t st = ctx->stream;
   const int64_t n = t->n;
   DevBuf Fs, ws, nearT, farT, dXs, gpool, part;
-  Fs.alloc(st, 3 * n * sizeof(T));
-  ws.alloc(st, 3 * n * sizeof(T));
+  Fs.alloc(ctx, 3 * n * sizeof(T));
+  ws.alloc(ctx, 3 * n * sizeof(T));
   hipLaunchKernelGGL((k_gather3<T>), dim3(nblk(n)), dim3(TB), 0, st, (const T*)F,
                      t->perm.as<int32_t>(), n, Fs.as<T>());
   hipLaunchKernelGGL((k_gather3<T>), dim3(nblk(n)), dim3(TB), 0, st, (const T*)dU,
                      t->perm.as<int32_t>(), n, ws.as<T>());
-  farT.alloc(st, 3 * n * sizeof(double));
+  farT.alloc(ctx, 3 * n * sizeof(double));
   HIP_OK(hipMemsetAsync(farT.p, 0, 3 * n * sizeof(double), st));
   const bool mlp = k->kind == KIND_MLP && (dX || dparams);
   const int64_t nG = p->nG;
@@ -726,13 +726,13 @@ void backward_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, co
     }
     chunk_max = std::max(chunk_max, cur);
     bounds.push_back(nG);
-    goff.alloc(st, nG * sizeof(int64_t));
+    goff.alloc(ctx, nG * sizeof(int64_t));
     HIP_OK(hipMemcpyAsync(goff.p, off.data(), nG * sizeof(int64_t), hipMemcpyHostToDevice, st));
-    gpool.alloc(st, chunk_max * sizeof(T));
+    gpool.alloc(ctx, chunk_max * sizeof(T));
   }
   const int gfb = (int)std::min<int64_t>(std::max<int64_t>(nG, 1), 256);
   if (mlp) {
-    dXs.alloc(st, 3 * n * sizeof(double));
+    dXs.alloc(ctx, 3 * n * sizeof(double));
     HIP_OK(hipMemsetAsync(dXs.p, 0, 3 * n * sizeof(double), st));
   }
   // FP32: near and sampled pairs on the FP32 MFMA tile (persistent waves, one
@@ -744,9 +744,9 @@ void backward_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, co
   // dtheta partial slots: near, far, and fallback where a block fell back
   const int nparts = gnear + gfar + (lr->n_fallback > 0 ? gfb : 0);
   DevBuf pre;   // items of the MFMA kernels' sequences
-  if (mlp && mf) pre.alloc(st, (vjp_f32_waves(ctx) + 1) * sizeof(int64_t));
+  if (mlp && mf) pre.alloc(ctx, (vjp_f32_waves(ctx) + 1) * sizeof(int64_t));
   if (mlp) {
-    part.alloc(st, (int64_t)nparts * MLP_NP * sizeof(double));
+    part.alloc(ctx, (int64_t)nparts * MLP_NP * sizeof(double));
     HIP_OK(hipMemsetAsync(part.p, 0, (int64_t)nparts * MLP_NP * sizeof(double), st));
   }
   const T* wgt = (const T*)(sizeof(T) == 8 ? k->p64.p : k->p32.p);
@@ -790,7 +790,7 @@ void backward_t(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k, co
     const int prec = sizeof(T) == 8 ? HH_FP64 : HH_FP32;
     const int groups = near_groups(ctx, t, p, k, prec);
     const bool f64 = near_rows_f64(k, prec, groups);
-    nearT.alloc(st, 3 * n * (int64_t)groups * (f64 ? sizeof(double) : sizeof(T)));
+    nearT.alloc(ctx, 3 * n * (int64_t)groups * (f64 ? sizeof(double) : sizeof(T)));
     launch_near_neg(ctx, t, p, k, prec, ws.p, nearT.p, groups);
     if (f64)
       hipLaunchKernelGGL((k_scatter_dF<T, double>), dim3(nblk(n)), dim3(TB), 0, st, ws.as<T>(),

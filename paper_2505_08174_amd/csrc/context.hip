@@ -363,9 +363,8 @@ hh_status hh_ctx_create(int device, void* stream, hh_ctx* out) {
     HIP_OK(hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
     HIP_OK(hipEventCreateWithFlags(&ctx->fork, hipEventDisableTiming));
     HIP_OK(hipEventCreateWithFlags(&ctx->join, hipEventDisableTiming));
-    ctx->budget_bytes = (size_t)(0.4 * (double)devmem_attach(device));
-    ctx->attached = true;
-    ctx->scratch_flag.alloc(ctx->stream, 64 * sizeof(int64_t));
+    ctx->budget_bytes = (size_t)(0.4 * (double)devmem_attach(ctx));
+    ctx->scratch_flag.alloc(ctx, 64 * sizeof(int64_t));
     HIP_OK(hipHostMalloc((void**)&ctx->pinned, 64 * sizeof(int64_t), hipHostMallocDefault));
   } catch (const hh_error& e) {
     hh_ctx_destroy(ctx);
@@ -382,7 +381,7 @@ void hh_ctx_destroy(hh_ctx ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
   ctx->scratch_flag.release();
-  (void)hipStreamSynchronize(ctx->stream);
+  bool waited = hipStreamSynchronize(ctx->stream) == hipSuccess;
   for (auto& r : ctx->pending) {
     (void)hipEventDestroy(r.a);
     (void)hipEventDestroy(r.b);
@@ -395,11 +394,9 @@ void hh_ctx_destroy(hh_ctx ctx) {
   if (ctx->fork) (void)hipEventDestroy(ctx->fork);
   if (ctx->join) (void)hipEventDestroy(ctx->join);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
-  if (ctx->attached) {
-    // blocks freed on a stream used earlier may still be in use there
-    const bool all = ctx->restreamed && hipDeviceSynchronize() == hipSuccess;
-    devmem_detach(ctx->device, ctx->stream, all);
-  }
+  // work queued on a stream used earlier may still be running
+  if (ctx->restreamed || !waited) waited = hipDeviceSynchronize() == hipSuccess;
+  devmem_detach(ctx, waited);
   delete ctx;
 }
 
@@ -407,8 +404,10 @@ const char* hh_last_error(hh_ctx ctx) { return ctx ? ctx->last_error.c_str() : "
 
 hh_status hh_ctx_set_stream(hh_ctx ctx, void* stream) {
   if (!ctx) return HH_ERR_INVALID_ARG;
-  ctx->restreamed |= ctx->stream != (hipStream_t)stream;
+  if (ctx->stream == (hipStream_t)stream) return HH_OK;
+  ctx->restreamed = true;
   ctx->stream = (hipStream_t)stream;
+  devmem_restream(ctx, ctx->stream);
   return HH_OK;
 }
 
@@ -512,23 +511,23 @@ hh_status hh_kernel_create_mlp(hh_ctx ctx, const double* params, int input_mode,
     k->host_params.assign(params, params + MLP_NP);
     std::vector<float> p32(params, params + MLP_NP);
     std::vector<uint16_t> fr = build_bf16_frags(params);
-    k->pbf.alloc(ctx->stream, fr.size() * sizeof(uint16_t));
+    k->pbf.alloc(ctx, fr.size() * sizeof(uint16_t));
     HIP_OK(hipMemcpyAsync(k->pbf.p, fr.data(), fr.size() * sizeof(uint16_t),
                           hipMemcpyHostToDevice, ctx->stream));
     std::vector<float> f32 = build_f32_frags(params);
-    k->pf32.alloc(ctx->stream, f32.size() * sizeof(float));
+    k->pf32.alloc(ctx, f32.size() * sizeof(float));
     HIP_OK(hipMemcpyAsync(k->pf32.p, f32.data(), f32.size() * sizeof(float),
                           hipMemcpyHostToDevice, ctx->stream));
     std::vector<uint32_t> x2 = build_x2_frags(params);
-    k->px2.alloc(ctx->stream, x2.size() * sizeof(uint32_t));
+    k->px2.alloc(ctx, x2.size() * sizeof(uint32_t));
     HIP_OK(hipMemcpyAsync(k->px2.p, x2.data(), x2.size() * sizeof(uint32_t),
                           hipMemcpyHostToDevice, ctx->stream));
     std::vector<float> f32t = build_f32_bwd(params);
-    k->pf32t.alloc(ctx->stream, f32t.size() * sizeof(float));
+    k->pf32t.alloc(ctx, f32t.size() * sizeof(float));
     HIP_OK(hipMemcpyAsync(k->pf32t.p, f32t.data(), f32t.size() * sizeof(float),
                           hipMemcpyHostToDevice, ctx->stream));
-    k->p64.alloc(ctx->stream, MLP_NP * sizeof(double));
-    k->p32.alloc(ctx->stream, MLP_NP * sizeof(float));
+    k->p64.alloc(ctx, MLP_NP * sizeof(double));
+    k->p32.alloc(ctx, MLP_NP * sizeof(float));
     HIP_OK(hipMemcpyAsync(k->p64.p, params, MLP_NP * sizeof(double), hipMemcpyHostToDevice,
                           ctx->stream));
     HIP_OK(hipMemcpyAsync(k->p32.p, p32.data(), MLP_NP * sizeof(float), hipMemcpyHostToDevice,

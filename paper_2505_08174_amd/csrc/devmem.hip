@@ -9,9 +9,12 @@
 // blocks therefore stay here, one list per size class (eight classes per
 // power of two, so a block is at most an eighth larger than asked for).
 //
-// A block is reused only on the stream it was freed on (stream order then
-// keeps its earlier readers ahead of its next writers), or on any stream once
-// that stream has been waited for. The lists of a device hold at most
+// A kept block belongs to the context whose buffer it was, and a later buffer takes
+// it if the order of streams puts the block's earlier work ahead: the same context's
+// buffers, those of another context on the same stream (if neither ever changed its
+// stream), and, once the context has been waited for and destroyed, any. That wait
+// says nothing about another context's blocks: their work may have been queued
+// after it, by another thread. The lists of a device hold at most
 // KEEP_SHARE of its memory, or the largest budget a caller granted a context up to
 // KEEP_MOST of it (the largest blocks go first: with KEEP_SHARE alone, a budget of
 // 280 GB and a factor pool above 115 GB, the pool was mapped anew in every other
@@ -30,17 +33,34 @@ namespace {
 constexpr int MAX_DEVICES = 64;
 constexpr double KEEP_SHARE = 0.4, KEEP_MOST = 0.75;
 
+// Owners of kept blocks besides the contexts' numbers.
+constexpr uint64_t IDLE = 0;               // nothing queued uses it any more
+constexpr uint64_t LOST = ~(uint64_t)0;    // of a context that could not be waited for
+
 struct Block {
   void* p;
+  uint64_t owner;
+};
+
+struct Owner {
   hipStream_t stream;
-  bool idle;   // nothing queued uses it any more: any stream may take it
+  bool moved;   // it has been on another stream
 };
 
 struct DeviceBlocks {
   std::map<size_t, std::vector<Block>> free;
+  std::map<uint64_t, Owner> contexts;   // the living ones by number
   size_t kept = 0, limit = 0, most = 0;
-  int contexts = 0;
 };
+uint64_t g_contexts = 0;   // contexts so far
+
+// Whether the work of context `owner`'s blocks is ahead of what context c queues.
+bool ordered(const DeviceBlocks* d, uint64_t owner, hh_ctx c) {
+  if (owner == IDLE || owner == c->mem) return true;
+  const auto a = d->contexts.find(owner), b = d->contexts.find(c->mem);
+  return a != d->contexts.end() && b != d->contexts.end() && !a->second.moved &&
+         !b->second.moved && a->second.stream == b->second.stream;
+}
 
 std::mutex g_mu;
 // never destroyed: handles may be freed while the process ends
@@ -72,10 +92,11 @@ void DevBuf::release() {
   if (!p) return;
   std::lock_guard<std::mutex> lock(g_mu);
   DeviceBlocks* d = device_blocks(dev);
-  if (!d || d->contexts == 0) {
+  if (!d || d->contexts.empty()) {
     (void)hipFreeAsync(p, s);
   } else {
-    d->free[bytes].push_back(Block{p, s, false});
+    // (a context that is gone was waited for)
+    d->free[bytes].push_back(Block{p, d->contexts.count(owner) ? owner : IDLE});
     d->kept += bytes;
     if (d->kept > d->limit) {
       (void)hipDeviceSynchronize();
@@ -92,11 +113,23 @@ void DevBuf::release() {
   bytes = 0;
 }
 
-void DevBuf::alloc(hipStream_t stream, size_t nbytes) {
+void DevBuf::take(DevBuf& src) {
   release();
-  s = stream;
+  p = src.p;
+  bytes = src.bytes;
+  owner = src.owner;
+  s = src.s;
+  dev = src.dev;
+  src.p = nullptr;
+  src.bytes = 0;
+}
+
+void DevBuf::alloc(hh_ctx ctx, size_t nbytes) {
+  release();
+  owner = ctx->mem;
+  s = ctx->stream;
+  dev = ctx->device;
   const size_t c = size_class(nbytes);
-  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
   std::lock_guard<std::mutex> lock(g_mu);
   DeviceBlocks* d = device_blocks(dev);
   if (d) {
@@ -104,7 +137,7 @@ void DevBuf::alloc(hipStream_t stream, size_t nbytes) {
     for (auto it = d->free.lower_bound(c); it != d->free.end() && it->first <= c + c / 4; ++it) {
       std::vector<Block>& v = it->second;
       for (size_t i = v.size(); i-- > 0;) {
-        if (!v[i].idle && v[i].stream != stream) continue;
+        if (!ordered(d, v[i].owner, ctx)) continue;
         p = v[i].p;
         bytes = it->first;
         v.erase(v.begin() + i);
@@ -114,11 +147,11 @@ void DevBuf::alloc(hipStream_t stream, size_t nbytes) {
       }
     }
   }
-  hipError_t e = hipMallocAsync(&p, c, stream);
+  hipError_t e = hipMallocAsync(&p, c, s);
   if (e != hipSuccess && d && d->kept > 0) {
     (void)hipGetLastError();
     give_back(d);
-    e = hipMallocAsync(&p, c, stream);
+    e = hipMallocAsync(&p, c, s);
   }
   if (e != hipSuccess) {
     p = nullptr;
@@ -129,15 +162,16 @@ void DevBuf::alloc(hipStream_t stream, size_t nbytes) {
   bytes = c;
 }
 
-size_t devmem_attach(int dev) {
+size_t devmem_attach(hh_ctx ctx) {
   std::lock_guard<std::mutex> lock(g_mu);
-  DeviceBlocks* d = device_blocks(dev);
+  DeviceBlocks* d = device_blocks(ctx->device);
   size_t fr = 0, tot = 0;
   HIP_OK(hipMemGetInfo(&fr, &tot));
   if (!d) return fr;
-  if (d->contexts == 0) d->limit = (size_t)(KEEP_SHARE * (double)tot);
+  if (d->contexts.empty()) d->limit = (size_t)(KEEP_SHARE * (double)tot);
   d->most = (size_t)(KEEP_MOST * (double)tot);
-  d->contexts += 1;
+  d->contexts[++g_contexts] = Owner{ctx->stream, false};
+  ctx->mem = g_contexts;
   return fr + d->kept;
 }
 
@@ -147,11 +181,20 @@ void devmem_grant(int dev, size_t bytes) {
   if (d) d->limit = std::max(d->limit, std::min(bytes, d->most));
 }
 
-void devmem_detach(int dev, hipStream_t stream, bool whole_device) {
+void devmem_restream(hh_ctx ctx, hipStream_t stream) {
   std::lock_guard<std::mutex> lock(g_mu);
-  DeviceBlocks* d = device_blocks(dev);
+  DeviceBlocks* d = device_blocks(ctx->device);
   if (!d) return;
+  const auto c = d->contexts.find(ctx->mem);
+  if (c != d->contexts.end()) c->second = Owner{stream, true};
+}
+
+void devmem_detach(hh_ctx ctx, bool waited) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  DeviceBlocks* d = device_blocks(ctx->device);
+  if (!d || !d->contexts.erase(ctx->mem)) return;
   for (auto& c : d->free)
-    for (Block& b : c.second) b.idle |= whole_device || b.stream == stream;
-  if (--d->contexts == 0) give_back(d);
+    for (Block& b : c.second)
+      if (b.owner == ctx->mem) b.owner = waited ? IDLE : LOST;
+  if (d->contexts.empty()) give_back(d);
 }

@@ -32,11 +32,13 @@ struct hh_error {
 
 // ------------------------------------------------------------- device memory
 
-// A stream-ordered device buffer: allocated for use on `stream`, returned to
-// the kept blocks of its device on that stream (devmem.hip). Not cleared.
+// A device buffer of a context, for use in the context's stream order and
+// returned to the kept blocks of its device in that order (devmem.hip). Not
+// cleared.
 struct DevBuf {
   void* p = nullptr;
-  size_t bytes = 0;   // of the block, at least what was asked for
+  size_t bytes = 0;     // of the block, at least what was asked for
+  uint64_t owner = 0;   // number of the context (hh_ctx_s::mem)
   hipStream_t s = nullptr;
   int dev = -1;
   DevBuf() = default;
@@ -44,22 +46,23 @@ struct DevBuf {
   DevBuf& operator=(const DevBuf&) = delete;
   ~DevBuf() { release(); }
   void release();
-  void alloc(hipStream_t stream, size_t nbytes);
+  void alloc(hh_ctx ctx, size_t nbytes);
   // keeps the buffer when it already holds nbytes (no allocation, so a
   // repeated call can be captured in a graph)
-  void ensure(hipStream_t stream, size_t nbytes) {
-    if (!p || bytes < nbytes) alloc(stream, nbytes);
+  void ensure(hh_ctx ctx, size_t nbytes) {
+    if (!p || bytes < nbytes) alloc(ctx, nbytes);
   }
+  void take(DevBuf& src);   // moves the storage of src here
   template <class T> T* as() const { return reinterpret_cast<T*>(p); }
 };
 
-// A context on device `dev` exists (returns its free memory, the kept blocks
-// counted as free) or is gone, after a wait for `stream`, or with whole_device
-// for every stream of the device. devmem_grant: a caller's budget, which the kept
-// blocks may fill.
-size_t devmem_attach(int dev);
+// A context exists (returns its device's free memory, the kept blocks counted as
+// free) or goes; waited: nothing it queued is still running. devmem_grant: a
+// caller's budget, which the kept blocks may fill.
+size_t devmem_attach(hh_ctx ctx);
 void devmem_grant(int dev, size_t bytes);
-void devmem_detach(int dev, hipStream_t stream, bool whole_device);
+void devmem_restream(hh_ctx ctx, hipStream_t stream);   // the context leaves its stream
+void devmem_detach(hh_ctx ctx, bool waited);
 
 struct PhaseRec {
   int phase;
@@ -74,7 +77,8 @@ struct hh_ctx_s {
   // runs beside the single-wave kernel, forked from and joined to `stream`
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
-  bool attached = false, restreamed = false;   // counted in devmem; the stream was replaced
+  uint64_t mem = 0;          // its number in devmem, 0: not counted there
+  bool restreamed = false;   // the stream was replaced
   std::string last_error;
   DevBuf scratch_flag;   // small device scratch for readbacks (64 x int64)
   int64_t* pinned = nullptr;  // host pinned mirror for readbacks (64 x int64)

@@ -166,14 +166,14 @@ void ensure_units(hh_ctx ctx, hh_tree t) {
   hipStream_t st = ctx->stream;
   int64_t nl = t->n_leaves;
   DevBuf cnt, pos;
-  cnt.alloc(st, (nl + 1) * sizeof(int64_t));
-  pos.alloc(st, (nl + 1) * sizeof(int64_t));
+  cnt.alloc(ctx, (nl + 1) * sizeof(int64_t));
+  pos.alloc(ctx, (nl + 1) * sizeof(int64_t));
   unsigned g = (unsigned)((nl + 1 + T256_UNITS - 1) / T256_UNITS);
   hipLaunchKernelGGL(k_units_count, dim3(g), dim3(T256_UNITS), 0, st, t->leaves.as<int32_t>(), nl,
                      t->nodes.as<int4>(), cnt.as<int64_t>());
   scan_exclusive_i64(ctx, cnt.as<int64_t>(), pos.as<int64_t>(), nl + 1);
   int64_t nu = read_i64(ctx, pos.as<int64_t>() + nl);
-  t->units.alloc(st, std::max<int64_t>(1, nu) * sizeof(int2));
+  t->units.alloc(ctx, std::max<int64_t>(1, nu) * sizeof(int2));
   hipLaunchKernelGGL(k_units_fill, dim3(g), dim3(T256_UNITS), 0, st, cnt.as<int64_t>(),
                      pos.as<int64_t>(), nl, t->units.as<int2>());
   HIP_OK(hipGetLastError());

@@ -191,8 +191,8 @@ static void sort_pairs(hh_ctx ctx, const int2* src, int64_t m, int nb, int2* dst
   if (m < 1) return;
   hipStream_t st = ctx->stream;
   DevBuf key, val;
-  key.alloc(st, m * sizeof(uint64_t));
-  val.alloc(st, m * sizeof(uint32_t));
+  key.alloc(ctx, m * sizeof(uint64_t));
+  val.alloc(ctx, m * sizeof(uint32_t));
   hipLaunchKernelGGL(k_pack, dim3(nblk(m)), dim3(T256), 0, st, src, m, nb, key.as<uint64_t>(),
                      val.as<uint32_t>());
   radix_sort_u64(ctx, key.as<uint64_t>(), val.as<uint32_t>(), m, 2 * nb);
@@ -226,15 +226,15 @@ hh_status hh_partition(hh_ctx ctx, hh_tree tree, double eta, int dense_mode, hh_
     int64_t capG = 160 * m + 1024, capH = 64 * m + 1024;
     int64_t capF = std::max<int64_t>(160 * m + 1024, nsys);
     DevBuf G, H, f0, f1, cnt;
-    cnt.alloc(st, NCNT * sizeof(unsigned long long));
+    cnt.alloc(ctx, NCNT * sizeof(unsigned long long));
     std::vector<int64_t> c(NCNT);
     const unsigned grid = (unsigned)std::min<int64_t>(4 * (int64_t)ctx->n_cu, nblk(capF));
     bool done = false;
     while (!done) {
-      G.ensure(st, capG * sizeof(int2));
-      H.ensure(st, capH * sizeof(int2));
-      f0.ensure(st, capF * sizeof(int2));
-      f1.ensure(st, capF * sizeof(int2));
+      G.ensure(ctx, capG * sizeof(int2));
+      H.ensure(ctx, capH * sizeof(int2));
+      f0.ensure(ctx, capF * sizeof(int2));
+      f1.ensure(ctx, capF * sizeof(int2));
       hipLaunchKernelGGL(k_roots_frontier, dim3((std::max(nsys, NCNT) + 255) / 256), dim3(256), 0,
                          st, tree->roots.as<int32_t>(), nsys, f0.as<int2>(),
                          cnt.as<unsigned long long>(), NCNT);
@@ -266,19 +266,19 @@ hh_status hh_partition(hh_ctx ctx, hh_tree tree, double eta, int dense_mode, hh_
     }
     p->nG = c[0];
     p->nH = c[1];
-    p->G.alloc(st, std::max<int64_t>(1, p->nG) * sizeof(int2));
-    p->H.alloc(st, std::max<int64_t>(1, p->nH) * sizeof(int2));
+    p->G.alloc(ctx, std::max<int64_t>(1, p->nG) * sizeof(int2));
+    p->H.alloc(ctx, std::max<int64_t>(1, p->nH) * sizeof(int2));
     int nb = 1;
     while ((1ll << nb) < tree->n_nodes) ++nb;
     sort_pairs(ctx, G.as<int2>(), p->nG, nb, p->G.as<int2>());
     sort_pairs(ctx, H.as<int2>(), p->nH, nb, p->H.as<int2>());
-    p->near_ptr.alloc(st, (tree->n_leaves + 1) * sizeof(int32_t));
-    p->far_ptr.alloc(st, (tree->n_nodes + 1) * sizeof(int32_t));
+    p->near_ptr.alloc(ctx, (tree->n_leaves + 1) * sizeof(int32_t));
+    p->far_ptr.alloc(ctx, (tree->n_nodes + 1) * sizeof(int32_t));
     hipLaunchKernelGGL(k_near_ptr, dim3(nblk(p->nH + 1)), dim3(T256), 0, st, p->H.as<int2>(),
                        p->nH, tree->leaf_id.as<int32_t>(), tree->n_leaves,
                        p->near_ptr.as<int32_t>());
-    p->near_src.alloc(st, std::max<int64_t>(1, p->nH) * sizeof(int4));
-    p->near_q.alloc(st, tree->n_leaves * sizeof(int32_t));
+    p->near_src.alloc(ctx, std::max<int64_t>(1, p->nH) * sizeof(int4));
+    p->near_q.alloc(ctx, tree->n_leaves * sizeof(int32_t));
     hipLaunchKernelGGL(k_near_src, dim3(nblk(64 * tree->n_leaves)), dim3(T256), 0, st,
                        p->H.as<int2>(), nodes, p->near_ptr.as<int32_t>(), tree->n_leaves,
                        p->near_src.as<int4>(), p->near_q.as<int32_t>());

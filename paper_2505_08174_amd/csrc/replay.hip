@@ -266,13 +266,13 @@ hh_lowrank_s* build_lowrank_pivots(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k
     lr->streamed = false;
     const size_t es = elem_size(prec);
     const int64_t nb = std::max<int64_t>(nG, 1);
-    lr->rank.alloc(st, nb * sizeof(int32_t));
-    lr->flag.alloc(st, nb * sizeof(int32_t));
-    lr->piv.alloc(st, nb * 2 * LMAX_CAP * sizeof(int32_t));
-    lr->fptr.alloc(st, nb * LMAX_CAP * sizeof(int64_t));
-    lr->toff.alloc(st, (nb + 1) * sizeof(int64_t));
+    lr->rank.alloc(ctx, nb * sizeof(int32_t));
+    lr->flag.alloc(ctx, nb * sizeof(int32_t));
+    lr->piv.alloc(ctx, nb * 2 * LMAX_CAP * sizeof(int32_t));
+    lr->fptr.alloc(ctx, nb * LMAX_CAP * sizeof(int64_t));
+    lr->toff.alloc(ctx, (nb + 1) * sizeof(int64_t));
     lr->pool_elems = std::max<int64_t>(off, 1024);
-    lr->pool.alloc(st, lr->pool_elems * es);
+    lr->pool.alloc(ctx, lr->pool_elems * es);
     lr->used_elems = off;
     HIP_OK(hipMemcpyAsync(lr->rank.p, rk.data(), nb * sizeof(int32_t), hipMemcpyHostToDevice, st));
     HIP_OK(hipMemcpyAsync(lr->flag.p, fl.data(), nb * sizeof(int32_t), hipMemcpyHostToDevice, st));
@@ -302,7 +302,7 @@ hh_lowrank_s* build_lowrank_pivots(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k
       HIP_OK(hipGetLastError());
     }
     lowrank_stats(ctx, t, p, lr, true);
-    lr->tbuf.alloc(st, std::max<int64_t>(1, lr->rank_sum) * 3 * sizeof(double));
+    lr->tbuf.alloc(ctx, std::max<int64_t>(1, lr->rank_sum) * 3 * sizeof(double));
     // the plan of a stored build: one range over all blocks
     lr->bounds.assign({0, nG});
   } catch (...) {

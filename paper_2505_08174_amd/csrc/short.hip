@@ -481,7 +481,7 @@ __global__ __launch_bounds__(SB) void k_short_f32(const double* __restrict__ xs,
 template <class T>
 void upload_params(hh_ctx ctx, DevBuf& d, const double* p, int np) {
   std::vector<T> v(p, p + np);
-  d.alloc(ctx->stream, np * sizeof(T));
+  d.alloc(ctx, np * sizeof(T));
   HIP_OK(hipMemcpyAsync(d.p, v.data(), np * sizeof(T), hipMemcpyHostToDevice, ctx->stream));
   ctx_sync(ctx);   // v is freed on return
 }
@@ -491,7 +491,7 @@ void short_matvec_t(hh_ctx ctx, hh_short_s* sh, const void* F, void* U) {
   hipStream_t st = ctx->stream;
   hh_tree t = sh->tree;
   const int64_t n = sh->n;
-  sh->ws_f.ensure(st, 3 * n * sizeof(T));
+  sh->ws_f.ensure(ctx, 3 * n * sizeof(T));
   hipLaunchKernelGGL((k_gather_f<TI, T>), dim3(nblk(n)), dim3(TB), 0, st, (const TI*)F,
                      t->perm.as<int32_t>(), n, sh->ws_f.as<T>());
   if constexpr (sizeof(T) == 4) {
@@ -542,8 +542,8 @@ hh_status hh_short_create(hh_ctx ctx, hh_tree tree, const double* s2_params,
     upload_params<float>(ctx, sh->w3_32, g3_params, G3_NP);
     {
       const std::vector<float> fh = build_f32_frags(s2_params), fg = build_g32_frags(g3_params);
-      sh->fr_h.alloc(st, fh.size() * sizeof(float));
-      sh->fr_g.alloc(st, fg.size() * sizeof(float));
+      sh->fr_h.alloc(ctx, fh.size() * sizeof(float));
+      sh->fr_g.alloc(ctx, fg.size() * sizeof(float));
       HIP_OK(hipMemcpyAsync(sh->fr_h.p, fh.data(), fh.size() * sizeof(float),
                             hipMemcpyHostToDevice, st));
       HIP_OK(hipMemcpyAsync(sh->fr_g.p, fg.data(), fg.size() * sizeof(float),
@@ -565,10 +565,10 @@ hh_status hh_short_create(hh_ctx ctx, hh_tree tree, const double* s2_params,
     }
     HH_REQUIRE(ncell < (1ll << 31), HH_ERR_CAPACITY, "the cell grid would be too large");
     DevBuf key, val, cnt, cstart;
-    key.alloc(st, n * sizeof(uint64_t));
-    val.alloc(st, n * sizeof(uint32_t));
-    cnt.alloc(st, (ncell + 1) * sizeof(int64_t));
-    cstart.alloc(st, (ncell + 1) * sizeof(int64_t));
+    key.alloc(ctx, n * sizeof(uint64_t));
+    val.alloc(ctx, n * sizeof(uint32_t));
+    cnt.alloc(ctx, (ncell + 1) * sizeof(int64_t));
+    cstart.alloc(ctx, (ncell + 1) * sizeof(int64_t));
     zero_words(ctx, cnt.p, ncell + 1);
     hipLaunchKernelGGL(k_cell_key, dim3(nblk(n)), dim3(TB), 0, st, tree->xs.as<double>(), n, G,
                        key.as<uint64_t>(), val.as<uint32_t>(), cnt.as<int64_t>());
@@ -579,15 +579,15 @@ hh_status hh_short_create(hh_ctx ctx, hh_tree tree, const double* s2_params,
     scan_exclusive_i64(ctx, cnt.as<int64_t>(), cstart.as<int64_t>(), ncell + 1);
     const double rc2 = r_cut * r_cut;
     DevBuf ncnt;
-    ncnt.alloc(st, (n + 1) * sizeof(int64_t));
+    ncnt.alloc(ctx, (n + 1) * sizeof(int64_t));
     zero_words(ctx, ncnt.p, n + 1);
     hipLaunchKernelGGL(k_nb_count, dim3(nblk(n)), dim3(TB), 0, st, tree->xs.as<double>(), n, G,
                        rc2, cstart.as<int64_t>(), val.as<uint32_t>(), ncnt.as<int64_t>());
-    sh->nb_ptr.alloc(st, (n + 1) * sizeof(int64_t));
+    sh->nb_ptr.alloc(ctx, (n + 1) * sizeof(int64_t));
     scan_exclusive_i64(ctx, ncnt.as<int64_t>(), sh->nb_ptr.as<int64_t>(), n + 1);
     sh->n_pairs = read_i64(ctx, sh->nb_ptr.as<int64_t>() + n);
     HH_REQUIRE(sh->n_pairs < (1ll << 40), HH_ERR_CAPACITY, "too many neighbour pairs");
-    sh->nb.alloc(st, std::max<int64_t>(sh->n_pairs, 1) * sizeof(int32_t));
+    sh->nb.alloc(ctx, std::max<int64_t>(sh->n_pairs, 1) * sizeof(int32_t));
     hipLaunchKernelGGL(k_nb_fill, dim3(nblk(n)), dim3(TB), 0, st, tree->xs.as<double>(), n, G,
                        rc2, cstart.as<int64_t>(), val.as<uint32_t>(), sh->nb_ptr.as<int64_t>(),
                        sh->nb.as<int32_t>());

@@ -301,7 +301,7 @@ void scan_exclusive_i64(hh_ctx ctx, const int64_t* in, int64_t* out, int64_t n) 
   }
   int64_t tiles = (n + SCAN_TILE - 1) / SCAN_TILE;
   DevBuf sums;
-  sums.alloc(ctx->stream, tiles * sizeof(int64_t));
+  sums.alloc(ctx, tiles * sizeof(int64_t));
   hipLaunchKernelGGL(k_scan_reduce, dim3(tiles), dim3(SCAN_T), 0, ctx->stream, in, n,
                      sums.as<int64_t>());
   hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(SCAN_T), 0, ctx->stream, sums.as<int64_t>(),
@@ -322,9 +322,9 @@ void radix_sort_u64(hh_ctx ctx, uint64_t* keys, uint32_t* vals, int64_t n, int b
   }
   int64_t nblocks = (n + RS_TILE - 1) / RS_TILE;
   DevBuf k2, v2, hist;
-  k2.alloc(ctx->stream, n * sizeof(uint64_t));
-  v2.alloc(ctx->stream, n * sizeof(uint32_t));
-  hist.alloc(ctx->stream, 256 * nblocks * sizeof(int64_t));
+  k2.alloc(ctx, n * sizeof(uint64_t));
+  v2.alloc(ctx, n * sizeof(uint32_t));
+  hist.alloc(ctx, 256 * nblocks * sizeof(int64_t));
   uint64_t *ka = keys, *kb = k2.as<uint64_t>();
   uint32_t *va = vals, *vb = v2.as<uint32_t>();
   for (int p = 0; p < passes; ++p) {

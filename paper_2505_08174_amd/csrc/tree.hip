@@ -494,17 +494,6 @@ __global__ __launch_bounds__(T256) void k_six_nodes(int64_t m, int4* __restrict_
   nodes[i] = v;
 }
 
-// moves the storage of src into dst (both on the context stream)
-void take(DevBuf& dst, DevBuf& src) {
-  dst.release();
-  dst.p = src.p;
-  dst.bytes = src.bytes;
-  dst.dev = src.dev;
-  dst.s = src.s;
-  src.p = nullptr;
-  src.bytes = 0;
-}
-
 }  // namespace
 
 static void build_tree_impl(hh_ctx ctx, hh_tree_s* t, const double* X, int64_t n,
@@ -516,18 +505,18 @@ static void build_tree_impl(hh_ctx ctx, hh_tree_s* t, const double* X, int64_t n
   t->ctx = ctx;
   t->n = n;
   t->c_leaf = *std::max_element(cls.begin(), cls.end());
-  t->cl.alloc(st, nsys * sizeof(int32_t));
+  t->cl.alloc(ctx, nsys * sizeof(int32_t));
   HIP_OK(hipMemcpyAsync(t->cl.p, cls.data(), nsys * sizeof(int32_t), hipMemcpyHostToDevice, st));
   t->n_sys = nsys;
   t->offs_host = offs;
-  t->offs.alloc(st, (nsys + 1) * sizeof(int64_t));
+  t->offs.alloc(ctx, (nsys + 1) * sizeof(int64_t));
   HIP_OK(hipMemcpyAsync(t->offs.p, offs.data(), (nsys + 1) * sizeof(int64_t),
                         hipMemcpyHostToDevice, st));
   const int64_t* off = t->offs.as<int64_t>();
   // a1: per-system box, quantisation constants, Morton keys
   DevBuf mm, qc;
-  mm.alloc(st, 6 * nsys * sizeof(unsigned long long));
-  qc.alloc(st, 4 * nsys * sizeof(double));
+  mm.alloc(ctx, 6 * nsys * sizeof(unsigned long long));
+  qc.alloc(ctx, 4 * nsys * sizeof(double));
   int* flags = (int*)ctx->scratch_flag.p;   // [0] non-finite, [1] duplicates
   HIP_OK(hipMemsetAsync(flags, 0, 4 * sizeof(int), st));
   hipLaunchKernelGGL(k_mm_init, dim3((6 * nsys + 255) / 256), dim3(256), 0, st,
@@ -540,10 +529,10 @@ static void build_tree_impl(hh_ctx ctx, hh_tree_s* t, const double* X, int64_t n
                        mm.as<unsigned long long>(), flags);
   hipLaunchKernelGGL(k_sys_final, dim3((nsys + 255) / 256), dim3(256), 0, st,
                      mm.as<unsigned long long>(), nsys, qc.as<double>());
-  t->keys.alloc(st, n * sizeof(uint64_t));
+  t->keys.alloc(ctx, n * sizeof(uint64_t));
   DevBuf idx, sysk;
-  idx.alloc(st, n * sizeof(uint32_t));
-  sysk.alloc(st, n * sizeof(int32_t));
+  idx.alloc(ctx, n * sizeof(uint32_t));
+  sysk.alloc(ctx, n * sizeof(int32_t));
   hipLaunchKernelGGL(k_morton, dim3(nblk(n)), dim3(T256), 0, st, X, n, off, nsys,
                      qc.as<double>(), t->keys.as<uint64_t>(), idx.as<uint32_t>());
   HIP_OK(hipGetLastError());
@@ -557,8 +546,8 @@ static void build_tree_impl(hh_ctx ctx, hh_tree_s* t, const double* X, int64_t n
   hipLaunchKernelGGL(k_rekey, dim3(nblk(n)), dim3(T256), 0, st, X, n, off, nsys,
                      qc.as<double>(), idx.as<uint32_t>(), t->keys.as<uint64_t>(),
                      sysk.as<int32_t>());
-  t->xs.alloc(st, 3 * n * sizeof(double));
-  t->perm.alloc(st, n * sizeof(int32_t));
+  t->xs.alloc(ctx, 3 * n * sizeof(double));
+  t->perm.alloc(ctx, n * sizeof(int32_t));
   hipLaunchKernelGGL(k_gather_check, dim3(nblk(n)), dim3(T256), 0, st, X, n,
                      t->keys.as<uint64_t>(), sysk.as<int32_t>(), idx.as<uint32_t>(),
                      t->xs.as<double>(), t->perm.as<int32_t>(), flags + 1);
@@ -566,16 +555,16 @@ static void build_tree_impl(hh_ctx ctx, hh_tree_s* t, const double* X, int64_t n
   // a3: radix tree, truncation, pre-order
   int64_t nt = 2 * n - 1;
   DevBuf rng, kid, par, keep, kpos;
-  rng.alloc(st, std::max<int64_t>(1, n - 1) * sizeof(int2));
-  kid.alloc(st, std::max<int64_t>(1, n - 1) * sizeof(int2));
-  par.alloc(st, nt * sizeof(int32_t));
+  rng.alloc(ctx, std::max<int64_t>(1, n - 1) * sizeof(int2));
+  kid.alloc(ctx, std::max<int64_t>(1, n - 1) * sizeof(int2));
+  par.alloc(ctx, nt * sizeof(int32_t));
   HIP_OK(hipMemsetAsync(par.p, 0xff, nt * sizeof(int32_t), st));
   if (n > 1)
     hipLaunchKernelGGL(k_radix_tree, dim3(nblk(n - 1)), dim3(T256), 0, st,
                        t->keys.as<uint64_t>(), sysk.as<int32_t>(), sbits, n, rng.as<int2>(),
                        kid.as<int2>(), par.as<int32_t>());
-  keep.alloc(st, (nt + 1) * sizeof(int64_t));
-  kpos.alloc(st, (nt + 1) * sizeof(int64_t));
+  keep.alloc(ctx, (nt + 1) * sizeof(int64_t));
+  kpos.alloc(ctx, (nt + 1) * sizeof(int64_t));
   HIP_OK(hipMemsetAsync(keep.as<int64_t>() + nt, 0, sizeof(int64_t), st));
   hipLaunchKernelGGL(k_keep, dim3(nblk(nt)), dim3(T256), 0, st, rng.as<int2>(),
                      par.as<int32_t>(), t->keys.as<uint64_t>(), sysk.as<int32_t>(), n,
@@ -590,41 +579,41 @@ static void build_tree_impl(hh_ctx ctx, hh_tree_s* t, const double* X, int64_t n
   HH_REQUIRE(!fl_dup, HH_ERR_DUPLICATE_POINTS, "two particles have identical positions");
   t->n_nodes = m;
   DevBuf skey, sval, map;
-  skey.alloc(st, m * sizeof(uint64_t));
-  sval.alloc(st, m * sizeof(uint32_t));
+  skey.alloc(ctx, m * sizeof(uint64_t));
+  sval.alloc(ctx, m * sizeof(uint32_t));
   hipLaunchKernelGGL(k_keep_emit, dim3(nblk(nt)), dim3(T256), 0, st, rng.as<int2>(),
                      keep.as<int64_t>(), kpos.as<int64_t>(), n, skey.as<uint64_t>(),
                      sval.as<uint32_t>());
   int bits = 32;
   while ((1ll << (bits - 32)) <= n) ++bits;
   radix_sort_u64(ctx, skey.as<uint64_t>(), sval.as<uint32_t>(), m, bits);
-  map.alloc(st, nt * sizeof(int32_t));
+  map.alloc(ctx, nt * sizeof(int32_t));
   hipLaunchKernelGGL(k_map, dim3(nblk(m)), dim3(T256), 0, st, sval.as<uint32_t>(), m,
                      map.as<int32_t>());
-  t->nodes.alloc(st, m * sizeof(int4));
-  t->parent.alloc(st, m * sizeof(int32_t));
+  t->nodes.alloc(ctx, m * sizeof(int4));
+  t->parent.alloc(ctx, m * sizeof(int32_t));
   HIP_OK(hipMemsetAsync(t->parent.p, 0xff, m * sizeof(int32_t), st));
   DevBuf isleaf, lpos;
-  isleaf.alloc(st, (m + 1) * sizeof(int64_t));
-  lpos.alloc(st, (m + 1) * sizeof(int64_t));
+  isleaf.alloc(ctx, (m + 1) * sizeof(int64_t));
+  lpos.alloc(ctx, (m + 1) * sizeof(int64_t));
   HIP_OK(hipMemsetAsync(isleaf.as<int64_t>() + m, 0, sizeof(int64_t), st));
   hipLaunchKernelGGL(k_nodes, dim3(nblk(m)), dim3(T256), 0, st, sval.as<uint32_t>(), m,
                      rng.as<int2>(), kid.as<int2>(), t->keys.as<uint64_t>(), sysk.as<int32_t>(),
                      n, t->cl.as<int32_t>(), map.as<int32_t>(), t->nodes.as<int4>(),
                      t->parent.as<int32_t>(),
                      isleaf.as<int64_t>());
-  t->roots.alloc(st, nsys * sizeof(int32_t));
+  t->roots.alloc(ctx, nsys * sizeof(int32_t));
   hipLaunchKernelGGL(k_roots, dim3(nblk(m)), dim3(T256), 0, st, t->nodes.as<int4>(), m,
                      t->parent.as<int32_t>(), sysk.as<int32_t>(), t->roots.as<int32_t>());
   scan_exclusive_i64(ctx, isleaf.as<int64_t>(), lpos.as<int64_t>(), m + 1);
   int64_t nl = read_i64(ctx, lpos.as<int64_t>() + m);
   t->n_leaves = nl;
-  t->leaf_id.alloc(st, m * sizeof(int32_t));
-  t->leaves.alloc(st, nl * sizeof(int32_t));
+  t->leaf_id.alloc(ctx, m * sizeof(int32_t));
+  t->leaves.alloc(ctx, nl * sizeof(int32_t));
   hipLaunchKernelGGL(k_leaves, dim3(nblk(m)), dim3(T256), 0, st, isleaf.as<int64_t>(),
                      lpos.as<int64_t>(), m, t->leaf_id.as<int32_t>(), t->leaves.as<int32_t>());
-  t->leaf_of.alloc(st, n * sizeof(int32_t));
-  t->bbox.alloc(st, 6 * m * sizeof(double));
+  t->leaf_of.alloc(ctx, n * sizeof(int32_t));
+  t->bbox.alloc(ctx, 6 * m * sizeof(double));
   hipLaunchKernelGGL(k_leaf_box, dim3(nblk(nl * 64)), dim3(T256), 0, st,
                      t->leaves.as<int32_t>(), nl, t->nodes.as<int4>(), t->xs.as<double>(),
                      t->leaf_of.as<int32_t>(), t->bbox.as<double>());
@@ -675,28 +664,28 @@ hh_status hh_build_tree6(hh_ctx ctx, const double* X, int64_t n, int32_t c_leaf,
     t->n_leaves = one.n_leaves;
     t->n_sys = 1;
     t->offs_host = {0, n2};
-    t->offs.alloc(st, 2 * sizeof(int64_t));
+    t->offs.alloc(ctx, 2 * sizeof(int64_t));
     HIP_OK(hipMemcpyAsync(t->offs.p, t->offs_host.data(), 2 * sizeof(int64_t),
                           hipMemcpyHostToDevice, st));
     const int32_t cl2 = 2 * c_leaf;
-    t->cl.alloc(st, sizeof(int32_t));
+    t->cl.alloc(ctx, sizeof(int32_t));
     HIP_OK(hipMemcpyAsync(t->cl.p, &cl2, sizeof(int32_t), hipMemcpyHostToDevice, st));
-    t->perm.alloc(st, n2 * sizeof(int32_t));
-    t->keys.alloc(st, n2 * sizeof(uint64_t));
-    t->xs.alloc(st, 3 * n2 * sizeof(double));
-    t->leaf_of.alloc(st, n2 * sizeof(int32_t));
+    t->perm.alloc(ctx, n2 * sizeof(int32_t));
+    t->keys.alloc(ctx, n2 * sizeof(uint64_t));
+    t->xs.alloc(ctx, 3 * n2 * sizeof(double));
+    t->leaf_of.alloc(ctx, n2 * sizeof(int32_t));
     hipLaunchKernelGGL(k_six_rows, dim3(nblk(n2)), dim3(T256), 0, st, n2, one.perm.as<int32_t>(),
                        one.keys.as<uint64_t>(), one.xs.as<double>(), one.leaf_of.as<int32_t>(),
                        t->perm.as<int32_t>(), t->keys.as<uint64_t>(), t->xs.as<double>(),
                        t->leaf_of.as<int32_t>());
-    take(t->nodes, one.nodes);
+    t->nodes.take(one.nodes);
     hipLaunchKernelGGL(k_six_nodes, dim3(nblk(m)), dim3(T256), 0, st, m, t->nodes.as<int4>());
     HIP_OK(hipGetLastError());
-    take(t->parent, one.parent);
-    take(t->bbox, one.bbox);
-    take(t->leaf_id, one.leaf_id);
-    take(t->leaves, one.leaves);
-    take(t->roots, one.roots);
+    t->parent.take(one.parent);
+    t->bbox.take(one.bbox);
+    t->leaf_id.take(one.leaf_id);
+    t->leaves.take(one.leaves);
+    t->roots.take(one.roots);
     ctx_sync(ctx);   // the host values above stay valid until the copies ran
   } catch (...) {
     delete t;

@@ -1,0 +1,212 @@
+// The kept device blocks on a host model of streams: csrc/devmem.hip compiled with a
+// runtime that runs nothing and only tracks order. Every use of a buffer on a stream
+// is a numbered item of that stream; a stream "knows" the items of the others that are
+// ordered ahead of what it queues next (by events and by waits of the host). A block
+// handed out while an item that uses it is not known to the new stream is a race.
+//
+// usage: devmem_host SCENARIO; prints "ok" or the faults found.
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <functional>
+#include <map>
+#include <set>
+
+#include "../paper_2505_08174_amd/csrc/devmem.hip"
+
+namespace model {
+using Clock = std::map<hipStream_t, int>;   // items of each stream that are known
+struct Stream {
+  int device = 0, items = 0;
+  bool capturing = false;
+  Clock knows;
+};
+struct Mem {
+  size_t bytes;
+  int device;
+  bool freed = false;
+  Clock uses;   // last item of each stream that uses it
+};
+std::map<hipStream_t, Stream> streams = {{nullptr, Stream{}}};   // and the null stream
+std::map<void*, Mem> mem;
+std::map<hipEvent_t, Clock> events;
+int current = 0, bad = 0, mallocs = 0;
+size_t live[2] = {0, 0}, total = (size_t)64 << 20;
+std::function<void()> after_wait;   // another thread, between a wait of this one and what follows
+
+void fault(const char* what) {
+  printf("%s\n", what);
+  ++bad;
+}
+hipStream_t stream(long id, int device = 0) {
+  hipStream_t s = (hipStream_t)id;
+  streams[s].device = device;
+  return s;
+}
+void merge(Clock& to, const Clock& from) {
+  for (auto& k : from) to[k.first] = std::max(to[k.first], k.second);
+}
+Clock tail(hipStream_t s) {
+  Clock c = streams[s].knows;
+  c[s] = streams[s].items;
+  return c;
+}
+void host_knows(const Clock& c) {
+  for (auto& s : streams) merge(s.second.knows, c);
+}
+// the work of this buffer that is not ahead of what stream s queues next
+bool pending(const Mem& m, hipStream_t s) {
+  for (auto& u : m.uses)
+    if (u.first != s && u.second > streams[s].knows[u.first]) return true;
+  return false;
+}
+void use(const DevBuf& b, hipStream_t s) {
+  Mem& m = mem[b.p];
+  if (m.freed) fault("use of freed memory");
+  if (pending(m, s)) fault("a block is used on a stream that its earlier work is not ahead of");
+  m.uses[s] = ++streams[s].items;
+}
+void drop(void* p, hipStream_t s, bool wait) {
+  Mem& m = mem[p];
+  if (m.freed) fault("memory freed twice");
+  if (!wait && pending(m, s)) fault("memory returned while its work may be running");
+  m.freed = true;
+  live[m.device] -= m.bytes;
+}
+}  // namespace model
+
+// ------------------------------------------------------------ the runtime calls
+extern "C" {
+hipError_t hipGetDevice(int* d) {
+  *d = model::current;
+  return hipSuccess;
+}
+hipError_t hipSetDevice(int d) {
+  model::current = d;
+  return hipSuccess;
+}
+hipError_t hipMemGetInfo(size_t* fr, size_t* tot) {
+  *tot = model::total;
+  *fr = model::total - model::live[model::current];
+  return hipSuccess;
+}
+const char* hipGetErrorString(hipError_t) { return "error"; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipMallocAsync(void** p, size_t n, hipStream_t s) {
+  const int dev = s ? model::streams[s].device : model::current;
+  if (model::live[dev] + n > model::total) return hipErrorOutOfMemory;
+  static uintptr_t next = 1 << 20;
+  *p = (void*)(next += 256);
+  model::mem[*p] = model::Mem{n, dev, false, {}};
+  model::live[dev] += n;
+  ++model::mallocs;
+  return hipSuccess;
+}
+hipError_t hipFreeAsync(void* p, hipStream_t s) {
+  // the null stream of the current device, not of the memory's
+  if (!s && model::mem[p].device != model::current) model::fault("memory freed on another device");
+  model::drop(p, s, false);
+  return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t s) {
+  model::host_knows(model::tail(s));
+  return hipSuccess;
+}
+hipError_t hipDeviceSynchronize(void) {
+  model::Clock c;
+  for (auto& s : model::streams)
+    if (s.second.device == model::current) model::merge(c, model::tail(s.first));
+  model::host_knows(c);
+  return hipSuccess;
+}
+}
+
+// ------------------------------------------------------------------ scenarios
+using model::stream;
+using model::use;
+
+static hh_ctx_s* context(hipStream_t s, int device = 0) {
+  hh_ctx_s* c = new hh_ctx_s();
+  c->device = device;
+  c->stream = s;
+  model::current = device;
+  devmem_attach(c);
+  return c;
+}
+static void destroy(hh_ctx_s* c) {
+  model::current = c->device;
+  bool waited = hipStreamSynchronize(c->stream) == hipSuccess;
+  if (c->restreamed) waited = hipDeviceSynchronize() == hipSuccess;
+  if (model::after_wait) model::after_wait();
+  model::after_wait = nullptr;
+  devmem_detach(c, waited);
+  delete c;
+}
+static void set_stream(hh_ctx_s* c, hipStream_t s) {
+  c->restreamed = true;
+  c->stream = s;
+  devmem_restream(c, s);
+}
+
+// Another thread frees a buffer with work queued while a context is destroyed, between
+// that context's wait and the return of its blocks; a third stream allocates. With two
+// contexts on one stream, and with streams of their own where the destroyed context
+// has changed its stream.
+static void destroy_race(bool same_stream) {
+  hipStream_t S = stream(1), T = stream(2), V = stream(3);
+  hh_ctx_s *x = context(S), *y = context(same_stream ? S : V), *z = context(T);
+  if (!same_stream) set_stream(x, stream(4));
+  DevBuf a, b;
+  a.alloc(y, 4096);
+  model::after_wait = [&] {
+    use(a, y->stream);
+    a.release();
+  };
+  destroy(x);
+  b.alloc(z, 4096);
+  use(b, T);
+  b.release();
+  destroy(y);
+  destroy(z);
+}
+
+// A context's own blocks come back to it at once, to another context on its stream,
+// and to any once it was destroyed: no allocation after the first.
+static void reuse() {
+  hipStream_t S = stream(1), T = stream(2);
+  hh_ctx_s *x = context(S), *y = context(S), *z = context(T);
+  DevBuf a;
+  for (hh_ctx_s* c : {x, x, y, y}) {
+    a.alloc(c, 4096);
+    use(a, S);
+    a.release();
+  }
+  if (model::mallocs != 1) model::fault("a kept block was not reused on its stream");
+  a.alloc(z, 4096);
+  if (model::mallocs != 2) model::fault("a block in use elsewhere was handed out");
+  use(a, T);
+  a.release();
+  destroy(x);
+  destroy(y);
+  DevBuf b, c;
+  b.alloc(z, 4096);
+  use(b, T);
+  c.alloc(z, 4096);
+  use(c, T);
+  if (model::mallocs != 2) model::fault("a destroyed context's block was not reused");
+  b.release();
+  c.release();
+  destroy(z);
+  if (model::live[0] != 0) model::fault("memory is left after the last context");
+}
+
+int main(int argc, char** argv) {
+  const std::string s = argc > 1 ? argv[1] : "";
+  if (s == "destroy_same_stream") destroy_race(true);
+  else if (s == "destroy_restreamed") destroy_race(false);
+  else if (s == "reuse") reuse();
+  else return 2;
+  if (model::bad == 0) printf("ok\n");
+  return model::bad != 0;
+}
