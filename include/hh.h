@@ -99,7 +99,11 @@ typedef enum { HH_MLP_INPUT_DIRECTION = 0, HH_MLP_INPUT_DISPLACEMENT = 1 } hh_ml
 hh_status hh_ctx_create(int device, void* stream, hh_ctx* out);
 void hh_ctx_destroy(hh_ctx ctx);
 const char* hh_last_error(hh_ctx ctx);
-/* Replace the stream used by later calls. */
+/* Replace the stream used by later calls. They run after everything this context
+ * queued before, on whatever stream; a stream in capture is left unordered (whoever
+ * launches the graph orders its replays). A handle that was used through another
+ * context is freed only after that work, or with it ordered behind its own context's
+ * stream; the same holds for replays of graphs that hold a handle's products. */
 hh_status hh_ctx_set_stream(hh_ctx ctx, void* stream);
 /* Device memory (bytes) that ACA factors may occupy. When the factors of all
  * admissible blocks would not fit in half of it, hh_aca_build only plans

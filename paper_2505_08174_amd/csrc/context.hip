@@ -381,7 +381,7 @@ void hh_ctx_destroy(hh_ctx ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);
   ctx->scratch_flag.release();
-  bool waited = hipStreamSynchronize(ctx->stream) == hipSuccess;
+  const bool waited = devmem_wait(ctx);
   for (auto& r : ctx->pending) {
     (void)hipEventDestroy(r.a);
     (void)hipEventDestroy(r.b);
@@ -394,8 +394,6 @@ void hh_ctx_destroy(hh_ctx ctx) {
   if (ctx->fork) (void)hipEventDestroy(ctx->fork);
   if (ctx->join) (void)hipEventDestroy(ctx->join);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
-  // work queued on a stream used earlier may still be running
-  if (ctx->restreamed || !waited) waited = hipDeviceSynchronize() == hipSuccess;
   devmem_detach(ctx, waited);
   delete ctx;
 }
@@ -403,12 +401,9 @@ void hh_ctx_destroy(hh_ctx ctx) {
 const char* hh_last_error(hh_ctx ctx) { return ctx ? ctx->last_error.c_str() : "null context"; }
 
 hh_status hh_ctx_set_stream(hh_ctx ctx, void* stream) {
-  if (!ctx) return HH_ERR_INVALID_ARG;
-  if (ctx->stream == (hipStream_t)stream) return HH_OK;
-  ctx->restreamed = true;
-  ctx->stream = (hipStream_t)stream;
-  devmem_restream(ctx, ctx->stream);
-  return HH_OK;
+  HH_API_BEGIN(ctx)
+  devmem_restream(ctx, (hipStream_t)stream);
+  HH_API_END(ctx)
 }
 
 hh_status hh_ctx_set_budget(hh_ctx ctx, size_t bytes) {

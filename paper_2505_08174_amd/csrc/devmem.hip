@@ -11,8 +11,9 @@
 //
 // A kept block belongs to the context whose buffer it was, and a later buffer takes
 // it if the order of streams puts the block's earlier work ahead: the same context's
-// buffers, those of another context on the same stream (if neither ever changed its
-// stream), and, once the context has been waited for and destroyed, any. That wait
+// buffers (a context that changes its stream orders the new one after the old one),
+// those of another context on the same stream, and, once the context has been waited
+// for and destroyed, any. That wait
 // says nothing about another context's blocks: their work may have been queued
 // after it, by another thread. The lists of a device hold at most
 // KEEP_SHARE of its memory, or the largest budget a caller granted a context up to
@@ -44,7 +45,7 @@ struct Block {
 
 struct Owner {
   hipStream_t stream;
-  bool moved;   // it has been on another stream
+  bool behind;   // it queued work elsewhere that this stream is not ordered after
 };
 
 struct DeviceBlocks {
@@ -58,8 +59,16 @@ uint64_t g_contexts = 0;   // contexts so far
 bool ordered(const DeviceBlocks* d, uint64_t owner, hh_ctx c) {
   if (owner == IDLE || owner == c->mem) return true;
   const auto a = d->contexts.find(owner), b = d->contexts.find(c->mem);
-  return a != d->contexts.end() && b != d->contexts.end() && !a->second.moved &&
-         !b->second.moved && a->second.stream == b->second.stream;
+  return a != d->contexts.end() && b != d->contexts.end() && !a->second.behind &&
+         a->second.stream == b->second.stream;
+}
+
+// Also where the runtime cannot say (the null stream while another one is captured).
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
 }
 
 std::mutex g_mu;
@@ -181,12 +190,42 @@ void devmem_grant(int dev, size_t bytes) {
   if (d) d->limit = std::max(d->limit, std::min(bytes, d->most));
 }
 
+// A stream in capture runs nothing and cannot wait for work outside: it is ordered
+// after nothing, its replays by whoever launches them. The streams left out then, and
+// one that is captured itself now, are waited for by a later stream.
 void devmem_restream(hh_ctx ctx, hipStream_t stream) {
+  if (stream == ctx->stream) return;
+  std::vector<hipStream_t> left;
+  ctx->behind.push_back(ctx->stream);
+  if (capturing(stream)) {
+    left = ctx->behind;
+  } else {
+    for (hipStream_t s : ctx->behind) {
+      if (s == stream) continue;
+      if (capturing(s)) {
+        left.push_back(s);
+      } else if (hipEventRecord(ctx->fork, s) != hipSuccess ||
+                 hipStreamWaitEvent(stream, ctx->fork, 0) != hipSuccess) {
+        (void)hipGetLastError();   // a stream that is gone: its work was the device's
+        HIP_OK(hipDeviceSynchronize());
+      }
+    }
+  }
+  ctx->behind = left;
+  ctx->stream = stream;
   std::lock_guard<std::mutex> lock(g_mu);
   DeviceBlocks* d = device_blocks(ctx->device);
   if (!d) return;
   const auto c = d->contexts.find(ctx->mem);
-  if (c != d->contexts.end()) c->second = Owner{stream, true};
+  if (c != d->contexts.end()) c->second = Owner{stream, !left.empty()};
+}
+
+bool devmem_wait(hh_ctx ctx) {
+  bool ok = hipStreamSynchronize(ctx->stream) == hipSuccess;
+  for (hipStream_t s : ctx->behind) ok &= hipStreamSynchronize(s) == hipSuccess;
+  if (!ok) ok = hipDeviceSynchronize() == hipSuccess;
+  (void)hipGetLastError();
+  return ok;
 }
 
 void devmem_detach(hh_ctx ctx, bool waited) {

@@ -61,8 +61,10 @@ struct DevBuf {
 // caller's budget, which the kept blocks may fill.
 size_t devmem_attach(hh_ctx ctx);
 void devmem_grant(int dev, size_t bytes);
-void devmem_restream(hh_ctx ctx, hipStream_t stream);   // the context leaves its stream
 void devmem_detach(hh_ctx ctx, bool waited);
+// The context goes on on another stream, behind all that it queued so far.
+void devmem_restream(hh_ctx ctx, hipStream_t stream);
+bool devmem_wait(hh_ctx ctx);   // for all that it queued; false: not possible
 
 struct PhaseRec {
   int phase;
@@ -78,7 +80,7 @@ struct hh_ctx_s {
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
   uint64_t mem = 0;          // its number in devmem, 0: not counted there
-  bool restreamed = false;   // the stream was replaced
+  std::vector<hipStream_t> behind;   // earlier streams that `stream` is not ordered after
   std::string last_error;
   DevBuf scratch_flag;   // small device scratch for readbacks (64 x int64)
   int64_t* pinned = nullptr;  // host pinned mirror for readbacks (64 x int64)

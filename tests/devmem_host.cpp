@@ -113,6 +113,20 @@ hipError_t hipStreamSynchronize(hipStream_t s) {
   model::host_knows(model::tail(s));
   return hipSuccess;
 }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* cs) {
+  *cs = model::streams[s].capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  if (model::streams[s].capturing) model::fault("an event outside the graph in a capture");
+  model::events[e] = model::tail(s);
+  return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+  if (model::streams[s].capturing) model::fault("a wait for work outside the graph in a capture");
+  model::merge(model::streams[s].knows, model::events[e]);
+  return hipSuccess;
+}
 hipError_t hipDeviceSynchronize(void) {
   model::Clock c;
   for (auto& s : model::streams)
@@ -136,18 +150,13 @@ static hh_ctx_s* context(hipStream_t s, int device = 0) {
 }
 static void destroy(hh_ctx_s* c) {
   model::current = c->device;
-  bool waited = hipStreamSynchronize(c->stream) == hipSuccess;
-  if (c->restreamed) waited = hipDeviceSynchronize() == hipSuccess;
+  const bool waited = devmem_wait(c);
   if (model::after_wait) model::after_wait();
   model::after_wait = nullptr;
   devmem_detach(c, waited);
   delete c;
 }
-static void set_stream(hh_ctx_s* c, hipStream_t s) {
-  c->restreamed = true;
-  c->stream = s;
-  devmem_restream(c, s);
-}
+static void set_stream(hh_ctx_s* c, hipStream_t s) { devmem_restream(c, s); }
 
 // Another thread frees a buffer with work queued while a context is destroyed, between
 // that context's wait and the return of its blocks; a third stream allocates. With two
@@ -169,6 +178,56 @@ static void destroy_race(bool same_stream) {
   b.release();
   destroy(y);
   destroy(z);
+}
+
+// A buffer made on one stream, used on another after the context went there, and freed:
+// neither a second context on the first stream nor the same one back there may be
+// ahead of that use.
+static void restream() {
+  hipStream_t A = stream(1), B = stream(2);
+  hh_ctx_s *x = context(A), *y = context(A);
+  DevBuf a, b, c;
+  a.alloc(x, 4096);
+  use(a, A);
+  set_stream(x, B);
+  use(a, B);
+  a.release();
+  b.alloc(y, 4096);
+  use(b, A);
+  b.release();
+  set_stream(x, A);
+  c.alloc(x, 4096);
+  use(c, A);
+  c.release();
+  destroy(x);
+  destroy(y);
+}
+
+// The same through a stream in capture: nothing is ordered in it, and the stream after
+// it comes behind the one before it.
+static void restream_capture() {
+  hipStream_t A = stream(1), S = stream(2), B = stream(3);
+  hh_ctx_s *x = context(A), *y = context(B);
+  DevBuf a, b, c;
+  a.alloc(x, 4096);
+  use(a, A);
+  model::streams[S].capturing = true;
+  set_stream(x, S);
+  a.release();
+  b.alloc(y, 4096);
+  use(b, B);
+  b.release();
+  model::streams[S].capturing = false;
+  set_stream(x, B);
+  c.alloc(y, 4096);
+  use(c, B);
+  b.alloc(x, 4096);
+  use(b, B);
+  b.release();
+  c.release();
+  set_stream(x, S);
+  destroy(x);
+  destroy(y);
 }
 
 // A context's own blocks come back to it at once, to another context on its stream,
@@ -205,6 +264,8 @@ int main(int argc, char** argv) {
   const std::string s = argc > 1 ? argv[1] : "";
   if (s == "destroy_same_stream") destroy_race(true);
   else if (s == "destroy_restreamed") destroy_race(false);
+  else if (s == "restream") restream();
+  else if (s == "restream_capture") restream_capture();
   else if (s == "reuse") reuse();
   else return 2;
   if (model::bad == 0) printf("ok\n");

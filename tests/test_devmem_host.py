@@ -17,7 +17,8 @@ def model(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["destroy_same_stream", "destroy_restreamed", "reuse"])
+@pytest.mark.parametrize("scenario", ["destroy_same_stream", "destroy_restreamed", "reuse",
+                                      "restream", "restream_capture"])
 def test_scenario(model, scenario):
     r = subprocess.run([model, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "ok\n", r.stdout + r.stderr
