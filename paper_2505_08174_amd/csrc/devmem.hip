@@ -55,10 +55,10 @@ struct DeviceBlocks {
 };
 uint64_t g_contexts = 0;   // contexts so far
 
-// Whether the work of context `owner`'s blocks is ahead of what context c queues.
-bool ordered(const DeviceBlocks* d, uint64_t owner, hh_ctx c) {
-  if (owner == IDLE || owner == c->mem) return true;
-  const auto a = d->contexts.find(owner), b = d->contexts.find(c->mem);
+// Whether the work of context `owner`'s blocks is ahead of what context `next` queues.
+bool ordered(const DeviceBlocks* d, uint64_t owner, uint64_t next) {
+  if (owner == IDLE || owner == next) return true;
+  const auto a = d->contexts.find(owner), b = d->contexts.find(next);
   return a != d->contexts.end() && b != d->contexts.end() && !a->second.behind &&
          a->second.stream == b->second.stream;
 }
@@ -84,6 +84,25 @@ size_t size_class(size_t n) {
   return (n + step - 1) / step * step;
 }
 
+// Returns kept blocks above the limit, the largest first, in the stream order of the
+// context that released the last one: its own and those ordered ahead of it. That
+// order holds whichever device is current (handles are freed from any thread, also by
+// a garbage collector), and nothing waits.
+void trim(DeviceBlocks* d, uint64_t owner) {
+  const auto c = d->contexts.find(owner);
+  if (c == d->contexts.end() || c->second.behind || capturing(c->second.stream)) return;
+  for (auto it = d->free.end(); d->kept > d->limit && it != d->free.begin();) {
+    std::vector<Block>& v = (--it)->second;
+    for (size_t i = v.size(); i-- > 0 && d->kept > d->limit;) {
+      if (!ordered(d, v[i].owner, owner)) continue;
+      (void)hipFreeAsync(v[i].p, c->second.stream);
+      d->kept -= it->first;
+      v.erase(v.begin() + i);
+    }
+    if (v.empty()) it = d->free.erase(it);
+  }
+}
+
 // Returns every kept block to the runtime. The device is idle afterwards.
 void give_back(DeviceBlocks* d) {
   (void)hipDeviceSynchronize();
@@ -107,16 +126,7 @@ void DevBuf::release() {
     // (a context that is gone was waited for)
     d->free[bytes].push_back(Block{p, d->contexts.count(owner) ? owner : IDLE});
     d->kept += bytes;
-    if (d->kept > d->limit) {
-      (void)hipDeviceSynchronize();
-      while (d->kept > d->limit && !d->free.empty()) {
-        auto it = std::prev(d->free.end());
-        (void)hipFreeAsync(it->second.back().p, nullptr);
-        d->kept -= it->first;
-        it->second.pop_back();
-        if (it->second.empty()) d->free.erase(it);
-      }
-    }
+    if (d->kept > d->limit) trim(d, owner);
   }
   p = nullptr;
   bytes = 0;
@@ -146,7 +156,7 @@ void DevBuf::alloc(hh_ctx ctx, size_t nbytes) {
     for (auto it = d->free.lower_bound(c); it != d->free.end() && it->first <= c + c / 4; ++it) {
       std::vector<Block>& v = it->second;
       for (size_t i = v.size(); i-- > 0;) {
-        if (!ordered(d, v[i].owner, ctx)) continue;
+        if (!ordered(d, v[i].owner, owner)) continue;
         p = v[i].p;
         bytes = it->first;
         v.erase(v.begin() + i);

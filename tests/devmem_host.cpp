@@ -230,6 +230,30 @@ static void restream_capture() {
   destroy(y);
 }
 
+// Above the limit the largest blocks go back to the runtime, with kernels that use them
+// still queued and another device current; those of a context elsewhere stay.
+static void trim_other_device() {
+  hipStream_t S = stream(1), T = stream(2), V = stream(3, 1);
+  hh_ctx_s *x = context(S), *y = context(T), *z = context(V, 1);
+  const size_t big = (size_t)14 << 20;   // the limit is 25.6 MiB
+  DevBuf a, b, c;
+  a.alloc(y, big);
+  use(a, T);
+  b.alloc(x, big);
+  use(b, S);
+  c.alloc(x, 4096);
+  use(c, S);
+  model::current = 1;
+  a.release();
+  b.release();
+  c.release();
+  if (model::live[0] > model::total * 4 / 10) model::fault("more is kept than the limit");
+  destroy(x);
+  destroy(y);
+  destroy(z);
+  if (model::live[0] + model::live[1] != 0) model::fault("memory is left after the last context");
+}
+
 // A context's own blocks come back to it at once, to another context on its stream,
 // and to any once it was destroyed: no allocation after the first.
 static void reuse() {
@@ -266,6 +290,7 @@ int main(int argc, char** argv) {
   else if (s == "destroy_restreamed") destroy_race(false);
   else if (s == "restream") restream();
   else if (s == "restream_capture") restream_capture();
+  else if (s == "trim_other_device") trim_other_device();
   else if (s == "reuse") reuse();
   else return 2;
   if (model::bad == 0) printf("ok\n");

@@ -18,7 +18,7 @@ def model(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["destroy_same_stream", "destroy_restreamed", "reuse",
-                                      "restream", "restream_capture"])
+                                      "restream", "restream_capture", "trim_other_device"])
 def test_scenario(model, scenario):
     r = subprocess.run([model, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "ok\n", r.stdout + r.stderr
