@@ -21,8 +21,10 @@
 // 280 GB and a factor pool above 115 GB, the pool was mapped anew in every other
 // step, 3.9 s of a 4.2 s training step at 200,000 particles), and everything is
 // returned when the last context on the device is destroyed or when an
-// allocation fails. One lock per process: contexts may live in any thread.
+// allocation fails. Contexts may live in any thread: one lock per device, not held
+// while the runtime allocates.
 #include <algorithm>
+#include <atomic>
 #include <map>
 #include <mutex>
 #include <vector>
@@ -49,11 +51,12 @@ struct Owner {
 };
 
 struct DeviceBlocks {
+  std::mutex mu;
   std::map<size_t, std::vector<Block>> free;
   std::map<uint64_t, Owner> contexts;   // the living ones by number
   size_t kept = 0, limit = 0, most = 0;
 };
-uint64_t g_contexts = 0;   // contexts so far
+std::atomic<uint64_t> g_contexts{0};   // contexts so far
 
 // Whether the work of context `owner`'s blocks is ahead of what context `next` queues.
 bool ordered(const DeviceBlocks* d, uint64_t owner, uint64_t next) {
@@ -71,7 +74,6 @@ bool capturing(hipStream_t s) {
   return true;
 }
 
-std::mutex g_mu;
 // never destroyed: handles may be freed while the process ends
 DeviceBlocks* device_blocks(int dev) {
   static DeviceBlocks* all = new DeviceBlocks[MAX_DEVICES];
@@ -103,31 +105,64 @@ void trim(DeviceBlocks* d, uint64_t owner) {
   }
 }
 
-// Returns every kept block to the runtime. The device is idle afterwards.
-void give_back(DeviceBlocks* d) {
-  (void)hipDeviceSynchronize();
-  for (auto& c : d->free)
-    for (Block& b : c.second) (void)hipFreeAsync(b.p, nullptr);
-  d->free.clear();
-  d->kept = 0;
-  (void)hipStreamSynchronize(nullptr);
+// Returns kept blocks to the runtime through stream s, which is waited for: those of
+// no living context, and those of the contexts whose stream can be waited for.
+void give_back(DeviceBlocks* d, hipStream_t s) {
+  if (capturing(s)) return;   // a graph would record the frees
+  std::map<uint64_t, bool> done;
+  for (auto& c : d->contexts)
+    done[c.first] = !c.second.behind && !capturing(c.second.stream) &&
+                    hipStreamSynchronize(c.second.stream) == hipSuccess;
+  for (auto it = d->free.begin(); it != d->free.end();) {
+    std::vector<Block>& v = it->second;
+    for (size_t i = v.size(); i-- > 0;) {
+      if (v[i].owner == LOST || (v[i].owner != IDLE && !done[v[i].owner])) continue;
+      (void)hipFreeAsync(v[i].p, s);
+      d->kept -= it->first;
+      v.erase(v.begin() + i);
+    }
+    it = v.empty() ? d->free.erase(it) : std::next(it);
+  }
+  (void)hipStreamSynchronize(s);
   (void)hipGetLastError();
+}
+
+bool keep(DeviceBlocks* d, void* p, size_t bytes, uint64_t owner) {
+  if (!d) return false;
+  std::lock_guard<std::mutex> lock(d->mu);
+  if (d->contexts.empty()) return false;
+  // (a context that is gone was waited for)
+  d->free[bytes].push_back(Block{p, d->contexts.count(owner) ? owner : IDLE});
+  d->kept += bytes;
+  if (d->kept > d->limit) trim(d, owner);
+  return true;
+}
+
+// A kept block of class c, or of the next ones up to a quarter more memory, for a
+// buffer of context `owner`: its size, 0 without one.
+size_t take_kept(DeviceBlocks* d, size_t c, uint64_t owner, void** p) {
+  if (!d) return 0;
+  std::lock_guard<std::mutex> lock(d->mu);
+  for (auto it = d->free.lower_bound(c); it != d->free.end() && it->first <= c + c / 4; ++it) {
+    std::vector<Block>& v = it->second;
+    for (size_t i = v.size(); i-- > 0;) {
+      if (!ordered(d, v[i].owner, owner)) continue;
+      const size_t bytes = it->first;
+      *p = v[i].p;
+      v.erase(v.begin() + i);
+      d->kept -= bytes;
+      if (v.empty()) d->free.erase(it);
+      return bytes;
+    }
+  }
+  return 0;
 }
 
 }  // namespace
 
 void DevBuf::release() {
   if (!p) return;
-  std::lock_guard<std::mutex> lock(g_mu);
-  DeviceBlocks* d = device_blocks(dev);
-  if (!d || d->contexts.empty()) {
-    (void)hipFreeAsync(p, s);
-  } else {
-    // (a context that is gone was waited for)
-    d->free[bytes].push_back(Block{p, d->contexts.count(owner) ? owner : IDLE});
-    d->kept += bytes;
-    if (d->kept > d->limit) trim(d, owner);
-  }
+  if (!keep(device_blocks(dev), p, bytes, owner)) (void)hipFreeAsync(p, s);
   p = nullptr;
   bytes = 0;
 }
@@ -149,27 +184,16 @@ void DevBuf::alloc(hh_ctx ctx, size_t nbytes) {
   s = ctx->stream;
   dev = ctx->device;
   const size_t c = size_class(nbytes);
-  std::lock_guard<std::mutex> lock(g_mu);
   DeviceBlocks* d = device_blocks(dev);
-  if (d) {
-    // the class itself, or the next ones up to a quarter more memory
-    for (auto it = d->free.lower_bound(c); it != d->free.end() && it->first <= c + c / 4; ++it) {
-      std::vector<Block>& v = it->second;
-      for (size_t i = v.size(); i-- > 0;) {
-        if (!ordered(d, v[i].owner, owner)) continue;
-        p = v[i].p;
-        bytes = it->first;
-        v.erase(v.begin() + i);
-        d->kept -= bytes;
-        if (v.empty()) d->free.erase(it);
-        return;
-      }
-    }
-  }
+  bytes = take_kept(d, c, owner, &p);
+  if (bytes > 0) return;
   hipError_t e = hipMallocAsync(&p, c, s);
-  if (e != hipSuccess && d && d->kept > 0) {
+  if (e != hipSuccess && d) {
     (void)hipGetLastError();
-    give_back(d);
+    {
+      std::lock_guard<std::mutex> lock(d->mu);
+      give_back(d, s);
+    }
     e = hipMallocAsync(&p, c, s);
   }
   if (e != hipSuccess) {
@@ -182,22 +206,24 @@ void DevBuf::alloc(hh_ctx ctx, size_t nbytes) {
 }
 
 size_t devmem_attach(hh_ctx ctx) {
-  std::lock_guard<std::mutex> lock(g_mu);
   DeviceBlocks* d = device_blocks(ctx->device);
   size_t fr = 0, tot = 0;
   HIP_OK(hipMemGetInfo(&fr, &tot));
   if (!d) return fr;
+  std::lock_guard<std::mutex> lock(d->mu);
   if (d->contexts.empty()) d->limit = (size_t)(KEEP_SHARE * (double)tot);
   d->most = (size_t)(KEEP_MOST * (double)tot);
-  d->contexts[++g_contexts] = Owner{ctx->stream, false};
-  ctx->mem = g_contexts;
+  const uint64_t number = ++g_contexts;
+  d->contexts[number] = Owner{ctx->stream, false};
+  ctx->mem = number;
   return fr + d->kept;
 }
 
 void devmem_grant(int dev, size_t bytes) {
-  std::lock_guard<std::mutex> lock(g_mu);
   DeviceBlocks* d = device_blocks(dev);
-  if (d) d->limit = std::max(d->limit, std::min(bytes, d->most));
+  if (!d) return;
+  std::lock_guard<std::mutex> lock(d->mu);
+  d->limit = std::max(d->limit, std::min(bytes, d->most));
 }
 
 // A stream in capture runs nothing and cannot wait for work outside: it is ordered
@@ -223,9 +249,9 @@ void devmem_restream(hh_ctx ctx, hipStream_t stream) {
   }
   ctx->behind = left;
   ctx->stream = stream;
-  std::lock_guard<std::mutex> lock(g_mu);
   DeviceBlocks* d = device_blocks(ctx->device);
   if (!d) return;
+  std::lock_guard<std::mutex> lock(d->mu);
   const auto c = d->contexts.find(ctx->mem);
   if (c != d->contexts.end()) c->second = Owner{stream, !left.empty()};
 }
@@ -239,11 +265,12 @@ bool devmem_wait(hh_ctx ctx) {
 }
 
 void devmem_detach(hh_ctx ctx, bool waited) {
-  std::lock_guard<std::mutex> lock(g_mu);
   DeviceBlocks* d = device_blocks(ctx->device);
-  if (!d || !d->contexts.erase(ctx->mem)) return;
+  if (!d) return;
+  std::lock_guard<std::mutex> lock(d->mu);
+  if (!d->contexts.erase(ctx->mem)) return;
   for (auto& c : d->free)
     for (Block& b : c.second)
       if (b.owner == ctx->mem) b.owner = waited ? IDLE : LOST;
-  if (d->contexts.empty()) give_back(d);
+  if (d->contexts.empty()) give_back(d, ctx->stream);
 }

@@ -9,9 +9,14 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <unistd.h>
+
+#include <chrono>
 #include <functional>
+#include <future>
 #include <map>
-#include <set>
+#include <memory>
+#include <thread>
 
 #include "../paper_2505_08174_amd/csrc/devmem.hip"
 
@@ -34,6 +39,25 @@ std::map<hipEvent_t, Clock> events;
 int current = 0, bad = 0, mallocs = 0;
 size_t live[2] = {0, 0}, total = (size_t)64 << 20;
 std::function<void()> after_wait;   // another thread, between a wait of this one and what follows
+
+std::function<void()> other;   // what another thread does while the runtime is busy
+void fault(const char* what);
+void meanwhile() {
+  if (!other) return;
+  auto f = other;
+  other = nullptr;
+  auto done = std::make_shared<std::promise<void>>();
+  std::thread([f, done] {
+    f();
+    done->set_value();
+  }).detach();
+  if (done->get_future().wait_for(std::chrono::seconds(10)) != std::future_status::ready) {
+    fault("another device's thread has to wait");
+    printf("\n");
+    fflush(stdout);
+    _exit(1);
+  }
+}
 
 void fault(const char* what) {
   printf("%s\n", what);
@@ -94,6 +118,7 @@ hipError_t hipMemGetInfo(size_t* fr, size_t* tot) {
 const char* hipGetErrorString(hipError_t) { return "error"; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipMallocAsync(void** p, size_t n, hipStream_t s) {
+  model::meanwhile();
   const int dev = s ? model::streams[s].device : model::current;
   if (model::live[dev] + n > model::total) return hipErrorOutOfMemory;
   static uintptr_t next = 1 << 20;
@@ -110,6 +135,7 @@ hipError_t hipFreeAsync(void* p, hipStream_t s) {
   return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t s) {
+  model::meanwhile();
   model::host_knows(model::tail(s));
   return hipSuccess;
 }
@@ -128,6 +154,7 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
   return hipSuccess;
 }
 hipError_t hipDeviceSynchronize(void) {
+  model::meanwhile();
   model::Clock c;
   for (auto& s : model::streams)
     if (s.second.device == model::current) model::merge(c, model::tail(s.first));
@@ -254,6 +281,42 @@ static void trim_other_device() {
   if (model::live[0] + model::live[1] != 0) model::fault("memory is left after the last context");
 }
 
+// While one device's thread allocates, and while it returns its kept blocks after a
+// failed allocation, which waits for their work, another device's thread allocates and
+// frees; and the failed allocation succeeds then.
+static void other_device_goes_on() {
+  hipStream_t S = stream(1), T = stream(2), V = stream(3, 1);
+  hh_ctx_s *x = context(S), *y = context(T), *z = context(V, 1);
+  DevBuf a, b, c, d;
+  a.alloc(z, 4096);
+  const auto step = [&] {
+    d.alloc(z, 4096);
+    d.release();
+  };
+  a.release();
+  model::current = 0;
+  model::other = step;
+  b.alloc(x, (size_t)20 << 20);
+  use(b, S);
+  b.release();
+  b.alloc(y, (size_t)20 << 20);
+  use(b, T);
+  model::other = nullptr;
+  model::mallocs = 0;
+  hipMallocAsync(&a.p, 20 << 20, S);   // the caller's own memory
+  model::other = step;
+  c.alloc(y, (size_t)24 << 20);
+  use(c, T);
+  if (model::other) model::fault("no allocation failed");
+  hipFreeAsync(a.p, S);
+  a.p = nullptr;
+  for (DevBuf* f : {&b, &c}) f->release();
+  destroy(x);
+  destroy(y);
+  destroy(z);
+  if (model::live[0] + model::live[1] != 0) model::fault("memory is left after the last context");
+}
+
 // A context's own blocks come back to it at once, to another context on its stream,
 // and to any once it was destroyed: no allocation after the first.
 static void reuse() {
@@ -291,6 +354,7 @@ int main(int argc, char** argv) {
   else if (s == "restream") restream();
   else if (s == "restream_capture") restream_capture();
   else if (s == "trim_other_device") trim_other_device();
+  else if (s == "other_device_goes_on") other_device_goes_on();
   else if (s == "reuse") reuse();
   else return 2;
   if (model::bad == 0) printf("ok\n");
