@@ -39,6 +39,9 @@ constexpr double KEEP_SHARE = 0.4, KEEP_MOST = 0.75;
 // Owners of kept blocks besides the contexts' numbers.
 constexpr uint64_t IDLE = 0;               // nothing queued uses it any more
 constexpr uint64_t LOST = ~(uint64_t)0;    // of a context that could not be waited for
+// Of a buffer that was allocated while its stream was captured: the memory belongs to
+// the graph, is there during its replays only, and is not kept.
+constexpr uint64_t GRAPH = LOST - 1;
 
 struct Block {
   void* p;
@@ -128,7 +131,7 @@ void give_back(DeviceBlocks* d, hipStream_t s) {
 }
 
 bool keep(DeviceBlocks* d, void* p, size_t bytes, uint64_t owner) {
-  if (!d) return false;
+  if (!d || owner == GRAPH) return false;
   std::lock_guard<std::mutex> lock(d->mu);
   if (d->contexts.empty()) return false;
   // (a context that is gone was waited for)
@@ -187,6 +190,7 @@ void DevBuf::alloc(hh_ctx ctx, size_t nbytes) {
   DeviceBlocks* d = device_blocks(dev);
   bytes = take_kept(d, c, owner, &p);
   if (bytes > 0) return;
+  if (capturing(s)) owner = GRAPH;
   hipError_t e = hipMallocAsync(&p, c, s);
   if (e != hipSuccess && d) {
     (void)hipGetLastError();

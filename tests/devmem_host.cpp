@@ -30,7 +30,7 @@ struct Stream {
 struct Mem {
   size_t bytes;
   int device;
-  bool freed = false;
+  bool freed = false, graph = false;   // graph: allocated in a capture
   Clock uses;   // last item of each stream that uses it
 };
 std::map<hipStream_t, Stream> streams = {{nullptr, Stream{}}};   // and the null stream
@@ -88,6 +88,7 @@ bool pending(const Mem& m, hipStream_t s) {
 void use(const DevBuf& b, hipStream_t s) {
   Mem& m = mem[b.p];
   if (m.freed) fault("use of freed memory");
+  if (m.graph && !streams[s].capturing) fault("a graph's memory is used outside it");
   if (pending(m, s)) fault("a block is used on a stream that its earlier work is not ahead of");
   m.uses[s] = ++streams[s].items;
 }
@@ -120,10 +121,11 @@ hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipMallocAsync(void** p, size_t n, hipStream_t s) {
   model::meanwhile();
   const int dev = s ? model::streams[s].device : model::current;
+  const bool graph = model::streams[s].capturing;
   if (model::live[dev] + n > model::total) return hipErrorOutOfMemory;
   static uintptr_t next = 1 << 20;
   *p = (void*)(next += 256);
-  model::mem[*p] = model::Mem{n, dev, false, {}};
+  model::mem[*p] = model::Mem{n, dev, false, graph, {}};
   model::live[dev] += n;
   ++model::mallocs;
   return hipSuccess;
@@ -317,6 +319,25 @@ static void other_device_goes_on() {
   if (model::live[0] + model::live[1] != 0) model::fault("memory is left after the last context");
 }
 
+// A buffer allocated in a capture (the first product of a handle, recorded) is not
+// handed out after it.
+static void graph_memory() {
+  hipStream_t S = stream(1), G = stream(2);
+  hh_ctx_s* x = context(S);
+  DevBuf a, b;
+  model::streams[G].capturing = true;
+  set_stream(x, G);
+  a.alloc(x, 4096);
+  use(a, G);
+  model::streams[G].capturing = false;
+  set_stream(x, S);
+  a.release();
+  b.alloc(x, 4096);
+  use(b, S);
+  b.release();
+  destroy(x);
+}
+
 // A context's own blocks come back to it at once, to another context on its stream,
 // and to any once it was destroyed: no allocation after the first.
 static void reuse() {
@@ -355,6 +376,7 @@ int main(int argc, char** argv) {
   else if (s == "restream_capture") restream_capture();
   else if (s == "trim_other_device") trim_other_device();
   else if (s == "other_device_goes_on") other_device_goes_on();
+  else if (s == "graph_memory") graph_memory();
   else if (s == "reuse") reuse();
   else return 2;
   if (model::bad == 0) printf("ok\n");
