@@ -134,8 +134,12 @@ bool keep(DeviceBlocks* d, void* p, size_t bytes, uint64_t owner) {
   if (!d || owner == GRAPH) return false;
   std::lock_guard<std::mutex> lock(d->mu);
   if (d->contexts.empty()) return false;
-  // (a context that is gone was waited for)
-  d->free[bytes].push_back(Block{p, d->contexts.count(owner) ? owner : IDLE});
+  try {
+    // (a context that is gone was waited for)
+    d->free[bytes].push_back(Block{p, d->contexts.count(owner) ? owner : IDLE});
+  } catch (const std::bad_alloc&) {   // no host memory for the list
+    return false;
+  }
   d->kept += bytes;
   if (d->kept > d->limit) trim(d, owner);
   return true;

@@ -37,6 +37,7 @@ std::map<hipStream_t, Stream> streams = {{nullptr, Stream{}}};   // and the null
 std::map<void*, Mem> mem;
 std::map<hipEvent_t, Clock> events;
 int current = 0, bad = 0, mallocs = 0;
+bool no_host_memory = false;
 size_t live[2] = {0, 0}, total = (size_t)64 << 20;
 std::function<void()> after_wait;   // another thread, between a wait of this one and what follows
 
@@ -100,6 +101,14 @@ void drop(void* p, hipStream_t s, bool wait) {
   live[m.device] -= m.bytes;
 }
 }  // namespace model
+
+void* operator new(size_t n) {
+  void* p = model::no_host_memory ? nullptr : malloc(n);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
 
 // ------------------------------------------------------------ the runtime calls
 extern "C" {
@@ -186,6 +195,21 @@ static void destroy(hh_ctx_s* c) {
   delete c;
 }
 static void set_stream(hh_ctx_s* c, hipStream_t s) { devmem_restream(c, s); }
+
+// No host memory for the lists while a buffer is freed (handles are freed by calls that
+// cannot report an error): nothing is thrown, and the memory goes back.
+static void no_host_memory() {
+  hipStream_t S = stream(1);
+  hh_ctx_s* x = context(S);
+  DevBuf a;
+  a.alloc(x, 4096);
+  use(a, S);
+  model::no_host_memory = true;
+  a.release();
+  model::no_host_memory = false;
+  if (model::live[0] != 0) model::fault("the buffer's memory is lost");
+  destroy(x);
+}
 
 // Another thread frees a buffer with work queued while a context is destroyed, between
 // that context's wait and the return of its blocks; a third stream allocates. With two
@@ -377,6 +401,7 @@ int main(int argc, char** argv) {
   else if (s == "trim_other_device") trim_other_device();
   else if (s == "other_device_goes_on") other_device_goes_on();
   else if (s == "graph_memory") graph_memory();
+  else if (s == "no_host_memory") no_host_memory();
   else if (s == "reuse") reuse();
   else return 2;
   if (model::bad == 0) printf("ok\n");
