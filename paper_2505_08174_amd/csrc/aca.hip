@@ -1253,10 +1253,7 @@ void plan_aca(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, int force_streame
   std::vector<int32_t> cs, qs;
   block_sizes(ctx, t, p, cs, qs);
   const size_t es = lr->prec == HH_FP64 ? 8 : 4;
-  // est decides between stored and streamed factors (20 terms a block). The first
-  // pool takes the terms that the tolerance suggests (20 at 1e-4, more below it),
-  // or every block's worst case where that is no more than a GiB: an ACA that
-  // overflows its pool runs again as a whole.
+  // est decides between stored and streamed factors (20 terms a block)
   const int rank_guess =
       (int)std::min<double>(lr->l_max, std::max(20.0, -5.0 * log10(std::max(lr->eps, 1e-30))));
   int64_t est = 0, guess = 0, worst = 0;
@@ -1275,9 +1272,7 @@ void plan_aca(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, int force_streame
       arena = std::max(arena, 9 * cq * kc);
     }
   }
-  lr->pool_first = (double)worst * es <= (double)(1ll << 30)
-                       ? worst
-                       : std::max(est, std::min(guess, (int64_t)(0.5 * (double)ctx->budget_bytes / es)));
+  lr->pool_first = first_pool(est, guess, worst, es, ctx->budget_bytes);
   lr->streamed = force_streamed || (double)est * es > 0.5 * (double)ctx->budget_bytes;
   std::vector<int32_t> ord;
   ord.reserve(std::max<int64_t>(nG, 1));

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -268,6 +269,18 @@ void read_bytes(hh_ctx ctx, void* host, const void* dev, size_t bytes);
 void scan_exclusive_i64(hh_ctx ctx, const int64_t* in, int64_t* out, int64_t n);
 // Stable LSD radix sort of (key, value) pairs by the low `bits` bits of key.
 void radix_sort_u64(hh_ctx ctx, uint64_t* keys, uint32_t* vals, int64_t n, int bits);
+
+// Elements of es bytes of the factor pool that a stored ACA starts with, from the sums
+// over its blocks of 20 terms (est), of the terms that the tolerance suggests (guess:
+// 20 at 1e-4, more below it) and of the worst case. An ACA that overflows its pool
+// runs again as a whole, so every block's worst case is taken where that is no more
+// than a GiB; neither it nor the guess goes past half of the budget, which is where
+// est ends stored factors.
+inline int64_t first_pool(int64_t est, int64_t guess, int64_t worst, size_t es, size_t budget) {
+  const int64_t half = (int64_t)(0.5 * (double)budget / (double)es);
+  if (worst <= std::min(half, (int64_t)((1ll << 30) / es))) return worst;
+  return std::max(est, std::min(guess, half));
+}
 
 // Near-field launches (near.hip, near_mfma.hip). The near field of a row is
 // the sum of `groups` partial rows, out[g][n][3], in FP64 when the sources are
