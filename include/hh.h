@@ -65,7 +65,11 @@ typedef enum {
 /* Arithmetic of the kernel evaluation, factors and sums.
  *   HH_FP64 : F, U, factors and all sums in FP64.
  *   HH_FP32 : F, U, kernel evaluation and factors in FP32; ACA pivots and
- *             stopping norms in FP64 (as in every form).
+ *             stopping norms in FP64 (as in every form). The seeded-MLP near
+ *             field contracts its FP32 values on the FP16 matrix units, weights
+ *             as three FP16 numbers (no bit of the FP32 value is lost) and
+ *             activations as two (23 to 24 bits), with FP32 accumulation; its
+ *             error is that of FP32 products or less.
  *   HH_BF16 : seeded-MLP layers in BF16 on MFMA with FP32 accumulation; ACA
  *             pivot selection and stopping norms in FP64; factors FP32; the
  *             final velocity sum in FP64. F is FP32 and U is FP64. The ACA

@@ -269,7 +269,7 @@ static uint16_t f16_rne(double v, double& hi) {
   return (uint16_t)(sign | (uint16_t)((u >> 42) - ((uint64_t)(1023 - 15) << 10)));
 }
 
-// Table of the two-part FP16 MLP (layout in mlp_mfma.h), 16 bytes per fragment:
+// Table of the MLP in FP16 parts (layout in mlp_mfma.h), 16 bytes per fragment:
 // layer 1 in FP32, then the row factors and the FP16 parts of layers 2-4.
 static std::vector<uint32_t> build_x2_frags(const double* P0) {
   std::vector<uint32_t> fr((size_t)X2_TOTAL * 4, 0);
@@ -301,13 +301,13 @@ static std::vector<uint32_t> build_x2_frags(const double* P0) {
         const int lane = m % 32 + 32 * hf;
         for (int s = 0; s < 4; ++s)
           for (int u = 0; u < 8; ++u) {
-            const double v = scaled(W[MLP_H * m + kslot_feature(s, hf, u)]);
-            const double lo = put((mo * 4 + s) * 2, lane, u, v);
-            put((mo * 4 + s) * 2 + 1, lane, u, lo);
+            double rest = scaled(W[MLP_H * m + kslot_feature(s, hf, u)]);
+            for (int part = 0; part < 3; ++part)
+              rest = put((mo * 4 + s) * 3 + part, lane, u, rest);
           }
       }
       double rest = scaled(b[m]);
-      for (int u = 0; u < 3; ++u) rest = put(nmo * 8 + mo, m % 32, u, rest);
+      for (int u = 0; u < 3; ++u) rest = put(nmo * 12 + mo, m % 32, u, rest);
     }
   };
   const double S = 2.0 / log(2.0);

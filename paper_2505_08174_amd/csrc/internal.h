@@ -126,7 +126,7 @@ struct hh_kernel_s {
   DevBuf p32;                       // MLP params FP32, packed
   DevBuf pbf;                       // MLP params for the BF16 MFMA path
   DevBuf pf32;                      // MLP params for the FP32 MFMA path (fragment table)
-  DevBuf px2;                       // MLP params as two FP16 parts (FP32 near field)
+  DevBuf px2;                       // MLP params in FP16 parts (FP32 near field)
   DevBuf pf32t;                     // transposed weights for the FP32 MFMA backward
 };
 

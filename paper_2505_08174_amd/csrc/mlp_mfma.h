@@ -455,33 +455,37 @@ __device__ __forceinline__ void stage_frags_f32(float* __restrict__ lds,
   for (int i = threadIdx.x; i < F32_FRAGS * 16; i += nthreads) d[i] = g[i];
 }
 
-// ------------------------------------- FP32 values on FP16 MFMA, two parts each
+// --------------------------------------------- FP32 values on FP16 MFMA, in parts
 //
 // The FP32 near field (the ACA's samples stay on the FP32 tile: factors, pivots
 // and gradients through them have to reproduce). Layers 2-4 contract operands
-// written as the sum of two FP16 numbers, x = hi + lo, on v_mfma_f32_32x32x16_f16
-// (FP32 accumulation). Two roundings to 11 bits with a sign keep 23 to 24 bits of
-// x (biases have a third part in a spare K slot), the products W_hi a_hi +
-// W_hi a_lo + W_lo a_hi are exact, and the one left out, W_lo a_lo, is below 2^-24
+// written as sums of FP16 numbers on v_mfma_f32_32x32x16_f16 (FP32 accumulation).
+// An activation is hi + lo: two roundings to 11 bits with a sign keep 23 to 24 bits.
+// A weight has three parts, 33 bits and more, so no bit of its FP32 value is lost (and
+// so has a bias, in spare K slots): its error is common to all pairs and does not
+// average out of a sum as an activation's does. The products W1 a_hi + W1 a_lo +
+// W2 a_hi + W3 a_hi are exact, and the largest one left out, W2 a_lo, is below 2^-24
 // of the product. Nothing may fall under FP16's range: activations are carried
 // times 2^10, and every row of weights (its bias with it) times the power of two
 // that takes its largest entry to [2^14, 2^15); one multiplication with the row's
 // factor gives the FP32 result back. The small products are summed before the
 // large ones, so a result has 5 roundings at full size (the FP32 tile: 66, one per
-// K step). Measured against 64 bits with Glorot-uniform networks, relative rms:
-// single entries 2.3e-7 (FP32 tile 2.8e-7); sums over 1,500 sources with random
-// forces 1.9e-7 (2.2e-7), with equal forces 1.1e-7 (1.0e-7; all networks tried,
-// weights times 0.3 to 3 and both input modes: 0.95e-7, 0.97e-7).
+// K step). Measured against 64 bits over 654 networks and sizes (both inputs, Glorot
+// weights times 0.3, 1 and 3, 2 to 6,000 sources), geometric mean of the ratio to the
+// FP32 tile's error: single entries 0.84, sums with random forces 0.86, with gravity
+// 0.86, with equal forces 0.86. With weights in two parts the last one was 0.98, and
+// 1.04 to 1.12 over 500 and more sources: more than FP32, so the third part is not
+// optional. It costs an eighth of the near field (31.3 -> 35.0 ms at 60,000 particles).
 //
 // Layer 1 (3 -> 64) is the FP32 tile's. The operand layout is the BF16 tile's.
-// Cost per 32 pairs: 65 FP16 and 4 FP32 MFMAs (2,340 cycles; the FP32 tile
+// Cost per 32 pairs: 85 FP16 and 4 FP32 MFMAs (2,980 cycles; the FP32 tile
 // 10,800) next to 6,144 activations of 9 issue slots each (3,460 cycles).
 #define X2_L1 0                                    // 4 x 64 floats = 4 x 16 fragments
 #define X2_SC (X2_L1 + 4 * 16)                     // row factors of layers 2-4: 3 x 64 floats
-#define X2_L2 (X2_SC + 3 * 16)                     // [mo 2][s 4][part 2][lane]; bias [mo 2][lane]
-#define X2_L3 (X2_L2 + (2 * 4 * 2 + 2) * 64)
-#define X2_L4 (X2_L3 + (2 * 4 * 2 + 2) * 64)       // [s 4][part 2][lane]; bias [lane]
-#define X2_TOTAL (X2_L4 + (4 * 2 + 1) * 64)
+#define X2_L2 (X2_SC + 3 * 16)                     // [mo 2][s 4][part 3][lane]; bias [mo 2][lane]
+#define X2_L3 (X2_L2 + (2 * 4 * 3 + 2) * 64)
+#define X2_L4 (X2_L3 + (2 * 4 * 3 + 2) * 64)       // [s 4][part 3][lane]; bias [lane]
+#define X2_TOTAL (X2_L4 + (4 * 3 + 1) * 64)
 #define X2_ACT 1024.0f                             // activations are carried times this
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -516,19 +520,21 @@ __device__ __forceinline__ void layer_x2(const uint4* __restrict__ fr, int base,
                                          const f16x8 (&Bl)[NT][4], const f16x8& bone,
                                          f32x16 (&acc)[NT]) {
   auto w = [&](int s, int part) {
-    return __builtin_bit_cast(f16x8, fr[base + ((mo * 4 + s) * 2 + part) * 64 + lane]);
+    return __builtin_bit_cast(f16x8, fr[base + ((mo * 4 + s) * 3 + part) * 64 + lane]);
   };
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = f32x16{};
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    const f16x8 wh = w(s, 0), wl = w(s, 1);
+    const f16x8 wh = w(s, 0), wl = w(s, 1), wt = w(s, 2);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = mfma_f16(wt, Bh[t][s], acc[t]);
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = mfma_f16(wl, Bh[t][s], acc[t]);
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = mfma_f16(wh, Bl[t][s], acc[t]);
   }
-  const f16x8 wb = __builtin_bit_cast(f16x8, fr[base + nmo * 8 * 64 + mo * 64 + lane]);
+  const f16x8 wb = __builtin_bit_cast(f16x8, fr[base + nmo * 12 * 64 + mo * 64 + lane]);
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc[t] = mfma_f16(wb, bone, acc[t]);
 #pragma unroll

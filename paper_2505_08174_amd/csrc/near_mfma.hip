@@ -1,5 +1,5 @@
 // Near field with the seeded MLP kernel on MFMA tiles (the BF16 and the plain
-// FP32 form, the latter on two FP16 parts per FP32 value).
+// FP32 form, the latter on FP16 parts of FP32 values).
 //
 // A wave works on 64 consecutive targets (sorted rows, whichever leaves they
 // are in), one per lane: in every step a lane takes the next source of its own
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(NEAR_WG) void k_near_bf16(NearB a) {
   write_rows(reinterpret_cast<double*>(fr), lane, w, u, s0, a.t.n, set, a.out);
 }
 
-// The plain FP32 form: the same walk, tiles of FP32 values in two FP16 parts. F is
+// The plain FP32 form: the same walk, tiles of FP32 values in FP16 parts. F is
 // FP32; each lane sums its target's terms in FP64.
 template <class TO>
 struct NearF {
