@@ -7,10 +7,11 @@
 // to, one atomic per wave and list. The order of visits does not change the
 // resulting sets, which are sorted by (tau, sigma) at the end. A level finds the
 // size of its frontier on the device, so levels are launched eight at a time
-// between readbacks; a list that would outgrow its buffer is counted on, and the
-// walk starts again with larger ones. (Classification, three scans of three
-// launches each, emission and a readback per level took 1.9 ms at 2,000 particles
-// and 5.8 ms at 250,000; this walk and its sorts take 0.22 and 1.3 ms.)
+// between readbacks. A level whose lists outgrow their buffers counts on, the levels
+// after it do nothing, and that one level is run again with larger buffers.
+// (Classification, three scans of three launches each, emission and a readback per
+// level took 1.9 ms at 2,000 particles and 5.8 ms at 250,000; this walk and its sorts
+// take 0.22 and 1.3 ms.)
 //
 // Eq. (7) on tight bounding boxes: diam^2 = (dx*dx + dy*dy) + dz*dz, the gap
 // per axis g = max(0, lo_s - hi_t, lo_t - hi_s), dist^2 = (gx*gx + gy*gy) +
@@ -40,8 +41,9 @@ __device__ __forceinline__ double dist2(const double* t, const double* s) {
   return (g[0] * g[0] + g[1] * g[1]) + g[2] * g[2];
 }
 
-// Appends v of the lanes with on set to list (cap entries; counted past it).
-__device__ __forceinline__ void append(bool on, int2 v, int2* __restrict__ list,
+// Appends v of the lanes with on set to list behind its `base` entries (cap entries;
+// counted past it).
+__device__ __forceinline__ void append(bool on, int2 v, int2* __restrict__ list, int64_t base,
                                        unsigned long long* __restrict__ cnt, int64_t cap) {
   const uint64_t m = __ballot(on);
   if (m == 0) return;
@@ -49,21 +51,44 @@ __device__ __forceinline__ void append(bool on, int2 v, int2* __restrict__ list,
   unsigned long long p0 = 0;
   if (lane == lead) p0 = atomicAdd(cnt, (unsigned long long)__popcll(m));
   p0 = __shfl(p0, lead, 64);
-  const int64_t p = (int64_t)p0 + __popcll(m & (lane == 0 ? 0ull : (~0ull >> (64 - lane))));
+  const int64_t p = base + (int64_t)p0 + __popcll(m & (lane == 0 ? 0ull : (~0ull >> (64 - lane))));
   if (on && p < cap) list[p] = v;
 }
 
-// cnt: [0] P^G, [1] P^H, [2 + l] the frontier of level l
-__global__ __launch_bounds__(T256) void k_level(const int2* __restrict__ fr, int level,
-                                                const int4* __restrict__ nodes,
-                                                const double* __restrict__ bbox, double eta2,
-                                                int dense_mode,
-                                                unsigned long long* __restrict__ cnt,
-                                                int2* __restrict__ G, int64_t capG,
-                                                int2* __restrict__ H, int64_t capH,
-                                                int2* __restrict__ next, int64_t capF) {
-  const int64_t nf = min((int64_t)cnt[2 + level], capF);
-  unsigned long long* nn = cnt + 3 + level;
+// One level of the walk. The host knows the lists up to level0: their entries in
+// P^G and P^H and the frontier of level0. cnt[3 l + 0, 1, 2]: what level l adds to P^G,
+// P^H and the frontier of level l + 1, final for the levels before this one.
+constexpr int BATCH = 8;   // levels between readbacks
+struct Walk {
+  const int4* nodes;
+  const double* bbox;
+  double eta2;
+  int dense_mode, level0;
+  int64_t nG, nH, nF;
+  unsigned long long* cnt;
+  int2 *G, *H, *fr[2];   // fr[l & 1]: the frontier of level l
+  int64_t capG, capH, capF[2];
+};
+
+__global__ __launch_bounds__(T256) void k_level(Walk a, int level) {
+  int64_t gb = a.nG, hb = a.nH, nf = a.nF;
+  bool again = false;   // an earlier level outgrew its lists
+#pragma unroll
+  for (int k = 0; k < BATCH - 1; ++k) {   // loads of all counters in flight at once
+    const int l = min(a.level0 + k, max(level - 1, 0));
+    const int64_t g = a.cnt[3 * l], h = a.cnt[3 * l + 1], f = a.cnt[3 * l + 2];
+    if (a.level0 + k < level) {
+      gb += g;
+      hb += h;
+      nf = f;
+      again |= gb > a.capG || hb > a.capH || nf > a.capF[(l + 1) & 1];
+    }
+  }
+  if (again) return;
+  const int2* __restrict__ fr = a.fr[level & 1];
+  int2* __restrict__ next = a.fr[(level + 1) & 1];
+  const int64_t capF = a.capF[(level + 1) & 1];
+  unsigned long long* c = a.cnt + 3 * level;
   const int64_t step = (int64_t)gridDim.x * T256;
   for (int64_t i0 = (int64_t)blockIdx.x * T256; i0 < nf; i0 += step) {
     const int64_t i = i0 + threadIdx.x;
@@ -73,23 +98,23 @@ __global__ __launch_bounds__(T256) void k_level(const int2* __restrict__ fr, int
     bool adm = false;
     if (act) {
       b = fr[i];
-      nt = nodes[b.x];
-      ns = nodes[b.y];
-      if (!dense_mode) {
-        const double* bt = bbox + 6 * (int64_t)b.x;
-        const double* bs = bbox + 6 * (int64_t)b.y;
+      nt = a.nodes[b.x];
+      ns = a.nodes[b.y];
+      if (!a.dense_mode) {
+        const double* bt = a.bbox + 6 * (int64_t)b.x;
+        const double* bs = a.bbox + 6 * (int64_t)b.y;
         const double d2 = dist2(bt, bs);
-        adm = d2 > 0.0 && fmax(diam2(bt), diam2(bs)) <= eta2 * d2;
+        adm = d2 > 0.0 && fmax(diam2(bt), diam2(bs)) <= a.eta2 * d2;
       }
     }
     const bool lt = nt.z < 0, ls = ns.z < 0;
     const bool split = act && !adm && !(lt && ls);
-    append(act && adm, b, G, cnt, capG);
-    append(act && !adm && lt && ls, b, H, cnt + 1, capH);
-    append(split, make_int2(lt ? b.x : nt.z, ls ? b.y : ns.z), next, nn, capF);
-    append(split, make_int2(lt ? b.x : nt.w, ls ? b.y : ns.w), next, nn, capF);
-    append(split && !lt && !ls, make_int2(nt.z, ns.w), next, nn, capF);
-    append(split && !lt && !ls, make_int2(nt.w, ns.z), next, nn, capF);
+    append(act && adm, b, a.G, gb, c, a.capG);
+    append(act && !adm && lt && ls, b, a.H, hb, c + 1, a.capH);
+    append(split, make_int2(lt ? b.x : nt.z, ls ? b.y : ns.z), next, 0, c + 2, capF);
+    append(split, make_int2(lt ? b.x : nt.w, ls ? b.y : ns.w), next, 0, c + 2, capF);
+    append(split && !lt && !ls, make_int2(nt.z, ns.w), next, 0, c + 2, capF);
+    append(split && !lt && !ls, make_int2(nt.w, ns.z), next, 0, c + 2, capF);
   }
 }
 
@@ -181,7 +206,7 @@ __global__ void k_roots_frontier(const int32_t* __restrict__ roots, int nsys,
                                  int ncnt) {
   int s = blockIdx.x * 256 + threadIdx.x;
   if (s < nsys) fr[s] = make_int2(roots[s], roots[s]);
-  if (s < ncnt) cnt[s] = s == 2 ? (unsigned long long)nsys : 0ull;
+  if (s < ncnt) cnt[s] = 0;
 }
 
 }  // namespace
@@ -219,53 +244,74 @@ hh_status hh_partition(hh_ctx ctx, hh_tree tree, double eta, int dense_mode, hh_
     double eta2 = eta * eta;
     // Algorithm 1 starts at (I, I) for every independent system. Room for the
     // lists of the workloads (112 admissible and 41 inadmissible blocks per node
-    // at 1M particles), more where a walk needs it.
-    constexpr int MAX_LEVELS = 200, BATCH = 8, NCNT = 2 + MAX_LEVELS + 1;
+    // at 1M particles), more where a level needs it; in dense mode the lists of one
+    // system are known (up to a GiB each here).
+    constexpr int MAX_LEVELS = 200, NCNT = 3 * MAX_LEVELS;
     const int nsys = tree->n_sys;
-    const int64_t m = tree->n_nodes;
-    int64_t capG = 160 * m + 1024, capH = 64 * m + 1024;
-    int64_t capF = std::max<int64_t>(160 * m + 1024, nsys);
-    DevBuf G, H, f0, f1, cnt;
+    const int64_t m = tree->n_nodes, nl = tree->n_leaves;
+    const int64_t all = dense_mode && nsys == 1 ? std::min<int64_t>(nl * nl, 1 << 27) : 0;
+    DevBuf G, H, f[2], cnt;
     cnt.alloc(ctx, NCNT * sizeof(unsigned long long));
     std::vector<int64_t> c(NCNT);
-    const unsigned grid = (unsigned)std::min<int64_t>(4 * (int64_t)ctx->n_cu, nblk(capF));
-    bool done = false;
-    while (!done) {
-      G.ensure(ctx, capG * sizeof(int2));
-      H.ensure(ctx, capH * sizeof(int2));
-      f0.ensure(ctx, capF * sizeof(int2));
-      f1.ensure(ctx, capF * sizeof(int2));
-      hipLaunchKernelGGL(k_roots_frontier, dim3((std::max(nsys, NCNT) + 255) / 256), dim3(256), 0,
-                         st, tree->roots.as<int32_t>(), nsys, f0.as<int2>(),
-                         cnt.as<unsigned long long>(), NCNT);
-      bool grow = false;
-      for (int level = 0; !done && !grow;) {
-        for (int e = std::min(level + BATCH, MAX_LEVELS); level < e; ++level)
-          hipLaunchKernelGGL(k_level, dim3(grid), dim3(T256), 0, st,
-                             (level & 1 ? f1 : f0).as<int2>(), level, nodes, bbox, eta2, dense_mode,
-                             cnt.as<unsigned long long>(), G.as<int2>(), capG, H.as<int2>(), capH,
-                             (level & 1 ? f0 : f1).as<int2>(), capF);
-        HIP_OK(hipGetLastError());
-        read_bytes(ctx, c.data(), cnt.p, NCNT * sizeof(int64_t));
-        int64_t fmax = 0;
-        for (int l = 0; l <= level; ++l) fmax = std::max(fmax, c[2 + l]);
-        HH_REQUIRE(c[0] < (1ll << 31) && c[1] < (1ll << 31) && fmax < (1ll << 31),
-                   HH_ERR_CAPACITY, "block lists exceed 2^31 entries");
-        grow = c[0] > capG || c[1] > capH || fmax > capF;
-        done = !grow && c[2 + level] == 0;
-        HH_REQUIRE(done || grow || level < MAX_LEVELS, HH_ERR_CAPACITY,
-                   "partition deeper than 200 levels");
-      }
-      if (grow) {
-        // counts past a full frontier are those of a part of the walk
-        if (c[0] > capG) capG = std::max(2 * capG, c[0] + c[0] / 4);
-        if (c[1] > capH) capH = std::max(2 * capH, c[1] + c[1] / 4);
-        for (int l = 0; l <= MAX_LEVELS; ++l)
-          if (c[2 + l] > capF) capF = std::max(2 * capF, c[2 + l] + c[2 + l] / 4);
+    Walk w = {};
+    w.nodes = nodes;
+    w.bbox = bbox;
+    w.eta2 = eta2;
+    w.dense_mode = dense_mode;
+    w.cnt = cnt.as<unsigned long long>();
+    w.capG = all > 0 ? 1 : 160 * m + 1024;
+    w.capH = std::max<int64_t>(all, 64 * m + 1024);
+    w.capF[0] = w.capF[1] = std::max<int64_t>({160 * m + 1024, nsys, all});
+    G.alloc(ctx, w.capG * sizeof(int2));
+    H.alloc(ctx, w.capH * sizeof(int2));
+    for (int i = 0; i < 2; ++i) {
+      f[i].alloc(ctx, w.capF[i] * sizeof(int2));
+      w.fr[i] = f[i].as<int2>();
+    }
+    hipLaunchKernelGGL(k_roots_frontier, dim3((std::max(nsys, NCNT) + 255) / 256), dim3(256), 0,
+                       st, tree->roots.as<int32_t>(), nsys, w.fr[0], w.cnt, NCNT);
+    // room for `need` entries of a list that holds `has`
+    auto grow = [&](DevBuf& list, int64_t& cap, int64_t has, int64_t need) {
+      if (need <= cap) return;
+      cap = std::max(2 * cap, need + need / 4);
+      DevBuf old;
+      old.take(list);
+      list.alloc(ctx, cap * sizeof(int2));
+      if (has > 0)
+        HIP_OK(hipMemcpyAsync(list.p, old.p, has * sizeof(int2), hipMemcpyDeviceToDevice, st));
+    };
+    for (w.nF = nsys; w.nF > 0;) {
+      HH_REQUIRE(w.level0 < MAX_LEVELS, HH_ERR_CAPACITY, "partition deeper than 200 levels");
+      w.G = G.as<int2>();
+      w.H = H.as<int2>();
+      for (int i = 0; i < 2; ++i) w.fr[i] = f[i].as<int2>();
+      const unsigned grid = (unsigned)std::min<int64_t>(
+          4 * (int64_t)ctx->n_cu, nblk(std::max(w.capF[0], w.capF[1])));
+      const int end = std::min(w.level0 + BATCH, MAX_LEVELS);
+      for (int l = w.level0; l < end; ++l)
+        hipLaunchKernelGGL(k_level, dim3(grid), dim3(T256), 0, st, w, l);
+      HIP_OK(hipGetLastError());
+      const int l0 = w.level0;
+      read_bytes(ctx, c.data() + 3 * l0, w.cnt + 3 * l0, 3 * (end - l0) * sizeof(int64_t));
+      for (; w.level0 < end && w.nF > 0; ++w.level0) {
+        const int l = w.level0, o = (l + 1) & 1;
+        const int64_t ng = w.nG + c[3 * l], nh = w.nH + c[3 * l + 1], nf = c[3 * l + 2];
+        HH_REQUIRE(ng < (1ll << 31) && nh < (1ll << 31) && nf < (1ll << 31), HH_ERR_CAPACITY,
+                   "block lists exceed 2^31 entries");
+        if (ng > w.capG || nh > w.capH || nf > w.capF[o]) {
+          grow(G, w.capG, w.nG, ng);
+          grow(H, w.capH, w.nH, nh);
+          grow(f[o], w.capF[o], 0, nf);
+          zero_words(ctx, w.cnt + 3 * l, 3);
+          break;
+        }
+        w.nG = ng;
+        w.nH = nh;
+        w.nF = nf;
       }
     }
-    p->nG = c[0];
-    p->nH = c[1];
+    p->nG = w.nG;
+    p->nH = w.nH;
     p->G.alloc(ctx, std::max<int64_t>(1, p->nG) * sizeof(int2));
     p->H.alloc(ctx, std::max<int64_t>(1, p->nH) * sizeof(int2));
     int nb = 1;
