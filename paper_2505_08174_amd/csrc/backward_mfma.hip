@@ -382,10 +382,10 @@ __device__ __forceinline__ void items_scan(int seqs, int64_t n, Tiles tiles,
 }
 
 __global__ __launch_bounds__(SEQ_MAX) void k_near_items(int seqs, const int2* __restrict__ units,
-                                                        int64_t n_units,
+                                                        const int64_t* __restrict__ n_units,
                                                         const int32_t* __restrict__ near_q,
                                                         int64_t* __restrict__ pre) {
-  items_scan(seqs, n_units, [&](int64_t u) { return (int64_t)near_q[units[u].x]; }, pre);
+  items_scan(seqs, *n_units, [&](int64_t u) { return (int64_t)near_q[units[u].x]; }, pre);
 }
 
 __device__ __forceinline__ int64_t block_tiles(const int2* __restrict__ G,
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(VB) void k_near_vjp_f32(VjpArgs a, const int32_t* _
                                                      const int4* __restrict__ src,
                                                      const int32_t* __restrict__ near_q,
                                                      const int2* __restrict__ units,
-                                                     int64_t n_units,
+                                                     const int64_t* __restrict__ unit_count,
                                                      const int64_t* __restrict__ pre, int seqs,
                                                      const float* __restrict__ Fs,
                                                      const float* __restrict__ ws) {
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(VB) void k_near_vjp_f32(VjpArgs a, const int32_t* _
   const float c8 = (float)(1.0 / (8.0 * HH_PI));
   VjpAcc A;
   acc_zero(A);
-  const int64_t items = pre[seqs];
+  const int64_t items = pre[seqs], n_units = *unit_count;
   for (int64_t it = wave; it < items; it += nw) {
     const int v = item_seq(pre, seqs, it);
     int64_t skip = FLUSH * (it - pre[v]);   // tiles of the sequence before this item
@@ -641,14 +641,16 @@ static VjpArgs vjp_args(hh_tree t, hh_kernel k, double* dXs, double* slots) {
 // pre: vjp_f32_waves + 1 int64 of scratch.
 void launch_near_vjp_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const float* Fs,
                          const float* ws, double* dXs, double* slots, int64_t* pre) {
-  ensure_units(ctx, t);
+  DevBuf units, pos;
+  build_units(ctx, t, units, pos);
+  const int64_t* n_units = pos.as<int64_t>() + t->n_leaves;
   const VjpArgs a = vjp_args(t, k, dXs, slots);
   const int seqs = (int)vjp_f32_waves(ctx);
   hipLaunchKernelGGL(k_near_items, dim3(1), dim3(SEQ_MAX), 0, ctx->stream, seqs,
-                     t->units.as<int2>(), t->n_units, p->near_q.as<int32_t>(), pre);
+                     units.as<int2>(), n_units, p->near_q.as<int32_t>(), pre);
   hipLaunchKernelGGL(k_near_vjp_f32, dim3((unsigned)(seqs / 4)), dim3(VB), 0, ctx->stream, a,
                      t->leaves.as<int32_t>(), p->near_ptr.as<int32_t>(), p->near_src.as<int4>(),
-                     p->near_q.as<int32_t>(), t->units.as<int2>(), t->n_units, pre, seqs, Fs, ws);
+                     p->near_q.as<int32_t>(), units.as<int2>(), n_units, pre, seqs, Fs, ws);
   HIP_OK(hipGetLastError());
 }
 

@@ -160,8 +160,6 @@ struct hh_tree_s {
   DevBuf leaf_id;   // int32 [n_nodes] rank among leaves, -1 for internal
   DevBuf leaves;    // int32 [n_leaves] node id of each leaf, in order
   DevBuf leaf_of;   // int32 [n] leaf node of sorted position s
-  DevBuf units;     // int2 [n_units] (leaf rank, chunk of 32 targets), built by the first FP32 backward
-  int64_t n_units = 0;
   int n_sys = 1;                    // independent systems (batched build)
   std::vector<int64_t> offs_host;   // particle offsets of the systems [n_sys+1]
   DevBuf offs;                      // same, on the device
@@ -308,6 +306,6 @@ void launch_near_vjp_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const fl
 void launch_far_vjp_f32(hh_ctx ctx, hh_tree t, hh_part p, hh_lowrank lr, hh_kernel k,
                         int64_t b0, int64_t b1, const int64_t* goff, const float* gpool,
                         double* dXs, double* slots, int64_t* pre);
-void ensure_units(hh_ctx ctx, hh_tree t);
+void build_units(hh_ctx ctx, hh_tree t, DevBuf& units, DevBuf& pos);
 void launch_aca(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, hh_lowrank lr, double eps,
                 int32_t l_max, int64_t* pool_top_dev);

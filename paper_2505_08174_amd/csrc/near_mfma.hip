@@ -159,25 +159,23 @@ __global__ __launch_bounds__(NEAR_WG) void k_near_f32(NearF<TO> a) {
 
 }  // namespace
 
-// Work units of the FP32 backward (leaf rank, chunk of 32 targets), built once per
-// tree.
-void ensure_units(hh_ctx ctx, hh_tree t) {
-  if (t->n_units > 0) return;
+// Work units of the FP32 backward (leaf rank, chunk of 32 targets): int2 units, their
+// number is pos[n_leaves]. Made by each call for itself: a tree may be in use on other
+// streams and in other threads.
+void build_units(hh_ctx ctx, hh_tree t, DevBuf& units, DevBuf& pos) {
   hipStream_t st = ctx->stream;
   int64_t nl = t->n_leaves;
-  DevBuf cnt, pos;
+  DevBuf cnt;
   cnt.alloc(ctx, (nl + 1) * sizeof(int64_t));
   pos.alloc(ctx, (nl + 1) * sizeof(int64_t));
+  units.alloc(ctx, (t->n / 32 + nl) * sizeof(int2));   // no leaf leaves more than one chunk unfilled
   unsigned g = (unsigned)((nl + 1 + T256_UNITS - 1) / T256_UNITS);
   hipLaunchKernelGGL(k_units_count, dim3(g), dim3(T256_UNITS), 0, st, t->leaves.as<int32_t>(), nl,
                      t->nodes.as<int4>(), cnt.as<int64_t>());
   scan_exclusive_i64(ctx, cnt.as<int64_t>(), pos.as<int64_t>(), nl + 1);
-  int64_t nu = read_i64(ctx, pos.as<int64_t>() + nl);
-  t->units.alloc(ctx, std::max<int64_t>(1, nu) * sizeof(int2));
   hipLaunchKernelGGL(k_units_fill, dim3(g), dim3(T256_UNITS), 0, st, cnt.as<int64_t>(),
-                     pos.as<int64_t>(), nl, t->units.as<int2>());
+                     pos.as<int64_t>(), nl, units.as<int2>());
   HIP_OK(hipGetLastError());
-  t->n_units = nu;
 }
 
 // A share of 32 sources takes some 100 us, staging a workgroup's 48 KB of weights
