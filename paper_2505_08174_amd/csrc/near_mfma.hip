@@ -85,8 +85,9 @@ __global__ __launch_bounds__(NEAR_WG) void k_near_bf16(NearB a) {
 #pragma unroll 1
   for (int st = 0; st < steps; ++st) {
     float rx = (float)(xi0 - xj0), ry = (float)(xi1 - xj1), rz = (float)(xi2 - xj2);
-    const float f0 = g0, f1 = g1, f2 = g2;
-    const bool skip = wk.j == ss || !act || wk.left <= 0;
+    const bool none = wk.left <= 0;   // the lane's share has ended: not its last source again
+    const float f0 = none ? 0.0f : g0, f1 = none ? 0.0f : g1, f2 = none ? 0.0f : g2;
+    const bool skip = wk.j == ss || !act || none;
     if (wk.j == ss) { rx = 1.0f; ry = 0.0f; rz = 0.0f; }
     // which of two equally good remainders layer 1 gets (see pair_rest): fixed
     // by the list alone, whatever the split of the sources
@@ -144,8 +145,10 @@ __global__ __launch_bounds__(NEAR_WG) void k_near_f32(NearF<TO> a) {
     float rx = a.sgn * (float)(xi0 - a.t.xs[3 * j]);
     float ry = a.sgn * (float)(xi1 - a.t.xs[3 * j + 1]);
     float rz = a.sgn * (float)(xi2 - a.t.xs[3 * j + 2]);
-    const float f0 = a.Fs[3 * j], f1 = a.Fs[3 * j + 1], f2 = a.Fs[3 * j + 2];
-    const bool skip = wk.j == ss || !act || wk.left <= 0;
+    const bool none = wk.left <= 0;   // the lane's share has ended: not its last source again
+    const float g0 = a.Fs[3 * j], g1 = a.Fs[3 * j + 1], g2 = a.Fs[3 * j + 2];
+    const float f0 = none ? 0.0f : g0, f1 = none ? 0.0f : g1, f2 = none ? 0.0f : g2;
+    const bool skip = wk.j == ss || !act || none;
     if (wk.j == ss) { rx = 1.0f; ry = 0.0f; rz = 0.0f; }
     const PairIn in = pair_in(a.input_mode, rx, ry, rz, false);
     float q[9];
