@@ -45,7 +45,7 @@ CU, CLK = 256, 2.4e9
 KERNEL_SOURCES = {"k_aca": ["aca.hip", "wave.h", "mlp_mfma.h", "devmath.h", "internal.h"],
                   "k_near": ["near_mfma.hip", "near.hip", "near_walk.h", "mlp_mfma.h", "devmath.h",
                              "internal.h"],
-                  "far": ["apply.hip", "internal.h"]}
+                  "far": ["apply.hip", "wave.h", "near_walk.h", "devmath.h", "internal.h"]}
 
 
 def log(*a):

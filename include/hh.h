@@ -271,10 +271,11 @@ hh_status hh_matvec(hh_ctx ctx, hh_tree tree, hh_part part, hh_lowrank lr, hh_ke
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * product of hh_matvec (same kernels, same result bit for bit) with its
  * workspaces -- the sorted forces, 3 n values, and the sets of near-field and
- * far-field rows, 3 n values each (several sets up to some 600,000 rows, for
- * which there is always room) -- in a file-scope device array of HH_NOALLOC_SCRATCH_BYTES instead of device
- * memory kept in lr; it calls no allocating routine and records no phase
- * events. Stored factors only (a streamed-mode lr -> HH_ERR_INVALID_ARG). A
+ * far-field rows, 3 n values each (on 256 compute units several sets up to 589,824
+ * rows with the MLP kernel in FP32 and BF16, 786,432 with the others: 57 MB at most,
+ * for which there is always room) -- in a file-scope device array of
+ * HH_NOALLOC_SCRATCH_BYTES instead of device memory kept in lr; it calls no
+ * allocating routine and records no phase events. Stored factors only (a streamed-mode lr -> HH_ERR_INVALID_ARG). A
  * product that needs more scratch than HH_NOALLOC_SCRATCH_BYTES (about 1.4M
  * particles in HH_FP64, 1.8M in HH_BF16, 2.8M in HH_FP32) -> HH_ERR_CAPACITY,
  * checked before anything else. Every call on a device shares that device's
@@ -293,7 +294,7 @@ hh_status hh_matvec_noalloc(hh_ctx ctx, hh_tree tree, hh_part part, hh_lowrank l
  *       d L / d theta, accumulated into (not overwritten).
  * F and dU as in hh_matvec. Precision HH_FP64 or HH_FP32; stored factors
  * only. The cotangents of the sampled kernel entries are kept for chunks of
- * consecutive blocks of at most 2^28 values (1 GiB in FP32) at a time. Syncs
+ * consecutive blocks of at most 2^31 values (8 GiB in FP32) at a time. Syncs
  * (reads back the ranks to plan those chunks). */
 hh_status hh_matvec_backward(hh_ctx ctx, hh_tree tree, hh_part part, hh_lowrank lr,
                              hh_kernel kern, hh_precision prec, const void* F, const void* dU,

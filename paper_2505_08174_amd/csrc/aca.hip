@@ -220,9 +220,9 @@ __device__ __forceinline__ void team_sync() {
     __syncthreads();
 }
 
-// Which remainder of its input a row's sample takes (pair_rest): 32-row tiles,
-// dealt to the TW waves of the team and taken in pairs; a tile left without a
-// partner takes the exact one.
+// Which remainder of its input a row's sample takes (pair_rest, where the reason
+// stands): as if 32-row tiles were dealt to the TW waves of the team and taken in
+// pairs; a tile left without a partner takes the exact one.
 template <int TW>
 __device__ __forceinline__ bool lone_tile(int i, int n) {
   const int t = i >> 5;
@@ -335,9 +335,8 @@ __device__ __forceinline__ void team_combine(TeamRed* tr, int wit, double (&v)[N
 // samples kept in registers, factor rows read through buffer resources and used
 // pivots in a bit mask, the ACA went from 415 to 374 ms at 250,000 particles
 // (BF16), from 61 to 52 ms in the 6N form (40,000), from 1.55 to 1.17 ms at 2,000
-// particles in FP64. Every wave of a team
-// computes the per-step scalars itself from the same combined values, so all
-// decisions are uniform over the team. Fused apply: u(i) += c_{k-1}(i) t_{k-1}
+// particles in FP64. Every wave of a team computes the per-step scalars itself from
+// the same combined values, so all decisions are uniform over the team. Fused apply: u(i) += c_{k-1}(i) t_{k-1}
 // rides on the next column pass (or a final pass).
 template <class T, int KIND, int MF, int TW>
 __device__ __forceinline__ void aca_worker(const AcaArgs<T>& a, const T* wl, const void* fr,

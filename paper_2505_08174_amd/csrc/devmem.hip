@@ -6,16 +6,17 @@
 // as the particles move. From hipMallocAsync each of them costs 5 + 14 us of
 // host time, and a pool that is a little larger than the freed one is mapped
 // anew: steps of 90 ms of kernels took 0.8 s, and of 0.4 s took 1.7 s. Freed
-// blocks therefore stay here, one list per size class (eight classes per
-// power of two, so a block is at most an eighth larger than asked for).
+// blocks therefore stay here, one list per size class: eight classes per power of
+// two, so a class is at most an eighth larger than what is asked for, and a kept block
+// may be a quarter larger than the class (1.41 times the request in all: a pool that
+// shrinks a little from step to step keeps its block).
 //
 // A kept block belongs to the context whose buffer it was, and a later buffer takes
 // it if the order of streams puts the block's earlier work ahead: the same context's
 // buffers (a context that changes its stream orders the new one after the old one),
 // those of another context on the same stream, and, once the context has been waited
-// for and destroyed, any. That wait
-// says nothing about another context's blocks: their work may have been queued
-// after it, by another thread. The lists of a device hold at most
+// for and destroyed, any. That wait says nothing about another context's blocks: their
+// work may have been queued after it, by another thread. The lists of a device hold at most
 // KEEP_SHARE of its memory, or the largest budget a caller granted a context up to
 // KEEP_MOST of it (the largest blocks go first: with KEEP_SHARE alone, a budget of
 // 280 GB and a factor pool above 115 GB, the pool was mapped anew in every other

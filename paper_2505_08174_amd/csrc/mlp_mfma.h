@@ -120,7 +120,10 @@ struct PairIn {
 __device__ __forceinline__ float pair_norm2(float rx, float ry, float rz) {
   return __builtin_fmaf(rz, rz, __builtin_fmaf(rx, rx, ry * ry));
 }
-// exact = true: the remainder of the unrounded product r |r|^-1, else of v.
+// exact = true: the remainder of the unrounded product r |r|^-1, else of v. Neither
+// is the better one (both are rounded to BF16 next); which one a pair takes is part of
+// what the BF16 forms have always computed (the compiler contracted one of two inlined
+// copies), and ranks and pivots that callers saved from earlier builds hang on it.
 __device__ __forceinline__ float pair_rest(float v, float r, float sc, bool exact) {
 #pragma clang fp contract(off)
   const float h = (float)(__bf16)v;

@@ -11,7 +11,7 @@
 // RPY tensor). One workgroup per leaf, which staged the sources in LDS and left
 // the rest of the chip idle at small sizes, took 800 us at 2,000 particles in
 // FP64 (32 leaves) and 5.5 ms at 60,000 in FP32 (a quarter of its lanes past
-// the leaf); this form takes 1.3 ms at 60,000, and the 6N kernel by particles
+// the leaf); this form takes 1.1 ms at 60,000, and the 6N kernel by particles
 // 0.75 ms at 40,000 particles (5.05 ms row by row).
 #include "devmath.h"
 #include "internal.h"
@@ -153,9 +153,12 @@ void launch_near_t(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, const void* Fs
 
 }  // namespace
 
-// The VALU kernels keep 4 workgroups and more on a compute unit, and a pair is
-// cheap enough that a share below 16 sources costs more in its search for the
-// first source and its partial row than it fills.
+// The RPY kernels keep 4 workgroups and more on a compute unit, and a pair is cheap
+// enough that a share below 16 sources costs more in its search for the first source
+// and its partial row than it fills. The MLP kernel in FP64 (79 KB of LDS, two
+// workgroups) takes the same split: a workgroup's 73 KB of weights are staged for 4,096
+// pairs and more, some 3 ms of work. Products, one workgroup per leaf before and this
+// split after: 700 particles 63.6 -> 1.8 ms, 2,000 194 -> 6.2, 12,000 919 -> 80 ms.
 int near_groups(hh_ctx ctx, hh_tree t, hh_part p, hh_kernel k, int prec) {
   return k->kind == KIND_MLP && prec != HH_FP64 ? near_groups_mfma(ctx, t, p)
                                                 : near_sets(ctx, t, p, 4, 32, 16);
