@@ -328,9 +328,9 @@ __device__ __forceinline__ void team_combine(TeamRed* tr, int wit, double (&v)[N
 //   nu^2 = tr(A_kk B_kk), lambda^2 += nu^2 + 2 sum_{m<k} tr(A_mk B_km).
 // So the Gram terms cost no extra pass over the factors. Raw samples never leave
 // the lane that subtracts from them, and a column of at most 128 rows stays in
-// registers up to its normalisation. Bound by VALU issue (78% busy at 250,000
+// registers up to its normalisation. Bound by VALU issue (79% busy at 250,000
 // particles in the BF16 form) and by the re-reading of the factors (3.2 TB/s
-// there, 5.4 TB/s in the 6N form, more than a large copy's rate). With the sums
+// there, 5.5 TB/s in the 6N form, more than a large copy's rate). With the sums
 // over the wave two swaps per value instead of six shuffles' worth of DPP moves,
 // samples kept in registers, factor rows read through buffer resources and used
 // pivots in a bit mask, the ACA went from 415 to 374 ms at 250,000 particles
