@@ -278,11 +278,22 @@ static std::vector<uint32_t> build_x2_frags(const double* P0) {
   memcpy(fr.data() + 4 * X2_L1, f32.data(), 4 * 64 * sizeof(float));
   float* sc = reinterpret_cast<float*>(fr.data() + 4 * X2_SC);
   uint16_t* h = reinterpret_cast<uint16_t*>(fr.data());
-  auto layer = [&](int base, float* c, const double* W, const double* b, double S, int nrow,
+  // Features that are zero whatever the input: their weights in the next layer count
+  // for nothing and must not take the row's range from the others.
+  bool dead[MLP_H], next[MLP_H];
+  for (int m = 0; m < MLP_H; ++m)
+    dead[m] = P0[OFF_B1 + m] == 0 && P0[OFF_W1 + 3 * m] == 0 && P0[OFF_W1 + 3 * m + 1] == 0 &&
+              P0[OFF_W1 + 3 * m + 2] == 0;
+  auto layer = [&](int base, float* c, const double* W0, const double* b, double S, int nrow,
                    int nmo) {
     for (int m = 0; m < nrow; ++m) {
-      double top = fabs(S * b[m]);
-      for (int f = 0; f < MLP_H; ++f) top = std::max(top, fabs(S * W[MLP_H * m + f]));
+      double W[MLP_H], top = fabs(S * b[m]);
+      next[m] = b[m] == 0;
+      for (int f = 0; f < MLP_H; ++f) {
+        W[f] = dead[f] ? 0.0 : W0[MLP_H * m + f];
+        next[m] &= W[f] == 0;
+        top = std::max(top, fabs(S * W[f]));
+      }
       int e = 1024;
       if (std::isfinite(top)) frexp(top, &e);   // top < 2^e
       // The factor 2^-(k + 10) has to be a normal FP32 number; rows above 2^152 (past
@@ -301,7 +312,7 @@ static std::vector<uint32_t> build_x2_frags(const double* P0) {
         const int lane = m % 32 + 32 * hf;
         for (int s = 0; s < 4; ++s)
           for (int u = 0; u < 8; ++u) {
-            double rest = scaled(W[MLP_H * m + kslot_feature(s, hf, u)]);
+            double rest = scaled(W[kslot_feature(s, hf, u)]);
             for (int part = 0; part < 3; ++part)
               rest = put((mo * 4 + s) * 3 + part, lane, u, rest);
           }
@@ -309,6 +320,7 @@ static std::vector<uint32_t> build_x2_frags(const double* P0) {
       double rest = scaled(b[m]);
       for (int u = 0; u < 3; ++u) rest = put(nmo * 12 + mo, m % 32, u, rest);
     }
+    memcpy(dead, next, sizeof(dead));
   };
   const double S = 2.0 / log(2.0);
   layer(X2_L2, sc, P0 + OFF_W2, P0 + OFF_B2, S, 64, 2);
