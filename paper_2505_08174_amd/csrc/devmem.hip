@@ -268,7 +268,7 @@ void devmem_restream(hh_ctx ctx, hipStream_t stream) {
 bool devmem_wait(hh_ctx ctx) {
   bool ok = hipStreamSynchronize(ctx->stream) == hipSuccess;
   for (hipStream_t s : ctx->behind) ok &= hipStreamSynchronize(s) == hipSuccess;
-  if (!ok) ok = hipDeviceSynchronize() == hipSuccess;
+  if (!ok && !capturing(ctx->stream)) ok = hipDeviceSynchronize() == hipSuccess;
   (void)hipGetLastError();
   return ok;
 }
