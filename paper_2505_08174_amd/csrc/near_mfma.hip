@@ -19,7 +19,7 @@
 // this split after: BF16, 500 particles 831 -> 25 us; BF16 hi + lo, 30,000
 // particles 28.8 -> 12.5 ms; FP32, 5,000 particles 33.1 -> 4.3 ms, 100,000
 // particles 244 -> 148 ms (76% of the FP32 MFMA rate), and with FP16 parts in
-// place of FP32 MFMA 1.7 ms and 63 ms (1.6e10 pairs/s).
+// place of FP32 MFMA 1.7 ms and 63 ms (1.27e10 pairs/s).
 #include <algorithm>
 
 #include "internal.h"
