@@ -113,7 +113,7 @@ hh_status hh_ctx_set_stream(hh_ctx ctx, void* stream);
  * admissible blocks would not fit in half of it, hh_aca_build only plans
  * and hh_matvec builds and applies them in batches of blocks whose factors
  * fit (a fixed buffer filled, applied and reused, Sec. 3.3.2). The default is
- * 40% of the free device memory at context creation. */
+ * 40% of the device memory free at context creation, kept blocks included. */
 hh_status hh_ctx_set_budget(hh_ctx ctx, size_t bytes);
 /* Work split of hh_aca_build / hh_matvec: admissible blocks with
  * c + q >= team_min (rounded up to a power of two) are approximated by a

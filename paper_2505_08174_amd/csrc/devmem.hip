@@ -186,8 +186,11 @@ void DevBuf::take(DevBuf& src) {
   src.bytes = 0;
 }
 
+static void follow(hh_ctx ctx, hipStream_t stream);
+
 void DevBuf::alloc(hh_ctx ctx, size_t nbytes) {
   release();
+  if (!ctx->behind.empty()) follow(ctx, ctx->stream);
   owner = ctx->mem;
   s = ctx->stream;
   dev = ctx->device;
@@ -237,11 +240,15 @@ void devmem_grant(int dev, size_t bytes) {
 
 // A stream in capture runs nothing and cannot wait for work outside: it is ordered
 // after nothing, its replays by whoever launches them. The streams left out then, and
-// one that is captured itself now, are waited for by a later stream.
+// one that is captured itself now, are waited for by a later stream, or by the same one
+// when it allocates after the capture.
 void devmem_restream(hh_ctx ctx, hipStream_t stream) {
   if (stream == ctx->stream) return;
-  std::vector<hipStream_t> left;
   ctx->behind.push_back(ctx->stream);
+  follow(ctx, stream);
+}
+static void follow(hh_ctx ctx, hipStream_t stream) {
+  std::vector<hipStream_t> left;
   if (capturing(stream)) {
     left = ctx->behind;
   } else {

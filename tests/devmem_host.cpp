@@ -362,6 +362,24 @@ static void graph_memory() {
   destroy(x);
 }
 
+// A context that stays on the stream after its capture: what it allocates there then
+// comes behind its work on the stream before.
+static void stay_after_capture() {
+  hipStream_t A = stream(1), S = stream(2);
+  hh_ctx_s* x = context(A);
+  DevBuf a, b;
+  a.alloc(x, 4096);
+  use(a, A);
+  model::streams[S].capturing = true;
+  set_stream(x, S);
+  a.release();
+  model::streams[S].capturing = false;
+  b.alloc(x, 4096);
+  use(b, S);
+  b.release();
+  destroy(x);
+}
+
 // A context's own blocks come back to it at once, to another context on its stream,
 // and to any once it was destroyed: no allocation after the first.
 static void reuse() {
@@ -401,6 +419,7 @@ int main(int argc, char** argv) {
   else if (s == "trim_other_device") trim_other_device();
   else if (s == "other_device_goes_on") other_device_goes_on();
   else if (s == "graph_memory") graph_memory();
+  else if (s == "stay_after_capture") stay_after_capture();
   else if (s == "no_host_memory") no_host_memory();
   else if (s == "reuse") reuse();
   else return 2;

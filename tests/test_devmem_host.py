@@ -19,7 +19,8 @@ def model(tmp_path_factory):
 
 @pytest.mark.parametrize("scenario", ["destroy_same_stream", "destroy_restreamed", "reuse",
                                       "restream", "restream_capture", "trim_other_device",
-                                      "other_device_goes_on", "graph_memory", "no_host_memory"])
+                                      "other_device_goes_on", "graph_memory", "no_host_memory",
+                                      "stay_after_capture"])
 def test_scenario(model, scenario):
     r = subprocess.run([model, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "ok\n", r.stdout + r.stderr
